@@ -8,8 +8,10 @@
 // whole run, the run's coefficients are staged once in LDS, and every
 // config writes one coalesced 512-byte row of costs and 64 bytes of depths,
 // the costs with streaming (nontemporal) stores, the depths too when their
-// runs are 64-byte aligned.  The kernel is bound by HBM writes (9 bytes per
-// candidate).
+// runs are 64-byte aligned.  Where slices repeat (equal layers) a second kernel
+// evaluates each config once per slice class and writes its rows by lookup.
+// Both are bound by HBM writes (9 bytes per candidate).
+#include <algorithm>
 #include <type_traits>
 
 #include "tg_device.h"
@@ -142,8 +144,87 @@ struct StagedCoef {
     int32_t rc, of;
 };
 
-// kExt: the space has context parallelism, recomputation or offloading
-// (two more slice sums, two more cost terms, the stash and depth rules).
+// Copies the coefficients the model reads from a config's row.
+template <bool kExt>
+__device__ inline StagedCoef stage_coef(const Coef &c) {
+    StagedCoef x;
+    x.alpha = c.alpha;
+    x.beta = c.beta;
+    x.gamma = c.gamma;
+    x.dd = c.dd;
+    x.de = c.de;
+    x.mud = c.mud;
+    x.mue = c.mue;
+    x.rho = c.rho;
+    x.H = c.H;
+    x.m_real = c.m_real;
+    x.inv_rho = c.inv_rho;
+    if (kExt) {  // read only by the extended variants
+        x.kappa = c.kappa;
+        x.omega = c.omega;
+        x.rc = c.rc;
+        x.of = c.of;
+    }
+    return x;
+}
+
+// A slice's sums: exact int64 prefix differences, then one rounding to
+// binary64.  The reciprocals only feed the depth guess.
+struct SliceSums {
+    double Fl = 0.0, Pd = 0.0, Pe = 0.0, Act = 0.0, Tb = 0.0, Ab = 0.0, inv_act = 0.0;
+    double Oa = 0.0, Cb = 0.0, inv_oa = 0.0;
+};
+
+template <bool kDense, bool kExt>
+__device__ inline SliceSums slice_sums(const DevProblem &P, uint32_t ij) {
+    SliceSums u;
+    const int i = (int)(ij & 0xFFFFu), j = (int)(ij >> 16);
+    const int64_t *pre = P.pre;
+    const int64_t Lp = P.L + 1;
+    u.Fl = (double)(pre[j] - pre[i]);
+    u.Pd = (double)(pre[Lp + j] - pre[Lp + i]);
+    u.Act = (double)(pre[3 * Lp + j] - pre[3 * Lp + i]);
+    u.Tb = (double)(pre[4 * Lp + j] - pre[4 * Lp + i]);
+    if (!kDense) {
+        u.Pe = (double)(pre[2 * Lp + j] - pre[2 * Lp + i]);
+        u.Ab = (double)(pre[5 * Lp + j] - pre[5 * Lp + i]);
+    }
+    u.inv_act = 1.0 / u.Act;
+    if (kExt) {
+        u.Oa = (double)(pre[6 * Lp + j] - pre[6 * Lp + i]);
+        u.Cb = (double)(pre[7 * Lp + j] - pre[7 * Lp + i]);
+        u.inv_oa = 1.0 / u.Oa;
+    }
+    return u;
+}
+
+// The cost and depth of one (slice, config).  kExt: the space has context
+// parallelism, recomputation or offloading (two more slice sums, two more cost
+// terms, the stash and depth rules).  Every lane of the wave calls it; `live`
+// lanes score a candidate.
+template <bool kDense, bool kExt>
+__device__ inline double score_one(const StagedCoef &c, const SliceSums &u, int K, bool live, int &dm) {
+    // with recomputation only the layer boundaries (outputs) are stashed
+    const double S = (kExt && c.rc) ? u.Oa : u.Act;
+    double v = c.alpha * u.Fl;
+    v = v + c.beta * u.Tb;
+    if (!kDense) v = v + c.gamma * u.Ab;
+    v = v + c.dd * u.Pd;
+    if (!kDense) v = v + c.de * u.Pe;
+    if (kExt) {
+        v = v + c.kappa * u.Cb;
+        v = v + c.omega * S;
+    }
+    double state = c.mud * u.Pd;
+    if (!kDense) state = state + c.mue * u.Pe;
+    const double A1 = c.rho * S;
+    if (kExt && c.of)  // offloaded: one micro-batch on the device at every depth
+        dm = (state + (fmin(1.0, c.m_real) * A1)) <= c.H ? K : 0;
+    else
+        dm = max_depth(state, A1, c.H, c.m_real, c.inv_rho * ((kExt && c.rc) ? u.inv_oa : u.inv_act), K, live);
+    return v;
+}
+
 // kNtDepth: a wave's 64 depths of a row start on a 64-byte boundary (NS a
 // multiple of 64) and go out with streaming stores like the costs; otherwise
 // the run straddles segments that the neighbouring waves also write, and
@@ -166,55 +247,13 @@ __global__ __launch_bounds__(256) void score_kernel(DevProblem P, int64_t first,
     const bool sv = s < P.NS;
     const int64_t g_beg = g_lo + gt * kCfg;
     const int ng = (int)(min(g_beg + kCfg, g_hi + 1) - g_beg);
-    if (lane < ng) {
-        const Coef &c = P.coef[g_beg + lane];
-        StagedCoef x;
-        x.alpha = c.alpha;
-        x.beta = c.beta;
-        x.gamma = c.gamma;
-        x.dd = c.dd;
-        x.de = c.de;
-        x.mud = c.mud;
-        x.mue = c.mue;
-        x.rho = c.rho;
-        x.H = c.H;
-        x.m_real = c.m_real;
-        x.inv_rho = c.inv_rho;
-        if (kExt) {  // read only by the extended variant
-            x.kappa = c.kappa;
-            x.omega = c.omega;
-            x.rc = c.rc;
-            x.of = c.of;
-        }
-        cs[wv][lane] = x;
-    }
+    if (lane < ng) cs[wv][lane] = stage_coef<kExt>(P.coef[g_beg + lane]);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-    // slice sums: exact int64 prefix differences, then one rounding to binary64
-    double Fl = 0.0, Pd = 0.0, Pe = 0.0, Act = 0.0, Tb = 0.0, Ab = 0.0, inv_act = 0.0;
-    double Oa = 0.0, Cb = 0.0, inv_oa = 0.0;
-    if (sv) {
-        const uint32_t ij = P.sij[s];
-        const int i = (int)(ij & 0xFFFFu), j = (int)(ij >> 16);
-        const int64_t *pre = P.pre;
-        const int64_t Lp = P.L + 1;
-        Fl = (double)(pre[j] - pre[i]);
-        Pd = (double)(pre[Lp + j] - pre[Lp + i]);
-        Act = (double)(pre[3 * Lp + j] - pre[3 * Lp + i]);
-        Tb = (double)(pre[4 * Lp + j] - pre[4 * Lp + i]);
-        if (!kDense) {
-            Pe = (double)(pre[2 * Lp + j] - pre[2 * Lp + i]);
-            Ab = (double)(pre[5 * Lp + j] - pre[5 * Lp + i]);
-        }
-        inv_act = 1.0 / Act;
-        if (kExt) {
-            Oa = (double)(pre[6 * Lp + j] - pre[6 * Lp + i]);
-            Cb = (double)(pre[7 * Lp + j] - pre[7 * Lp + i]);
-            inv_oa = 1.0 / Oa;
-        }
-    }
+    SliceSums u;
+    if (sv) u = slice_sums<kDense, kExt>(P, P.sij[s]);
     const int K = P.K;
     const int64_t NS = P.NS;
     // a tile wholly inside [first, last) with a slice for every lane stores
@@ -222,28 +261,8 @@ __global__ __launch_bounds__(256) void score_kernel(DevProblem P, int64_t first,
     const int64_t t0 = g_beg * NS + st * kWave;
     const bool whole = (st + 1) * kWave <= NS && t0 >= first && t0 + (int64_t)(ng - 1) * NS + (kWave - 1) < last;
     for (int t = 0; t < ng; ++t) {
-        const StagedCoef &c = cs[wv][t];
-        // with recomputation only the layer boundaries (outputs) are stashed
-        const double S = (kExt && c.rc) ? Oa : Act;
-        double v = c.alpha * Fl;
-        v = v + c.beta * Tb;
-        if (!kDense) v = v + c.gamma * Ab;
-        v = v + c.dd * Pd;
-        if (!kDense) v = v + c.de * Pe;
-        if (kExt) {
-            v = v + c.kappa * Cb;
-            v = v + c.omega * S;
-        }
-        double state = c.mud * Pd;
-        if (!kDense) state = state + c.mue * Pe;
-        const double A1 = c.rho * S;
         int dm;
-        if (kExt && c.of) {
-            // offloaded: one micro-batch on the device at every depth
-            dm = (state + (fmin(1.0, c.m_real) * A1)) <= c.H ? K : 0;
-        } else {
-            dm = max_depth(state, A1, c.H, c.m_real, c.inv_rho * ((kExt && c.rc) ? inv_oa : inv_act), K, sv);
-        }
+        const double v = score_one<kDense, kExt>(cs[wv][t], u, K, sv, dm);
         if (whole) {
             const int64_t row = t0 + (int64_t)t * NS - first;
             __builtin_nontemporal_store(v, cost + row + lane);
@@ -265,11 +284,220 @@ __global__ __launch_bounds__(256) void score_kernel(DevProblem P, int64_t first,
     }
 }
 
+// ---------------------------------------------------------------------------
+// scoring where slices repeat
+// ---------------------------------------------------------------------------
+// Slices with equal sums score alike under every config, and a model of equal
+// layers has L classes among its L (L + 1) / 2 slices.  A block takes a run of
+// configs, evaluates the model once per (config, class) into LDS and writes
+// the run's rows, one contiguous range of candidates, by looking each slice's
+// class up: the fp64 model (the general kernel issues 44 VALU instructions a
+// candidate) leaves the per-candidate path, which is two LDS reads and its
+// share of a 16-byte store (streaming for the costs).  The rows are written as
+// one range, so every store is aligned whatever NS is: costs two to a thread, then depths
+// sixteen to a thread.  Bound by HBM writes: what is left is their order.
+// Consecutive runs go to one XCD and a run is kept short (kClassRun), so that
+// each XCD writes a compact moving window, as a plain fill does: back to back
+// on the 128-layer instance (1.10e9 candidates) runs of 66,000 candidates dealt
+// round-robin over the XCDs took 1.97 ms, runs of 8,256 in XCD order 1.67 ms
+// (5.9 TB/s; a kernel that only writes these bytes reaches 6.1).  Inside the
+// plan search, general kernel -> this one: 128 layers 1868 -> 1673 us, 70B 109
+// -> 92, extended 70B 718 -> 643, MoE 73 -> 63, uneven 61 layers 129 -> 91, 8B
+// 12.4 -> 6.5 us; half and twice the run lost 13-30% and 5-15% on the 70B pair.
+// Slices are taken kClassSlices at a time (a wider model's rows are cut into
+// pieces, each written by a block of its own).
+constexpr int kClassSlices = 8192 + 128;  // a 128-layer model's slices (8256) are one piece
+constexpr int kMaxClasses = 512;
+constexpr int kClassCfg = 4;       // configs per block, at most
+constexpr int kClassRun = 8256;    // candidates a block writes, about (1, 2 and 4 configs on 128, 80 and 48 layers)
+constexpr size_t kClassLds = 60 * 1024;
+constexpr int64_t kClassBlocks = 1024;  // blocks wanted before configs share one
+
+struct ClassTile {
+    int32_t C;          // configs per block
+    int32_t pieces;     // pieces of a row
+    int32_t piece;      // slices per piece
+    int32_t NC;         // slice classes
+};
+
+typedef double double2v __attribute__((ext_vector_type(2)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+
+template <bool kDense, bool kExt>
+__global__ __launch_bounds__(256) void score_class_kernel(DevProblem P, ClassTile ct, int64_t first, int64_t last,
+                                                          int64_t g_lo, int64_t g_hi, double *__restrict__ cost,
+                                                          uint8_t *__restrict__ dmax) {
+    extern __shared__ double lds_cls[];
+    __shared__ StagedCoef cs[kClassCfg];
+    const int NC = ct.NC;
+    double *vals = lds_cls;                                // [C][NC]
+    uint16_t *cls = (uint16_t *)(vals + ct.C * NC);        // [piece]
+    uint8_t *deps = (uint8_t *)(cls + ct.piece);           // [C][NC]
+    const int64_t per_xcd = gridDim.x / kXcds;
+    const int64_t blk = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    const int64_t gb = blk / ct.pieces;
+    const int pc = (int)(blk - gb * ct.pieces);
+    if (g_lo + gb * ct.C > g_hi) return;
+    const int64_t NS = P.NS;
+    const int s0 = pc * ct.piece;
+    const int ns = (int)min((int64_t)ct.piece, NS - s0);   // slices of this piece
+    const int64_t g0 = g_lo + gb * ct.C;
+    const int ng = (int)(min(g0 + ct.C, g_hi + 1) - g0);
+    const int tid = threadIdx.x;
+    if (tid < ng) cs[tid] = stage_coef<kExt>(P.coef[g0 + tid]);
+    for (int t = tid; t < ns; t += 256) cls[t] = (uint16_t)P.cls[s0 + t];
+    __syncthreads();
+    // whole waves enter (the depth rule votes); lanes past the end score nothing
+    for (int t0 = tid & ~(kWave - 1); t0 < NC; t0 += 256) {
+        const int c = t0 + (tid & (kWave - 1));
+        const bool live = c < NC;
+        SliceSums u;
+        if (live) u = slice_sums<kDense, kExt>(P, P.cls_ij[c]);
+        for (int t = 0; t < ng; ++t) {
+            int dm;
+            const double v = score_one<kDense, kExt>(cs[t], u, P.K, live, dm);
+            if (live) {
+                vals[t * NC + c] = v;
+                deps[t * NC + c] = (uint8_t)dm;
+            }
+        }
+    }
+    __syncthreads();
+    // the runs of candidates this block writes: all rows at once when a piece
+    // is a whole row, else one run per row
+    const bool one = ct.pieces == 1;
+    for (int r = 0; r < (one ? 1 : ng); ++r) {
+        const int64_t run0 = (g0 + r) * NS + s0;  // candidate index of the run's first element
+        const int64_t run1 = run0 + (one ? (int64_t)ng * ns : ns);
+        const int64_t lo = max(run0, first), hi = min(run1, last);
+        if (lo >= hi) continue;
+        const int e0 = (int)(lo - run0), n = (int)(hi - lo);
+        double *cp = cost + (lo - first);
+        uint8_t *dp = dmax + (lo - first);
+        const double *vr = vals + r * NC;
+        const uint8_t *dr = deps + r * NC;
+        // element e of the run: row e / ns of it, slice e % ns of the piece.
+        // A thread's elements advance by a fixed step, so row and slice do too.
+        auto locate = [&](int e, int &row, int &s) {
+            row = e / ns;
+            s = e - row * ns;
+        };
+        {
+            const int head = (int)(((uintptr_t)cp >> 3) & 1) & (n > 0);  // to a 16-byte boundary
+            const int pairs = (n - head) >> 1;
+            const int srow = 512 / ns, srem = 512 - srow * ns;
+            int row, s;
+            locate(e0 + head + 2 * tid, row, s);
+            double2v *out = (double2v *)(cp + head);
+            for (int q = tid; q < pairs; q += 256) {
+                const bool wrap = s + 1 == ns;
+                double2v x;
+                x.x = vr[row * NC + cls[s]];
+                x.y = vr[(wrap ? row + 1 : row) * NC + cls[wrap ? 0 : s + 1]];
+                __builtin_nontemporal_store(x, out + q);
+                row += srow;
+                s += srem;
+                if (s >= ns) {
+                    s -= ns;
+                    ++row;
+                }
+            }
+            if (tid < 2) {  // the element before the first pair, the one after the last
+                const int e = tid == 0 ? 0 : n - 1;
+                if (tid == 0 ? head != 0 : ((n - head) & 1) != 0) {
+                    locate(e0 + e, row, s);
+                    __builtin_nontemporal_store(vr[row * NC + cls[s]], cp + e);
+                }
+            }
+        }
+        {
+            const int head = min(n, (int)((0 - (uintptr_t)dp) & 15));
+            const int quads = (n - head) >> 4;
+            const int srow = 4096 / ns, srem = 4096 - srow * ns;
+            int row, s;
+            locate(e0 + head + 16 * tid, row, s);
+            uint4v *out = (uint4v *)(dp + head);
+            for (int q = tid; q < quads; q += 256) {
+                uint4v x;
+                int rr = row, ss = s;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t b = 0;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        b |= (uint32_t)dr[rr * NC + cls[ss]] << (8 * k);
+                        if (++ss == ns) {
+                            ss = 0;
+                            ++rr;
+                        }
+                    }
+                    x[w] = b;
+                }
+                // ordinary stores: the prune reads the depths next (streaming
+                // them took 701 us against 638 on the extended 70B instance)
+                out[q] = x;
+                row += srow;
+                s += srem;
+                if (s >= ns) {
+                    s -= ns;
+                    ++row;
+                }
+            }
+            const int tail0 = head + 16 * quads;  // the bytes before the first quad and after the last
+            const int t = tid < head ? tid : tail0 + tid - head;
+            if (tid < head + (n - tail0)) {
+                locate(e0 + t, row, s);
+                dp[t] = dr[row * NC + cls[s]];
+            }
+        }
+    }
+}
+
+// The class kernel's tile, or C = 0 where the general kernel is the better:
+// fewer than four slices a class (the model would be evaluated nearly as often
+// as there are candidates, by blocks that then wait for it), or more classes
+// than a block holds.
+static ClassTile class_tile(const DevProblem &P, int64_t n_cfg) {
+    ClassTile ct{};
+    if (P.NC > kMaxClasses || P.NC * 4 > P.NS) return ct;
+    ct.NC = (int32_t)P.NC;
+    ct.pieces = (int32_t)((P.NS + kClassSlices - 1) / kClassSlices);
+    ct.piece = (int32_t)((P.NS + ct.pieces - 1) / ct.pieces);
+    const int64_t spread = n_cfg * ct.pieces / kClassBlocks;
+    const int64_t fit = (int64_t)(kClassLds - 2 * (size_t)ct.piece) / (9 * P.NC);
+    const int64_t most = std::min<int64_t>(std::min<int64_t>(kClassCfg, kClassRun / P.NS), fit);
+    ct.C = (int32_t)std::max<int64_t>(1, std::min(most, spread));
+    return ct;
+}
+
 hipError_t launch_score(const DevProblem &P, int64_t first, int64_t count, double *cost, uint8_t *dmax,
                         hipStream_t s) {
     if (count <= 0) return hipSuccess;
     const int64_t last = first + count;
     const int64_t g_lo = first / P.NS, g_hi = (last - 1) / P.NS;
+    using T_ = std::true_type;
+    using F_ = std::false_type;
+    auto by_space = [&](auto &&go) {
+        if (P.dense && !P.ext)
+            go(T_{}, F_{});
+        else if (!P.dense && !P.ext)
+            go(F_{}, F_{});
+        else if (P.dense)
+            go(T_{}, T_{});
+        else
+            go(F_{}, T_{});
+    };
+    const ClassTile ct = class_tile(P, g_hi - g_lo + 1);
+    if (ct.C > 0) {
+        const int64_t cblocks = ((g_hi - g_lo + ct.C) / ct.C * ct.pieces + kXcds - 1) / kXcds * kXcds;
+        if (cblocks > 0x7fffffffLL) return hipErrorInvalidValue;
+        const size_t lds = (size_t)ct.C * P.NC * 9 + (size_t)ct.piece * 2;
+        by_space([&](auto dense, auto ext) {
+            score_class_kernel<decltype(dense)::value, decltype(ext)::value>
+                <<<dim3((unsigned)cblocks), dim3(256), lds, s>>>(P, ct, first, last, g_lo, g_hi, cost, dmax);
+        });
+        return hipGetLastError();
+    }
     const bool nt_depth = (P.NS & 63) == 0;
     const int cfg = score_configs(nt_depth);
     const int64_t n_gtiles = (g_hi - g_lo + cfg) / cfg;
@@ -278,7 +506,7 @@ hipError_t launch_score(const DevProblem &P, int64_t first, int64_t count, doubl
     int64_t blocks = (n_tiles + kScoreWaves - 1) / kScoreWaves;
     blocks = (blocks + kXcds - 1) / kXcds * kXcds;  // whole rounds over the XCDs
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    auto go = [&](auto dense, auto ext) {
+    by_space([&](auto dense, auto ext) {
         constexpr bool D = decltype(dense)::value, X = decltype(ext)::value;
         if (nt_depth)
             score_kernel<D, X, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(P, first, last, g_lo, g_hi,
@@ -286,17 +514,7 @@ hipError_t launch_score(const DevProblem &P, int64_t first, int64_t count, doubl
         else
             score_kernel<D, X, false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(P, first, last, g_lo, g_hi,
                                                                                     n_stiles, n_tiles, cost, dmax);
-    };
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    if (P.dense && !P.ext)
-        go(T_{}, F_{});
-    else if (!P.dense && !P.ext)
-        go(F_{}, F_{});
-    else if (P.dense)
-        go(T_{}, T_{});
-    else
-        go(F_{}, T_{});
+    });
     return hipGetLastError();
 }
 
