@@ -25,10 +25,12 @@
 // records its entries in an LDS bit mask per member (lane bit = slice), 512
 // members at a time, written as whole 64-bit words of a bitmap with one row
 // per compatible config (a later pass ORs into the words it wrote).
-// Compaction: popcount per tile, scan of tile counts, then each thread writes
-// the candidate indices of its words' set bits in ascending order.
+// Compaction: popcounts per tile of words, then each block adds up the counts
+// of the tiles before its own (scanned first where there are many tiles) and
+// writes its candidate indices in ascending order.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "tg_device.h"
 
@@ -42,9 +44,19 @@ constexpr int kSmallGroup = 64;
 constexpr int kMaskChunk = 512;   // members per LDS mask round when a pass is recorded
 constexpr int kMemberBits = 23;   // an entry packs depth << kMemberBits | member
 constexpr uint32_t kMemberMask = (1u << kMemberBits) - 1u;
-constexpr int kCountThreads = 256;
-constexpr int kWordsPerThread = 4;
-constexpr int kTileWords = kCountThreads * kWordsPerThread;
+constexpr int kEmitThreads = 256;
+// Words a thread of the compaction takes: four, or one up to kFineWords words (a
+// tile of rows that survive everywhere has 64 outputs a word, and with few
+// tiles the densest sets the time: 24 -> 12 us on the 70B instance's 228,000
+// words).  In a bitmap of at most kSmallWords words a block counts the words
+// before its tile by itself (at most 32 a thread) and no count pass runs.
+constexpr int64_t kSmallWords = 8192;
+constexpr int64_t kFineWords = (int64_t)4096 * kEmitThreads;
+// Tile counts a block adds up by itself, at most (32 a thread); above that a
+// scan of the counts runs first.
+constexpr int64_t kSumTiles = 8192;
+
+static int words_per_thread(int64_t n_words) { return n_words <= kFineWords ? 1 : 4; }
 
 // Offer member m (cost c, depth d >= 1, later in idx than every entry) to a
 // lane's staircase.  Entry e beats m when d_e >= d and c_e <= c (equal cost:
@@ -192,22 +204,22 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
     } while (__ballot(need) != 0);
 }
 
-__global__ __launch_bounds__(kCountThreads) void count_kernel(const uint64_t *__restrict__ bitmap, int64_t n_words,
-                                                              int64_t *tile_cnt) {
-    __shared__ int64_t lds[kCountThreads / kWave + 1];
-    const int64_t base = (int64_t)blockIdx.x * kTileWords + (int64_t)threadIdx.x * kWordsPerThread;
+template <int WPT>
+__global__ __launch_bounds__(kEmitThreads) void count_kernel(const uint64_t *__restrict__ bitmap, int64_t n_words,
+                                                             int64_t *tile_cnt) {
+    __shared__ int64_t lds[kEmitThreads / kWave + 1];
+    const int64_t base = (int64_t)blockIdx.x * kEmitThreads * WPT + (int64_t)threadIdx.x * WPT;
     int64_t c = 0;
 #pragma unroll
-    for (int w = 0; w < kWordsPerThread; ++w)
+    for (int w = 0; w < WPT; ++w)
         if (base + w < n_words) c += __popcll(bitmap[base + w]);
     int64_t total;
     block_excl_scan<int64_t>(c, lds, &total);
     if (threadIdx.x == 0) tile_cnt[blockIdx.x] = total;
 }
 
-// Exclusive scan of n int64 values in place by one block; writes the sum to
-// *total and, when given, to *total_host.
-__global__ __launch_bounds__(1024) void scan_small_i64(int64_t *a, int64_t n, int64_t *total, int64_t *total_host) {
+// Exclusive scan of n int64 values in place by one block.
+__global__ __launch_bounds__(1024) void scan_small_i64(int64_t *a, int64_t n) {
     __shared__ int64_t lds[1024 / kWave + 1];
     int64_t carry = 0;
     for (int64_t base = 0; base < n; base += blockDim.x) {
@@ -218,71 +230,164 @@ __global__ __launch_bounds__(1024) void scan_small_i64(int64_t *a, int64_t n, in
         if (i < n) a[i] = carry + ex;
         carry += sum;
     }
-    if (threadIdx.x == 0) {
-        *total = carry;
-        if (total_host) *total_host = carry;
+}
+
+// Position of the n-th set bit of w (from 0; w has more than n).
+__device__ inline int nth_bit(uint64_t w, int n) {
+    uint32_t x = (uint32_t)w;
+    int pos = 0;
+    int c = __popc(x);
+    if (n >= c) {
+        n -= c;
+        x = (uint32_t)(w >> 32);
+        pos = 32;
+    }
+#pragma unroll
+    for (int half = 16; half > 0; half >>= 1) {
+        c = __popc(x & ((1u << half) - 1u));
+        if (n >= c) {
+            n -= c;
+            x >>= half;
+            pos += half;
+        }
+    }
+    return pos;
+}
+
+// Bitmap -> ascending candidate indices, and their number to *total and, when
+// given, *total_host.  A tile's outputs are dealt to its threads one by one
+// (the word by bisection over the words' offsets in LDS, the bit by popcounts),
+// so the stores are coalesced and a dense tile keeps every thread busy: a
+// thread walking its own words' bits had up to 256 dependent stores.
+// WPT: words a thread takes.  kFrom: where the bits before the tile come from.
+enum class Before { kWords, kCounts, kScan };
+
+template <int WPT, Before kFrom>
+__global__ __launch_bounds__(kEmitThreads) void emit_kernel(DevProblem P, const uint64_t *__restrict__ bitmap,
+                                                            int64_t n_words, const int64_t *__restrict__ tile_cnt,
+                                                            int64_t *out, int64_t capacity, int64_t *total,
+                                                            int64_t *total_host) {
+    constexpr int kTile = kEmitThreads * WPT;
+    __shared__ uint64_t sw[kTile];   // the words
+    __shared__ int64_t sbase[kTile]; // candidate index of each word's bit 0
+    __shared__ int32_t soff[kTile];  // set bits before each word in the tile
+    __shared__ int32_t lds[kEmitThreads / kWave + 1];
+    __shared__ int64_t wsum[kEmitThreads / kWave];
+    const int64_t tile = blockIdx.x;
+    const int64_t w0 = tile * kTile + (int64_t)threadIdx.x * WPT;
+    uint64_t w[WPT];
+    int32_t c = 0;
+#pragma unroll
+    for (int t = 0; t < WPT; ++t) w[t] = w0 + t < n_words ? bitmap[w0 + t] : 0ull;
+    int64_t mine = 0;  // this thread's share of the bits before the tile
+    if (kFrom == Before::kWords)
+        for (int64_t t = threadIdx.x; t < tile * kTile; t += kEmitThreads) mine += __popcll(bitmap[t]);
+    if (kFrom == Before::kCounts)
+        for (int64_t t = threadIdx.x; t < tile; t += kEmitThreads) mine += tile_cnt[t];
+    if (kFrom == Before::kScan && threadIdx.x == 0) mine = tile_cnt[tile];
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+    if (wave_lane() == 0) wsum[threadIdx.x / kWave] = mine;
+#pragma unroll
+    for (int t = 0; t < WPT; ++t) c += __popcll(w[t]);
+    int32_t count;
+    int32_t off = block_excl_scan<int32_t>(c, lds, &count);
+    int64_t row = w0 / P.words;
+    int64_t sc = w0 - row * P.words;
+#pragma unroll
+    for (int t = 0; t < WPT; ++t) {
+        const int at = (int)threadIdx.x * WPT + t;
+        sw[at] = w[t];
+        soff[at] = off;
+        off += __popcll(w[t]);
+        if (w[t]) sbase[at] = (int64_t)P.row_cfg[row] * P.NS + sc * kWave;
+        if (++sc == P.words) {
+            sc = 0;
+            ++row;
+        }
+    }
+    __syncthreads();
+    int64_t before = 0;
+#pragma unroll
+    for (int u = 0; u < kEmitThreads / kWave; ++u) before += wsum[u];
+    if (threadIdx.x == 0 && tile == gridDim.x - 1) {
+        *total = before + count;
+        if (total_host) *total_host = before + count;
+    }
+    for (int32_t r = threadIdx.x; r < count; r += kEmitThreads) {
+        int at = 0;  // the last word whose offset is at most r
+#pragma unroll
+        for (int step = kTile / 2; step > 0; step >>= 1)
+            if (soff[at + step] <= r) at += step;
+        const int64_t pos = before + r;
+        if (pos < capacity) out[pos] = sbase[at] + nth_bit(sw[at], r - soff[at]);
     }
 }
 
-__global__ __launch_bounds__(kCountThreads) void emit_kernel(DevProblem P, const uint64_t *__restrict__ bitmap,
-                                                             int64_t n_words, const int64_t *tile_off,
-                                                             int64_t *out, int64_t capacity) {
-    __shared__ int64_t lds[kCountThreads / kWave + 1];
-    const int64_t base = (int64_t)blockIdx.x * kTileWords + (int64_t)threadIdx.x * kWordsPerThread;
-    uint64_t w[kWordsPerThread];
-    int64_t c = 0;
-#pragma unroll
-    for (int t = 0; t < kWordsPerThread; ++t) {
-        w[t] = (base + t < n_words) ? bitmap[base + t] : 0ull;
-        c += __popcll(w[t]);
-    }
-    int64_t total;
-    int64_t pos = tile_off[blockIdx.x] + block_excl_scan<int64_t>(c, lds, &total);
-#pragma unroll
-    for (int t = 0; t < kWordsPerThread; ++t) {
-        uint64_t bits = w[t];
-        if (!bits) continue;
-        const int64_t wi = base + t;
-        const int64_t row = wi / P.words;
-        const int64_t s0 = (wi - row * P.words) * kWave;
-        const int64_t g = P.row_cfg[row];
-        while (bits) {
-            const int bit = __ffsll((unsigned long long)bits) - 1;
-            bits &= bits - 1;
-            if (pos < capacity) out[pos] = g * P.NS + s0 + bit;
-            ++pos;
-        }
-    }
+__global__ void no_survivors(int64_t *total, int64_t *total_host) {
+    *total = 0;
+    if (total_host) *total_host = 0;
 }
 
 // Redundancy pruning: bit s of a row of the slice bitmap is bit cls[s] of
 // the same row of the class bitmap (a class's staircase holds on every slice
-// of the class).  A wave builds kExpandWords consecutive 64-bit words, lane b
-// testing slice 64 w + b of each, the loads of all its words in flight.
-constexpr int kExpandWords = 8;
+// of the class).  A block keeps the classes of up to kExpandSlices slices in
+// LDS and runs kExpandRows rows through them, a wave per row: a row without
+// survivors (most are) is only cleared, else 64 slices' bits make a word by
+// ballot, 64 words go out in one store.  Reading the classes per word from L2
+// and dividing per word took 380 us on the 128-layer instance (4.2M words);
+// this takes 73 us.
+constexpr int kExpandSlices = 8192 + 128;
+constexpr int kExpandRows = 8;
+constexpr int kExpandWords = 8;  // words a wave builds at a time, their reads in flight together
 
 __global__ __launch_bounds__(256) void expand_kernel(DevProblem P, const uint64_t *__restrict__ cbits,
-                                                     int32_t cwords, uint64_t *bits, int64_t n_words) {
-    const int64_t w0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) * kExpandWords;
-    if (w0 >= n_words) return;  // whole waves leave together
-    const int lane = threadIdx.x & (kWave - 1);
-    uint32_t c[kExpandWords];
-    int64_t row[kExpandWords];
-#pragma unroll
-    for (int t = 0; t < kExpandWords; ++t) {
-        const int64_t w = min(w0 + t, n_words - 1);
-        row[t] = w / P.words;
-        const int64_t s = (w - row[t] * P.words) * kWave + lane;
-        c[t] = s < P.NS ? P.cls[s] : 0xFFFFFFFFu;
+                                                     int32_t cwords, uint64_t *bits, int pieces, int piece) {
+    __shared__ uint32_t cls[kExpandSlices];
+    const int pc = blockIdx.x % pieces;  // a piece: `piece` slices, whole words
+    const int64_t r0 = (int64_t)(blockIdx.x / pieces) * kExpandRows;
+    const int64_t r1 = min(r0 + kExpandRows, (int64_t)P.n_rows);
+    const int64_t s0 = (int64_t)pc * piece;
+    const int ns = (int)min((int64_t)piece, P.NS - s0);
+    const int nw = (ns + kWave - 1) / kWave;
+    const int lane = wave_lane(), wv = threadIdx.x / kWave;
+    // the classes only once a row needs them
+    bool any = false;
+    for (int64_t t = r0 * cwords + threadIdx.x; t < r1 * cwords; t += 256) any = any || cbits[t] != 0;
+    if (__syncthreads_or(any)) {
+        for (int t = threadIdx.x; t < ns; t += 256) cls[t] = P.cls[s0 + t];
+        __syncthreads();
     }
-    uint64_t x[kExpandWords];
+    for (int64_t row = r0 + wv; row < r1; row += 256 / kWave) {
+        const uint64_t *cb = cbits + row * cwords;
+        uint64_t *to = bits + row * P.words + s0 / kWave;
+        bool live = false;
+        for (int w = lane; w < cwords; w += kWave) live = live || cb[w] != 0;
+        if (__ballot(live) == 0) {
+            for (int w = lane; w < nw; w += kWave) to[w] = 0;
+            continue;
+        }
+        for (int b0 = 0; b0 < nw; b0 += kWave) {
+            uint64_t mine = 0;
+            for (int k0 = 0; k0 < kWave && b0 + k0 < nw; k0 += kExpandWords) {
+                uint32_t c[kExpandWords];
+                uint64_t x[kExpandWords];
 #pragma unroll
-    for (int t = 0; t < kExpandWords; ++t)
-        x[t] = c[t] != 0xFFFFFFFFu ? cbits[row[t] * cwords + (c[t] >> 6)] : 0ull;
+                for (int k = 0; k < kExpandWords; ++k) {
+                    const int t = (b0 + k0 + k) * kWave + lane;
+                    c[k] = cls[min(t, ns - 1)];
+                }
 #pragma unroll
-    for (int t = 0; t < kExpandWords; ++t) {
-        const uint64_t word = __ballot(c[t] != 0xFFFFFFFFu && ((x[t] >> (c[t] & 63)) & 1ull));
-        if (lane == 0 && w0 + t < n_words) bits[w0 + t] = word;
+                for (int k = 0; k < kExpandWords; ++k) x[k] = cb[c[k] >> 6];
+#pragma unroll
+                for (int k = 0; k < kExpandWords; ++k) {
+                    const bool in = (b0 + k0 + k) * kWave + lane < ns;
+                    const uint64_t word = __ballot(in && ((x[k] >> (c[k] & 63)) & 1ull));
+                    if (lane == k0 + k) mine = word;
+                }
+            }
+            if (b0 + lane < nw) to[b0 + lane] = mine;
+        }
     }
 }
 
@@ -290,12 +395,31 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static int64_t bitmap_words(const DevProblem &P) { return (int64_t)P.n_rows * P.words; }
 
-size_t prune_ws_bytes(const DevProblem &P) {
-    const int64_t nw = bitmap_words(P);
-    const int64_t nt = (nw + kTileWords - 1) / kTileWords;
-    return align256(sizeof(uint64_t) * (size_t)(nw > 0 ? nw : 1)) + align256(sizeof(int64_t) * (size_t)(nt + 1)) +
-           align256(sizeof(int64_t));
+// The prune workspace: the bitmap, the tile counts, the survivor count.
+struct PruneWs {
+    uint64_t *bitmap;
+    int64_t *tiles, *total;
+    int64_t n_words, n_tiles;
+    size_t bytes;
+};
+
+static PruneWs carve_prune(const DevProblem &P, void *ws) {
+    PruneWs w{};
+    w.n_words = bitmap_words(P);
+    const int64_t tile = (int64_t)kEmitThreads * words_per_thread(w.n_words);
+    w.n_tiles = (w.n_words + tile - 1) / tile;
+    const size_t tiles_at = align256(sizeof(uint64_t) * (size_t)(w.n_words > 0 ? w.n_words : 1));
+    const size_t total_at = tiles_at + align256(sizeof(int64_t) * (size_t)(w.n_tiles + 1));
+    w.bytes = total_at + align256(sizeof(int64_t));
+    if (ws) {
+        w.bitmap = (uint64_t *)ws;
+        w.tiles = (int64_t *)((char *)ws + tiles_at);
+        w.total = (int64_t *)((char *)ws + total_at);
+    }
+    return w;
 }
+
+size_t prune_ws_bytes(const DevProblem &P) { return carve_prune(P, nullptr).bytes; }
 
 static hipError_t launch_frontier(const DevProblem &P, const double *cost, const uint8_t *dmax, uint64_t *bitmap,
                                   hipStream_t s) {
@@ -312,30 +436,42 @@ static hipError_t launch_frontier(const DevProblem &P, const double *cost, const
     return hipGetLastError();
 }
 
-// Survivor bitmap (at the start of ws) -> ascending candidate indices.
-static hipError_t launch_compact(const DevProblem &P, int64_t *surv, int64_t capacity, void *ws, hipStream_t s,
-                                 int64_t **d_total_out, int64_t *total_host = nullptr) {
-    const int64_t nw = bitmap_words(P);
-    const int64_t nt = (nw + kTileWords - 1) / kTileWords;
-    char *p = (char *)ws;
-    uint64_t *bitmap = (uint64_t *)p;
-    p += align256(sizeof(uint64_t) * (size_t)(nw > 0 ? nw : 1));
-    int64_t *tiles = (int64_t *)p;
-    p += align256(sizeof(int64_t) * (size_t)(nt + 1));
-    int64_t *total = (int64_t *)p;
-    *d_total_out = total;
-    if (nt > 0) count_kernel<<<dim3((unsigned)nt), dim3(kCountThreads), 0, s>>>(bitmap, nw, tiles);
-    scan_small_i64<<<dim3(1), dim3(1024), 0, s>>>(tiles, nt, total, total_host);
-    if (nt > 0)
-        emit_kernel<<<dim3((unsigned)nt), dim3(kCountThreads), 0, s>>>(P, bitmap, nw, tiles, surv, capacity);
+// Survivor bitmap -> ascending candidate indices.
+static hipError_t launch_compact(const DevProblem &P, const PruneWs &w, int64_t *surv, int64_t capacity,
+                                 hipStream_t s, int64_t **d_total_out, int64_t *total_host = nullptr) {
+    *d_total_out = w.total;
+    const dim3 grid((unsigned)w.n_tiles), block(kEmitThreads);
+    auto emit = [&](auto wpt, auto from) {
+        emit_kernel<decltype(wpt)::value, decltype(from)::value><<<grid, block, 0, s>>>(
+            P, w.bitmap, w.n_words, w.tiles, surv, capacity, w.total, total_host);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Four = std::integral_constant<int, 4>;
+    if (w.n_words == 0) {
+        no_survivors<<<dim3(1), dim3(1), 0, s>>>(w.total, total_host);
+    } else if (w.n_words <= kSmallWords) {
+        emit(One{}, std::integral_constant<Before, Before::kWords>{});
+    } else if (words_per_thread(w.n_words) == 1) {
+        count_kernel<1><<<grid, block, 0, s>>>(w.bitmap, w.n_words, w.tiles);
+        emit(One{}, std::integral_constant<Before, Before::kCounts>{});
+    } else {
+        count_kernel<4><<<grid, block, 0, s>>>(w.bitmap, w.n_words, w.tiles);
+        if (w.n_tiles <= kSumTiles) {
+            emit(Four{}, std::integral_constant<Before, Before::kCounts>{});
+        } else {
+            scan_small_i64<<<dim3(1), dim3(1024), 0, s>>>(w.tiles, w.n_tiles);
+            emit(Four{}, std::integral_constant<Before, Before::kScan>{});
+        }
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_prune(const DevProblem &P, const double *cost, const uint8_t *dmax, int64_t *surv,
                         int64_t capacity, void *ws, hipStream_t s, int64_t **d_total_out, int64_t *total_host) {
-    hipError_t e = launch_frontier(P, cost, dmax, (uint64_t *)ws, s);
+    const PruneWs w = carve_prune(P, ws);
+    hipError_t e = launch_frontier(P, cost, dmax, w.bitmap, s);
     if (e != hipSuccess) return e;
-    return launch_compact(P, surv, capacity, ws, s, d_total_out, total_host);
+    return launch_compact(P, w, surv, capacity, s, d_total_out, total_host);
 }
 
 // Scratch of the prune variant that allocates nothing: a device array the
@@ -371,16 +507,19 @@ size_t prune_classes_ws_bytes(const DevProblem &P) {
 hipError_t launch_prune_classes(const DevProblem &P, const double *cost, const uint8_t *dmax, int64_t *surv,
                                 int64_t capacity, void *ws, hipStream_t s, int64_t **d_total_out) {
     const DevProblem C = class_view(P);
+    const PruneWs w = carve_prune(P, ws);
     uint64_t *cbits = (uint64_t *)((char *)ws + prune_ws_bytes(P));
     hipError_t e = launch_frontier(C, cost, dmax, cbits, s);
     if (e != hipSuccess) return e;
-    const int64_t nw = bitmap_words(P);
-    if (nw > 0)
-        expand_kernel<<<dim3((unsigned)((nw + 4 * kExpandWords - 1) / (4 * kExpandWords))), dim3(256), 0, s>>>(
-            P, cbits, C.words, (uint64_t *)ws, nw);
+    if (w.n_words > 0) {
+        const int pieces = (int)((P.NS + kExpandSlices - 1) / kExpandSlices);
+        const int piece = (int)((P.words + pieces - 1) / pieces) * kWave;
+        const int64_t blocks = ((int64_t)P.n_rows + kExpandRows - 1) / kExpandRows * pieces;
+        expand_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(P, cbits, C.words, w.bitmap, pieces, piece);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_compact(P, surv, capacity, ws, s, d_total_out);
+    return launch_compact(P, w, surv, capacity, s, d_total_out);
 }
 
 }  // namespace tg
