@@ -543,9 +543,10 @@ size_t tg_prune_classes_workspace_bytes(const tg_problem *p) { return p ? tg::pr
 
 // The handle's pinned read-back words, which kernels store into: the
 // composition's result block at 0 (the prune's count there too, in calls of
-// its own), then the fill depth limits (nb int32).
+// its own), then the fill depth limits (nb int32) or the all-orders
+// composition's values (nb doubles).
 static size_t readback_dlim_at() { return (sizeof(tg::ComposeResult) + 255) & ~(size_t)255; }
-static size_t readback_bytes(const tg_problem *p) { return readback_dlim_at() + sizeof(int32_t) * (size_t)p->P.nb; }
+static size_t readback_bytes(const tg_problem *p) { return readback_dlim_at() + sizeof(double) * (size_t)p->P.nb; }
 
 // The read-back words (the first call allocates them) when no other call
 // holds them: locks `lock` and returns them, else null (the caller reads back
@@ -851,11 +852,25 @@ tg_status tg_compose_pipeline_all_orders(const tg_problem *p, const int64_t *d_s
     const size_t need = p && n_survivors >= 0 ? tg::compose_orders_ws_bytes(p->P, n_survivors) : 0;
     tg_status st = compose_begin(p, d_survivors, n_survivors, d_cost, d_dmax, nullptr, out, d_ws, ws_bytes, need, s);
     if (st != TG_OK) return st;
-    tg::ComposeResult *res_dev = nullptr;
-    hipError_t e = tg::launch_compose_orders(p->P, p->bvals.data(), d_survivors, n_survivors, d_cost, d_dmax, d_ws, s,
-                                             &res_dev);
-    if (e != hipSuccess) return hip_fail(e, "all-orders compose kernels");
-    return compose_end(res_dev, out, s);
+    return no_throw([&] {
+        tg::ComposeResult *res_dev = nullptr;
+        // the handle's pinned read-back words, when no other call holds them
+        std::unique_lock<std::mutex> lock;
+        const tg::HostStage *pw = pinned_words(p, lock);
+        tg::ComposeHost host{};
+        if (pw) {
+            const size_t at = readback_dlim_at();
+            host = tg::ComposeHost{(int32_t *)((char *)pw->ptr + at), (int32_t *)((char *)pw->dev + at),
+                                   (tg::ComposeResult *)pw->ptr, (tg::ComposeResult *)pw->dev, nullptr};
+        }
+        hipError_t e = tg::launch_compose_orders(p->P, p->bvals.data(), d_survivors, n_survivors, d_cost, d_dmax,
+                                                 d_ws, s, &res_dev, pw ? &host : nullptr);
+        if (e != hipSuccess) {
+            (void)hipStreamSynchronize(s);  // nothing queued may store into the words once they are let go
+            return hip_fail(e, "all-orders compose kernels");
+        }
+        return compose_end(res_dev, out, s, host.res);
+    });
 }
 
 }  // extern "C"

@@ -1311,14 +1311,8 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(DevProblem P, co
         }
     }
     if (!res_host) return;
-    // the header and the S stages into host memory (8-byte words)
     __syncthreads();
-    static_assert(offsetof(ComposeResult, plan) % 8 == 0 && offsetof(tg_plan, stage) % 8 == 0 &&
-                      sizeof(tg_stage) % 8 == 0, "result words");
-    const int n = (int)((offsetof(ComposeResult, plan) + offsetof(tg_plan, stage) + sizeof(tg_stage) * S) / 8);
-    const uint64_t *src = (const uint64_t *)res;
-    uint64_t *dst = (uint64_t *)res_host;
-    for (int k = threadIdx.x; k < n; k += kFinishThreads) dst[k] = src[k];
+    store_result(res, res_host, S);
 }
 
 // ---------------------------------------------------------------------------

@@ -39,13 +39,18 @@ namespace tg {
 
 constexpr int kMaxSetIslands = 16;
 constexpr int kMaxLayers = 512;
-constexpr size_t kLevelLds = 12 * 1024;  // LDS bytes per level block: staged rows and continuation rows
-constexpr int kLevelThreads = 128;
+constexpr int kLevelLds = 640;  // LDS doubles per level block (one row of the longest model fits): staged rows
+                                // and continuation rows
+constexpr int kLevelThreads = 64;
+static_assert(kLevelLds >= kMaxLayers + 1, "one continuation row");
 constexpr int64_t kPruneCells = (int64_t)1 << 22;  // fill cells below which every b runs at once
 constexpr int kOrderFinishThreads = 1024;
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 constexpr int64_t kTargetBlocks = 8192;  // blocks per level launch worth splitting for
 constexpr int kReduceChunks = 64;        // partials per b in the root reductions
+constexpr int kCutOrders = 4;            // island orders tried for the bound
+constexpr int kCutThreads = 1024;
+constexpr int kAheadCut = 5;             // islands or cuts read at a time there
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -84,6 +89,14 @@ static SetLevels set_levels(const DevProblem &P) {
     return v;
 }
 
+// The b of each grid row of a run, passed by value (n = 0: every b in order).
+constexpr int kRunB = 32;
+struct BList {
+    int32_t n;
+    int32_t b[kRunB];
+    __device__ int at(int row) const { return n ? b[row] : row; }
+};
+
 struct OrdersWs {
     ComposeResult *res;
     int32_t *pos;       // [K] identity: groups are numbered by island id
@@ -102,7 +115,10 @@ struct OrdersWs {
     uint32_t *rootKey;  // [nb] (k << 24 | d << 16 | U) of the chosen root
     double *part_v;     // [nb][kReduceChunks] partial reductions
     uint32_t *part_k;   // [nb][kReduceChunks]
-    int32_t *blist;     // [nb] the b of each grid row in a fill run
+    unsigned long long *cut;  // [nb] least bottleneck over a few island orders (bits of a double)
+    double *tau;        // [nb] the bottleneck phase's bound
+    int32_t *ml;        // [nb][D+2][K] longest slice of island k within the bound at depth d (0 past D)
+    double *fixed;      // [nb][kCutOrders][2][K][L+1] rows of the fixed-order levels
     size_t bytes;
 };
 
@@ -139,7 +155,10 @@ static OrdersWs carve_orders(const DevProblem &P, int64_t n, void *base) {
     w.Pst = (double *)take(sizeof(double) * nb);
     w.rootF = (double *)take(sizeof(double) * nb);
     w.rootKey = (uint32_t *)take(sizeof(uint32_t) * nb);
-    w.blist = (int32_t *)take(sizeof(int32_t) * nb);
+    w.cut = (unsigned long long *)take(sizeof(unsigned long long) * nb);
+    w.tau = (double *)take(sizeof(double) * nb);
+    w.ml = (int32_t *)take(sizeof(int32_t) * nb * (lv.D + 2) * K);
+    w.fixed = (double *)take(sizeof(double) * nb * kCutOrders * 2 * K * (L + 1));
     w.part_v = (double *)take(sizeof(double) * nb * kReduceChunks);
     w.part_k = (uint32_t *)take(sizeof(uint32_t) * nb * kReduceChunks);
     w.bytes = off;
@@ -225,14 +244,187 @@ __global__ __launch_bounds__(256) void orders_links(DevProblem P, double *X) {
 }
 
 // ---------------------------------------------------------------------------
+// bounds and bands
+// ---------------------------------------------------------------------------
+// Most rows of most sets are of no use.  With a bound on the bottleneck, an
+// island takes at most so many layers, so the islands of U can only cover the
+// last layers up to their sum, and the islands outside U, whose stages are
+// deeper than |U|, can only cover the first layers up to theirs: the rows i of
+// a set's states that belong to some whole plan within the bound form a band
+// [L - sum over U of ml_1, sum outside U of ml_(|U|+1)], ml_d(k) the longest
+// slice of island k within the bound at depth d (an upper bound for every
+// starting layer, so also for uneven models).  A level computes, stores and
+// reads only its sets' bands; both sides derive a band from the set alone.
+// Rows outside cannot be part of a plan within the bound, so the least
+// bottleneck, the least fill and every argmin on their way are untouched.
+//   The bottleneck phase's bound: P*_b is at most the bottleneck P of the best
+// plan of any one island order, found by the fixed-order recurrence for
+// kCutOrders orders.  Across b, some plan has T at most UB = the least of
+// (m - 1) P + (2 D - 1) P (D stages and D - 1 links within P), and a b with
+// (m - 1) P*_b + P*_b above UB can neither win nor tie, so the bound is also at
+// most UB / m.  The fill phase's bound is P*_b itself.  On the 16-island 70B
+// instance the levels went from 5.4 + 2.3 ms (bottleneck, fill) to 1.1 + 0.85 ms,
+// the two kernels here that need the bound to 0.19 ms.
+__global__ __launch_bounds__(kCutThreads) void orders_cutoff(DevProblem P, int D, const double *__restrict__ T,
+                                                             const double *__restrict__ X, double *fixed,
+                                                             unsigned long long *cut) {
+    __shared__ int32_t ord[kMaxSetIslands];
+    const int L = P.L, K = P.K, R = L + 1;
+    const int v = blockIdx.x, bb = blockIdx.y;
+    double *V = fixed + ((int64_t)bb * kCutOrders + v) * 2 * K * R;
+    double *W = V + (int64_t)K * R;
+    if ((int)threadIdx.x < K) {
+        // the orders: large memory first (deep stages hold more), fast first or
+        // slow first among equals; fast first; the islands as numbered
+        const int k = threadIdx.x;
+        auto key = [&](int q, int f) {
+            if (v == 3) return 0.0;
+            const double mem = P.hbm[q], pk = P.cap[q];
+            return f == 0 ? (v == 2 ? pk : mem) : (v == 1 ? -pk : (v == 2 ? mem : pk));
+        };
+        int r = 0;
+        for (int q = 0; q < K; ++q) {
+            const double a0 = key(q, 0), b0 = key(k, 0), a1 = key(q, 1), b1 = key(k, 1);
+            if (a0 > b0 || (a0 == b0 && (a1 > b1 || (a1 == b1 && q < k)))) ++r;
+        }
+        ord[r] = k;
+    }
+    __syncthreads();
+    const double *Tb = T + (int64_t)bb * K * L * L;
+    const double *Xb = X + (int64_t)bb * K * K * R;
+    double best = kInf;
+    for (int e = threadIdx.x; e < K * R; e += kCutThreads) {
+        const int q = e / R, i = e - q * R;
+        const double x = i < L ? Tb[((int64_t)ord[q] * L + (L - i - 1)) * L + i] : kInf;
+        V[e] = x;
+        if (i == 0) best = fmin(best, x);
+    }
+    for (int d = 2; d <= D; ++d) {
+        const int jmax = L - d + 1;
+        __syncthreads();
+        for (int e = threadIdx.x; e < K * R; e += kCutThreads) {
+            const int q = e / R, j = e - q * R;
+            double w = kInf;
+            if (j >= 1 && j <= jmax) {
+                const double *Xr = Xb + (int64_t)ord[q] * K * R + j;
+                for (int t0 = q + 1; t0 < K; t0 += kAheadCut) {  // loads in flight together
+                    double x[kAheadCut], y[kAheadCut];
+#pragma unroll
+                    for (int u = 0; u < kAheadCut; ++u) {
+                        const int q2 = min(t0 + u, K - 1);
+                        x[u] = Xr[ord[q2] * R];
+                        y[u] = V[q2 * R + j];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAheadCut; ++u) w = fmin(w, fmax(x[u], y[u]));
+                }
+            }
+            W[e] = w;
+        }
+        __syncthreads();
+        const double *Td = Tb + (int64_t)(d - 1) * P.nb * K * L * L;
+        for (int e = threadIdx.x; e < K * R; e += kCutThreads) {
+            const int q = e / R, i = e - q * R;
+            double x = kInf;
+            if (i <= L - d) {
+                const double *Ti = Td + (int64_t)ord[q] * L * L + i;
+                const int js = P.jlo ? max(i + 1, P.jlo[ord[q] * L + i]) : i + 1;
+                bool go = true;
+                for (int j0 = js; go && j0 <= jmax; j0 += kAheadCut) {
+                    double t[kAheadCut], y[kAheadCut];
+#pragma unroll
+                    for (int u = 0; u < kAheadCut; ++u) {
+                        const int j = min(j0 + u, jmax);
+                        t[u] = Ti[(int64_t)(j - i - 1) * L];
+                        y[u] = W[q * R + j];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAheadCut; ++u) {
+                        go = go && t[u] < x;  // t never decreases in j (a repeated last cut changes nothing)
+                        if (go) x = fmin(x, fmax(t[u], y[u]));
+                    }
+                }
+                if (i == 0) best = fmin(best, x);
+            }
+            V[e] = x;
+        }
+    }
+    if (best < kInf) atomicMin(&cut[bb], (unsigned long long)__double_as_longlong(fmax(best, 0.0)));
+}
+
+// No plan known yet for the listed b's states.
+__global__ __launch_bounds__(256) void orders_reset(double *root, int64_t total, BList blist) {
+    double *r = root + (int64_t)blist.at(blockIdx.y) * total;
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) r[t] = kInf;
+}
+
+// The bottleneck phase's bound of every b.
+__global__ __launch_bounds__(256) void orders_bound(DevProblem P, int D, const unsigned long long *__restrict__ cut,
+                                                    double *tau) {
+    __shared__ double red[256];
+    double ub = kInf;
+    for (int b = threadIdx.x; b < P.nb; b += 256) {
+        const double p = __longlong_as_double((long long)cut[b]);
+        const double mm1 = (double)(P.B / P.bvals[b] - 1);
+        if (p < kInf) ub = fmin(ub, ((mm1 * p) + ((double)(2 * D - 1) * p)) * (1.0 + 1e-12));
+    }
+    red[threadIdx.x] = ub;
+    for (int h = 128; h > 0; h >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < h) red[threadIdx.x] = fmin(red[threadIdx.x], red[threadIdx.x + h]);
+    }
+    __syncthreads();
+    ub = red[0];
+    for (int b = threadIdx.x; b < P.nb; b += 256) {
+        const double m = (double)(P.B / P.bvals[b]);
+        tau[b] = fmin(__longlong_as_double((long long)cut[b]), (ub / m) * (1.0 + 4e-12));
+    }
+}
+
+// ml[b][d][k]: the longest slice of island k whose least cost at depth d is
+// within bound[b]; a wave per entry walks the lengths downwards.
+__global__ __launch_bounds__(256) void orders_longest(DevProblem P, int D, const double *__restrict__ T,
+                                                      const double *__restrict__ bound, int32_t *ml) {
+    const int L = P.L, K = P.K;
+    const int64_t e = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+    if (e >= (int64_t)P.nb * (D + 2) * K) return;  // whole waves leave
+    const int k = (int)(e % K), d = (int)((e / K) % (D + 2)), bb = (int)(e / ((int64_t)K * (D + 2)));
+    const int lane = wave_lane();
+    int len = 0;
+    if (d >= 1 && d <= D) {
+        const double lim = bound[bb];
+        const double *Tk = T + (((int64_t)(d - 1) * P.nb + bb) * K + k) * L * L;
+        constexpr int kLens = 8;  // lengths checked at a time
+        for (int l1 = L; l1 > 0 && len == 0; l1 -= kLens) {
+            int mine = 0;
+            for (int i = lane; i < L; i += kWave) {
+                double t[kLens];
+#pragma unroll
+                for (int u = 0; u < kLens; ++u) {
+                    const int l = l1 - u;
+                    t[u] = l > 0 && i + l <= L ? Tk[(int64_t)(l - 1) * L + i] : kInf;
+                }
+#pragma unroll
+                for (int u = kLens - 1; u >= 0; --u)
+                    if (t[u] < kInf && t[u] <= lim) mine = max(mine, l1 - u);
+            }
+#pragma unroll
+            for (int off = kWave / 2; off > 0; off >>= 1) mine = max(mine, __shfl_xor(mine, off));
+            len = mine;
+        }
+    }
+    if (lane == 0) ml[e] = len;
+}
+
+// ---------------------------------------------------------------------------
 // levels
 // ---------------------------------------------------------------------------
 // Level 1: one stage on island k covering [i, L).
 template <bool kFill>
 __global__ __launch_bounds__(256) void orders_level1(DevProblem P, SetLevels lv, const double *__restrict__ T,
                                                      const double *__restrict__ Pst, double *cur, double *root,
-                                                     const int32_t *__restrict__ blist) {
-    const int L = P.L, K = P.K, bb = blist ? blist[blockIdx.y] : blockIdx.y;
+                                                     BList blist) {
+    const int L = P.L, K = P.K, bb = blist.at(blockIdx.y);
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (int64_t)K * (L + 1)) return;
     const int k = (int)(e / (L + 1)), i = (int)(e - (int64_t)k * (L + 1));
@@ -246,40 +438,62 @@ __global__ __launch_bounds__(256) void orders_level1(DevProblem P, SetLevels lv,
 }
 
 // Level d >= 2, block (part of the islands outside a (d-1)-set U', b).  kFill:
-// the fill phase at bound P*, with argmins; otherwise the bottleneck phase.
-// The block's states (k, U' + {k}) go in chunks of C: first every
+// the fill phase at bound P*, with argmins; otherwise the bottleneck phase (at
+// its own bound).  The block's states (k, U' + {k}) go in chunks: first every
 // continuation row of the chunk into LDS (thread per (state, cut)), then every
 // stage scan (thread per (state, first layer)), two barriers per chunk and
-// every lane busy whatever L is.  kStage: the previous level's rows of U',
-// read by every state, are staged in LDS first.
-template <int NT, bool kFill, bool kStage>
-__global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, int d, int nsplit, int C,
+// every lane busy whatever L is.  Cuts are the band of U', first layers the
+// bands of the sets U' + {k}; LDS rows hold the band only, so a chunk takes
+// more states the narrower it is.  The previous level's rows of U', read by
+// every state, are staged in LDS first where they leave room for two states.
+// A level is bound by the blocks' chains of dependent loads (set, caps, rows,
+// links, costs; about 6 us), so it needs many blocks in flight: one wave and
+// 5 KB of LDS each, 31 to a CU: the 16-island 70B instance's levels took 0.69 +
+// 0.64 ms, against 1.10 + 0.85 with two waves and 12 KB (12 to a CU).
+template <int NT, bool kFill>
+__global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, int d, int nsplit, int lds_n,
                                                    const int32_t *__restrict__ masks,
                                                    const uint16_t *__restrict__ rank, const double *__restrict__ T,
                                                    const double *__restrict__ X, const double *__restrict__ prev,
-                                                   double *cur, double *root, const double *__restrict__ Pst,
-                                                   uint16_t *argF, uint8_t *argG, const int32_t *__restrict__ blist) {
-    // LDS: (kStage) the set's previous-level rows, then C continuation rows
+                                                   double *cur, double *root, const double *__restrict__ bounds,
+                                                   const int32_t *__restrict__ ml, uint16_t *argF, uint8_t *argG,
+                                                   BList blist) {
+    // LDS: (staged) the set's previous-level rows, then the chunk's continuation rows
     extern __shared__ double lds_rows[];
     __shared__ int16_t s_k[kMaxSetIslands];
     __shared__ int32_t s_st[kMaxSetIslands];
+    __shared__ int16_t s_lo[kMaxSetIslands], s_hi[kMaxSetIslands];  // the band of U' + {k}
     // per state: the first and last cut with a finite continuation (a scan
     // skips the cuts outside, where every candidate is +inf)
     __shared__ int32_t s_jlo[kMaxSetIslands], s_jhi[kMaxSetIslands];
     const int L = P.L, K = P.K, R = L + 1;
     const int rp = blockIdx.x / nsplit, part = blockIdx.x - rp * nsplit;
-    const int bb = blist ? blist[blockIdx.y] : blockIdx.y;  // a fill run covers a list of b
+    const int bb = blist.at(blockIdx.y);  // a fill run covers a list of b
     const uint32_t Up = (uint32_t)masks[lv.moff[d - 1] + rp];
     const int nk = K - (d - 1);
     const int per = (nk + nsplit - 1) / nsplit;
     const int q0 = part * per, q1 = min(nk, q0 + per);
     const int nu = d - 1;
-    const int jmax = L - d + 1;
-    const double bound = kFill ? Pst[bb] : 0.0;
+    const double bound = bounds[bb];
+    // the band of U' and what the bands of U' + {k} need (each wave by itself)
+    const int32_t *mlb = ml + (int64_t)bb * (lv.D + 2) * K;
+    int own = 0, out = 0, next = 0, m1max = 0, mdmin = 1 << 20;
+    for (int k = 0; k < K; ++k) {
+        const int m1 = mlb[K + k], md = mlb[d * K + k], mn = mlb[(d + 1) * K + k];
+        if (Up >> k & 1u) {
+            own += m1;
+        } else {
+            out += md;
+            next += mn;
+            m1max = max(m1max, m1);
+            mdmin = min(mdmin, mn);
+        }
+    }
+    const int jlo = max(1, L - own), jhi = min(L - d + 1, out);
+    const int ilo = max(0, L - own - m1max), ihi = min(L - d, next - mdmin);  // covers every state's band
+    if (ilo > ihi) return;  // no state has a row in its band
+    const int Bj = jhi - jlo + 1;
     const double *Vp = prev + ((int64_t)bb * lv.n[d - 1] + (int64_t)rp * nu) * R;
-    // (offsets from the LDS array itself keep these accesses LDS instructions)
-    const double *Vs = lds_rows;
-    double *Wl = lds_rows + (kStage ? nu * R : 0);
     // the islands of U' in ascending order (the same for every thread), and
     // each one's row offset in an X block
     int ks[kMaxSetIslands], koff[kMaxSetIslands];
@@ -292,7 +506,7 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
             r2 &= r2 - 1;
         }
     }
-    constexpr int kIsl = kStage ? 8 : 4;  // islands' link loads in flight
+    constexpr int kIsl = 8;  // islands' link loads in flight
     // the block's states: island k (the q-th outside U', from q0 on) and the
     // state number of (k, U' + {k})
     if ((int)threadIdx.x < q1 - q0) {
@@ -302,22 +516,42 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
         const uint32_t U = Up | (1u << k);
         s_k[threadIdx.x] = (int16_t)k;
         s_st[threadIdx.x] = (int)rank[U] * d + __builtin_popcount(U & ((1u << k) - 1u));
+        s_lo[threadIdx.x] = (int16_t)max(0, L - own - mlb[K + k]);
+        s_hi[threadIdx.x] = (int16_t)min(L - d, next - mlb[(d + 1) * K + k]);
         s_jlo[threadIdx.x] = INT_MAX;
         s_jhi[threadIdx.x] = -1;
     }
-    if (kStage)
-        for (int t = threadIdx.x; t < nu * R; t += NT) lds_rows[t] = Vp[t];
+    if (Bj <= 0) {  // nothing continues: the states' bands hold no plan
+        __syncthreads();
+        const int w = ihi - ilo + 1;
+        for (int p = threadIdx.x; p < (q1 - q0) * w; p += NT) {
+            const int s = p / w, i = ilo + p - s * w;
+            if (i >= s_lo[s] && i <= s_hi[s]) cur[((int64_t)bb * lv.n[d] + s_st[s]) * R + i] = kInf;
+        }
+        return;
+    }
+    const bool stage = (nu + 2) * Bj <= lds_n;
+    if (stage)
+        for (int t = threadIdx.x; t < nu * Bj; t += NT) {
+            const int r = t / Bj;
+            lds_rows[t] = Vp[(int64_t)r * R + jlo + t - r * Bj];
+        }
+    // (offsets from the LDS array itself keep these accesses LDS instructions)
+    const double *Vs = lds_rows;
+    double *Wl = lds_rows + (stage ? nu * Bj : 0);
+    const int C = min(q1 - q0, (lds_n - (stage ? nu * Bj : 0)) / Bj);  // states per chunk, at least one
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
     for (int c0 = 0; c0 < q1 - q0; c0 += C) {
         const int nst = min(C, q1 - q0 - c0);
         // continuation rows W(j, k, U') of the chunk's states
-        const int nwork = nst * jmax;
+        const int nwork = nst * Bj;
         for (int p0 = 0; p0 < nwork; p0 += NT) {
             const int p = p0 + (int)threadIdx.x;
             const bool act = p < nwork;
-            const int s = act ? p / jmax : nst;  // lanes past the end: a state of their own
-            const int j = act ? p - s * jmax + 1 : 0;
+            const int s = act ? p / Bj : nst;  // lanes past the end: a state of their own
+            const int jr = act ? p - s * Bj : 0;
+            const int j = jlo + jr;
             int jf = INT_MAX;  // j if W is finite
             if (act) {
                 const int qs = c0 + s;
@@ -332,7 +566,7 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
 #pragma unroll
                     for (int u = 0; u < kIsl; ++u) {
                         const int t = min(t0 + u, nu - 1);
-                        vv[u] = kStage ? Vs[t * R + j] : Vp[(int64_t)t * R + j];
+                        vv[u] = stage ? Vs[t * Bj + jr] : Vp[(int64_t)t * R + j];
                     }
 #pragma unroll
                     for (int u = 0; u < kIsl; ++u) {
@@ -358,7 +592,8 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
                         }
                     }
                 }
-                Wl[s * R + j] = w;
+                if (!kFill && !(w <= bound)) w = kInf;
+                Wl[p] = w;
                 if (kFill) {
                     const int64_t gst = (int64_t)bb * lv.total + lv.soff[d] + s_st[qs];
                     argG[gst * R + j] = (uint8_t)arg;
@@ -385,60 +620,52 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
         }
         __syncthreads();
         // the stage scans: one thread per (state, first layer i) walks the cuts j
-        const int nrow = nst * R;
+        const int Bi = ihi - ilo + 1;
+        const int nrow = nst * Bi;
         for (int p = threadIdx.x; p < nrow; p += NT) {
-            const int s = p / R, i = p - s * R;
+            const int s = p / Bi, i = ilo + p - s * Bi;
             const int qs = c0 + s;
+            if (i < s_lo[qs] || i > s_hi[qs]) continue;
             const int k = s_k[qs];
             const int st = s_st[qs];
             const int64_t gst = (int64_t)bb * lv.total + lv.soff[d] + st;
-            const double *Wrow = Wl + s * R;
+            const double *Wrow = Wl + s * Bj - jlo;
             double best = kInf;
             int bj = 0;
-            if (i <= L - d) {
-                const int jend = min(jmax, s_jhi[qs]);
-                // T_d(i, j, k) = Tr[(j - i - 1) * L + i]: the threads of a wave
-                // read consecutive first layers
-                const double *Ti = T + (((int64_t)(d - 1) * P.nb + bb) * K + k) * L * L + i;
-                bool go = true;
-                // with imbalance pruning the scan starts at the first balanced
-                // cut; it starts no earlier than the first finite continuation
-                const int js = max(P.jlo ? max(i + 1, P.jlo[k * L + i]) : i + 1, s_jlo[qs]);
-                // four cuts' stage costs and continuation values read at a
-                // time (clamped to the row), then taken in order without
-                // branches: the scan stops at the first cost that cannot
-                // improve the running best
-                for (int j0 = js; go && j0 <= jend; j0 += 4) {
-                    double tv[4], wv[4];
+            const int jend = s_jhi[qs];
+            // T_d(i, j, k) = Tr[(j - i - 1) * L + i]: the threads of a wave
+            // read consecutive first layers
+            const double *Ti = T + (((int64_t)(d - 1) * P.nb + bb) * K + k) * L * L + i;
+            bool go = true;
+            // with imbalance pruning the scan starts at the first balanced
+            // cut; it starts no earlier than the first finite continuation
+            const int js = max(P.jlo ? max(i + 1, P.jlo[k * L + i]) : i + 1, s_jlo[qs]);
+            // four cuts' stage costs and continuation values read at a
+            // time (clamped to the row), then taken in order without
+            // branches: the scan stops at the first cost that cannot
+            // improve the running best or exceeds the bound
+            for (int j0 = js; go && j0 <= jend; j0 += 4) {
+                double tv[4], wv[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int jc = min(j0 + u, jend);
-                        tv[u] = Ti[__umul24(jc - i - 1, L)];  // < L^2 <= 2^18
-                        wv[u] = Wrow[jc];
-                    }
+                for (int u = 0; u < 4; ++u) {
+                    const int jc = min(j0 + u, jend);
+                    tv[u] = Ti[__umul24(jc - i - 1, L)];  // < L^2 <= 2^18
+                    wv[u] = Wrow[jc];
+                }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int j = j0 + u;
-                        const bool live = go && j <= jend;
-                        if (kFill) {
-                            const bool stop = live && (tv[u] > bound || tv[u] >= best);
-                            const double y = tv[u] + wv[u];
-                            const bool take = live && !stop && y < best;
-                            best = take ? y : best;
-                            bj = take ? j : bj;
-                            go = go && !stop;
-                        } else {
-                            const bool stop = live && tv[u] >= best;
-                            const double y = tv[u] > wv[u] ? tv[u] : wv[u];
-                            const bool take = live && !stop && y < best;
-                            best = take ? y : best;
-                            go = go && !stop;
-                        }
-                    }
+                for (int u = 0; u < 4; ++u) {
+                    const int j = j0 + u;
+                    const bool live = go && j <= jend;
+                    const bool stop = live && (tv[u] > bound || tv[u] >= best);
+                    const double y = kFill ? tv[u] + wv[u] : (tv[u] > wv[u] ? tv[u] : wv[u]);
+                    const bool take = live && !stop && y < best;
+                    best = take ? y : best;
+                    if (kFill) bj = take ? j : bj;
+                    go = go && !stop;
                 }
             }
             cur[((int64_t)bb * lv.n[d] + st) * R + i] = best;
-            if (kFill && i < L) argF[gst * L + i] = (uint16_t)bj;
+            if (kFill) argF[gst * L + i] = (uint16_t)bj;
             if (i == 0) root[gst] = best;
         }
         __syncthreads();  // the chunk's rows are read; the next chunk rewrites them
@@ -485,10 +712,10 @@ __device__ inline void block_argmin(double *sv, uint32_t *sk) {
 template <bool kRoot>
 __global__ __launch_bounds__(256) void orders_reduce_part(SetLevels lv, const int32_t *__restrict__ masks,
                                                           const double *__restrict__ root, double *part_v,
-                                                          uint32_t *part_k, const int32_t *__restrict__ blist) {
+                                                          uint32_t *part_k, BList blist) {
     __shared__ double sv[256];
     __shared__ uint32_t sk[256];
-    const int c = blockIdx.x, bb = blist ? blist[blockIdx.y] : blockIdx.y;
+    const int c = blockIdx.x, bb = blist.at(blockIdx.y);
     const int64_t per = (lv.total + kReduceChunks - 1) / kReduceChunks;
     const int64_t q0 = (int64_t)c * per, q1 = min(lv.total, q0 + per);
     const double *rv = root + (int64_t)bb * lv.total;
@@ -519,10 +746,13 @@ __global__ __launch_bounds__(256) void orders_reduce_part(SetLevels lv, const in
     }
 }
 
-// No fill root yet for any b (a b whose fill does not run keeps none).
-__global__ __launch_bounds__(256) void orders_clear_roots(int nb, double *rootF, uint32_t *rootKey) {
+// No plan known and no fill root yet for any b (a b whose fill does not run
+// keeps none).
+__global__ __launch_bounds__(256) void orders_clear_b(int nb, unsigned long long *cut, double *rootF,
+                                                      uint32_t *rootKey) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < nb) {
+        cut[t] = 0x7FF0000000000000ull;
         rootF[t] = kInf;
         rootKey[t] = kNoKey;
     }
@@ -530,16 +760,17 @@ __global__ __launch_bounds__(256) void orders_clear_roots(int nb, double *rootF,
 
 __global__ __launch_bounds__(256) void orders_reduce_final(const double *__restrict__ part_v,
                                                            const uint32_t *__restrict__ part_k, double *out_v,
-                                                           uint32_t *out_key, const int32_t *__restrict__ blist) {
+                                                           uint32_t *out_key, double *host_v, BList blist) {
     __shared__ double sv[256];
     __shared__ uint32_t sk[256];
-    const int bb = blist ? blist[blockIdx.x] : blockIdx.x;
+    const int bb = blist.at(blockIdx.x);
     const bool in = threadIdx.x < kReduceChunks;
     sv[threadIdx.x] = in ? part_v[(int64_t)bb * kReduceChunks + threadIdx.x] : kInf;
     sk[threadIdx.x] = in ? part_k[(int64_t)bb * kReduceChunks + threadIdx.x] : kNoKey;
     block_argmin(sv, sk);
     if (threadIdx.x == 0) {
         out_v[bb] = sv[0];
+        if (host_v) host_v[bb] = sv[0];
         if (out_key) out_key[bb] = sk[0];
     }
 }
@@ -550,7 +781,7 @@ __global__ __launch_bounds__(kOrderFinishThreads) void orders_finish(
     DevProblem P, SetLevels lv, const int32_t *__restrict__ masks, const uint16_t *__restrict__ rank,
     const int32_t *gcnt, const double *ent_c, const uint8_t *ent_d, const int64_t *ent_i, const double *X,
     const double *Pst, const double *rootF, const uint32_t *rootKey, const uint16_t *argF, const uint8_t *argG,
-    ComposeResult *res) {
+    ComposeResult *res, ComposeResult *res_host) {
     __shared__ int32_t st_i[kMaxSetIslands], st_j[kMaxSetIslands], st_k[kMaxSetIslands], st_kn[kMaxSetIslands];
     __shared__ int32_t sh_S, sh_bb;
     const int L = P.L, K = P.K;
@@ -624,8 +855,7 @@ __global__ __launch_bounds__(kOrderFinishThreads) void orders_finish(
     }
     __syncthreads();
     const int S = sh_S;
-    if (S == 0) return;
-    const int bb = sh_bb;
+    const int bb = S > 0 ? sh_bb : 0;
     const int wv = threadIdx.x / kWave;
     for (int t = wv; t < S; t += kOrderFinishThreads / kWave) {
         const int d = S - t, i = st_i[t], j = st_j[t], k = st_k[t], kn = st_kn[t];
@@ -633,17 +863,23 @@ __global__ __launch_bounds__(kOrderFinishThreads) void orders_finish(
         resolve_stage(P, gcnt, ent_c, ent_d, ent_i, group_id(P, k, bb, slice_of(P.L, i, j)), i, j, k, d, link,
                       plan.stage[t], res);
     }
+    if (!res_host) return;
+    __syncthreads();
+    store_result(res, res_host, S);
 }
 
 // ---------------------------------------------------------------------------
 // host-side sequencing
 // ---------------------------------------------------------------------------
-// One phase's levels for nrow b: the b of grid row y is blist[y] (all b in
-// order without a list).
+// One phase's levels for nrow b, those of the list.
 template <bool kFill>
 static void run_levels(const DevProblem &P, const SetLevels &lv, const OrdersWs &w, hipStream_t s, int nrow,
-                       const int32_t *blist) {
+                       const BList &blist) {
     const int L = P.L;
+    const double *bounds = kFill ? w.Pst : w.tau;
+    // a level writes the roots of its sets whose band reaches layer 0
+    orders_reset<<<dim3((unsigned)std::min<int64_t>((lv.total + 1023) / 1024, 1024), (unsigned)nrow), dim3(256), 0,
+                   s>>>(w.root, lv.total, blist);
     const dim3 g1((unsigned)(((int64_t)P.K * (L + 1) + 255) / 256), (unsigned)nrow);
     orders_level1<kFill><<<g1, dim3(256), 0, s>>>(P, lv, w.T, w.Pst, w.Vb[1], w.root, blist);
     for (int d = 2; d <= lv.D; ++d) {
@@ -655,31 +891,16 @@ static void run_levels(const DevProblem &P, const SetLevels &lv, const OrdersWs 
         const dim3 grid((unsigned)(binom(P.K, d - 1) * nsplit), (unsigned)nrow);
         const double *prev = w.Vb[(d - 1) & 1];
         double *cur = w.Vb[d & 1];
-        // LDS per block: the set's previous-level rows (when they fit) and a
-        // chunk of continuation rows, within kLevelLds
-        const size_t rowb = (size_t)(L + 1) * sizeof(double);
-        const int fit = (int)std::max<size_t>(1, kLevelLds / rowb);  // rows within the budget
-        const bool stage = d < fit;                                   // nu = d - 1 rows and one more
-        const int C = std::max(1, std::min(std::min(nk, kMaxSetIslands), fit - (stage ? d - 1 : 0)));
-        const size_t lds = ((stage ? (size_t)(d - 1) : 0) + (size_t)C) * rowb;
-        auto go = [&](auto nt, auto st) {
-            constexpr int NT = decltype(nt)::value;
-            orders_level<NT, kFill, decltype(st)::value><<<grid, dim3(NT), lds, s>>>(
-                P, lv, d, nsplit, C, w.masks, w.rank, w.T, w.X, prev, cur, w.root, w.Pst, w.argF, w.argG, blist);
-        };
-        auto pick = [&](auto nt) {
-            if (stage)
-                go(nt, std::true_type{});
-            else
-                go(nt, std::false_type{});
-        };
-        pick(std::integral_constant<int, kLevelThreads>{});
+        orders_level<kLevelThreads, kFill>
+            <<<grid, dim3(kLevelThreads), sizeof(double) * kLevelLds, s>>>(
+                P, lv, d, nsplit, kLevelLds, w.masks, w.rank, w.T, w.X, prev, cur, w.root, bounds, w.ml, w.argF,
+                w.argG, blist);
     }
 }
 
 hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host, const int64_t *surv, int64_t n_surv,
                                  const double *cost, const uint8_t *dmax, void *ws, hipStream_t s,
-                                 ComposeResult **result_dev) {
+                                 ComposeResult **result_dev, const ComposeHost *host) {
     if (P.K > kMaxSetIslands || P.L > kMaxLayers || P.nb > 65535) return hipErrorInvalidValue;
     const SetLevels lv = set_levels(P);
     const OrdersWs w = carve_orders(P, n_surv, ws);
@@ -692,81 +913,82 @@ hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host,
                                                                                    w.g.ent_d, w.T);
     const int64_t nx = (int64_t)P.nb * P.K * P.K * (P.L + 1);
     orders_links<<<dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, s>>>(P, w.X);
-    // phase 1 for every b: the least bottleneck P*_b
+    // phase 1 for every b: the least bottleneck P*_b within the bound (+inf
+    // where none is looked for, or none can win)
     const int nb = P.nb;
-    run_levels<false>(P, lv, w, s, nb, nullptr);
+    const BList every{};
+    // a small search skips the bounds and fills every b: host and device round
+    // trips would cost more than they save
+    const bool small = (int64_t)nb * lv.total * (P.L + 1) < kPruneCells;
+    orders_clear_b<<<dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s>>>(nb, w.cut, w.rootF, w.rootKey);
+    if (!small)
+        orders_cutoff<<<dim3(kCutOrders, (unsigned)nb), dim3(kCutThreads), 0, s>>>(P, lv.D, w.T, w.X, w.fixed, w.cut);
+    orders_bound<<<dim3(1), dim3(256), 0, s>>>(P, lv.D, w.cut, w.tau);
+    auto longest = [&](const double *bound) {
+        const int64_t n = (int64_t)nb * (lv.D + 2) * P.K;
+        orders_longest<<<dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s>>>(P, lv.D, w.T, bound, w.ml);
+    };
+    longest(w.tau);
+    run_levels<false>(P, lv, w, s, nb, every);
+    double *hv = host && host->dlim ? (double *)host->dlim : nullptr;  // nb pinned words, and their device view
+    double *hv_dev = hv ? (double *)host->dlim_dev : nullptr;
     orders_reduce_part<false><<<dim3(kReduceChunks, (unsigned)nb), dim3(256), 0, s>>>(lv, w.masks, w.root, w.part_v,
-                                                                                     w.part_k, nullptr);
-    orders_reduce_final<<<dim3((unsigned)nb), dim3(256), 0, s>>>(w.part_v, w.part_k, w.Pst, nullptr, nullptr);
+                                                                                     w.part_k, every);
+    orders_reduce_final<<<dim3((unsigned)nb), dim3(256), 0, s>>>(w.part_v, w.part_k, w.Pst, nullptr, hv_dev, every);
+    longest(w.Pst);
+    // the values of the nb words at `dev`, through the pinned words or a copy
+    auto read_back = [&](const double *dev, double *out) -> hipError_t {
+        hipError_t e = hv ? hipSuccess : hipMemcpyAsync(out, dev, sizeof(double) * nb, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e == hipSuccess && hv) std::copy(hv, hv + nb, out);
+        return e;
+    };
+    auto fill_run = [&](const std::vector<int32_t> &bl) {
+        for (size_t at = 0; at < bl.size(); at += kRunB) {
+            BList list{};
+            list.n = (int32_t)std::min<size_t>(kRunB, bl.size() - at);
+            std::copy(bl.begin() + at, bl.begin() + at + list.n, list.b);
+            run_levels<true>(P, lv, w, s, list.n, list);
+            orders_reduce_part<true><<<dim3(kReduceChunks, (unsigned)list.n), dim3(256), 0, s>>>(
+                lv, w.masks, w.root, w.part_v, w.part_k, list);
+            orders_reduce_final<<<dim3((unsigned)list.n), dim3(256), 0, s>>>(w.part_v, w.part_k, w.rootF, w.rootKey,
+                                                                            hv_dev, list);
+        }
+    };
     // phase 2 only where a b can still win: its fill is at least P*_b (every
     // stage and link adds a non-negative time and one of them is at least
     // P*_b), so T_b >= (m - 1) P*_b + P*_b.  The most promising b runs first;
     // then every b whose bound beats its T (ties to the smaller b).
-    orders_clear_roots<<<dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s>>>(nb, w.rootF, w.rootKey);
     std::vector<int32_t> rows;
-    if ((int64_t)nb * lv.total * (P.L + 1) < kPruneCells) {
-        // a small search: every b in one run beats two host round trips
+    if (small) {
         for (int bi = 0; bi < nb; ++bi) rows.push_back(bi);
-        hipError_t e = hipMemcpyAsync(w.blist, rows.data(), sizeof(int32_t) * nb, hipMemcpyHostToDevice, s);
+        fill_run(rows);
+    } else {
+        std::vector<double> pst(nb), lb(nb, kInf), mm1(nb), f(nb);
+        hipError_t e = read_back(w.Pst, pst.data());
         if (e != hipSuccess) return e;
-        run_levels<true>(P, lv, w, s, nb, w.blist);
-        orders_reduce_part<true><<<dim3(kReduceChunks, (unsigned)nb), dim3(256), 0, s>>>(lv, w.masks, w.root,
-                                                                                        w.part_v, w.part_k, w.blist);
-        orders_reduce_final<<<dim3((unsigned)nb), dim3(256), 0, s>>>(w.part_v, w.part_k, w.rootF, w.rootKey,
-                                                                    w.blist);
-        orders_finish<<<dim3(1), dim3(kOrderFinishThreads), 0, s>>>(P, lv, w.masks, w.rank, w.g.gcnt, w.g.ent_c,
-                                                                    w.g.ent_d, w.g.ent_i, w.X, w.Pst, w.rootF,
-                                                                    w.rootKey, w.argF, w.argG, w.res);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(s);  // the b list above must outlive its copy
-        return e;
-    }
-    std::vector<double> pst(nb);
-    hipError_t e = hipMemcpyAsync(pst.data(), w.Pst, sizeof(double) * nb, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return e;
-    std::vector<double> lb(nb, kInf), mm1(nb);
-    int b0 = -1;
-    for (int bi = 0; bi < nb; ++bi) {
-        mm1[bi] = (double)(P.B / bvals_host[bi] - 1);
-        if (!(pst[bi] < kInf)) continue;
-        lb[bi] = (mm1[bi] * pst[bi]) + pst[bi];
-        if (b0 < 0 || lb[bi] < lb[b0]) b0 = bi;
-    }
-    auto fill_run = [&](const std::vector<int32_t> &bl) -> hipError_t {
-        hipError_t e2 = hipMemcpyAsync(w.blist, bl.data(), sizeof(int32_t) * bl.size(), hipMemcpyHostToDevice, s);
-        if (e2 != hipSuccess) return e2;
-        const int n = (int)bl.size();
-        run_levels<true>(P, lv, w, s, n, w.blist);
-        orders_reduce_part<true><<<dim3(kReduceChunks, (unsigned)n), dim3(256), 0, s>>>(lv, w.masks, w.root,
-                                                                                       w.part_v, w.part_k, w.blist);
-        orders_reduce_final<<<dim3((unsigned)n), dim3(256), 0, s>>>(w.part_v, w.part_k, w.rootF, w.rootKey,
-                                                                   w.blist);
-        return hipGetLastError();
-    };
-    if (b0 >= 0) {
-        rows.assign(1, b0);
-        e = fill_run(rows);
-        double f0 = kInf;
-        if (e == hipSuccess) e = hipMemcpyAsync(&f0, w.rootF + b0, sizeof(double), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return e;
-        const double t0 = (mm1[b0] * pst[b0]) + f0;
-        std::vector<int32_t> rest;
-        for (int bi = 0; bi < nb; ++bi)
-            if (bi != b0 && lb[bi] < kInf && (lb[bi] < t0 || (lb[bi] == t0 && bi < b0))) rest.push_back(bi);
-        if (!rest.empty()) {
-            rows = rest;
-            e = fill_run(rows);
+        int b0 = -1;
+        for (int bi = 0; bi < nb; ++bi) {
+            mm1[bi] = (double)(P.B / bvals_host[bi] - 1);
+            if (!(pst[bi] < kInf)) continue;
+            lb[bi] = (mm1[bi] * pst[bi]) + pst[bi];
+            if (b0 < 0 || lb[bi] < lb[b0]) b0 = bi;
+        }
+        if (b0 >= 0) {
+            fill_run({b0});
+            e = read_back(w.rootF, f.data());
             if (e != hipSuccess) return e;
+            const double t0 = (mm1[b0] * pst[b0]) + f[b0];
+            for (int bi = 0; bi < nb; ++bi)
+                if (bi != b0 && lb[bi] < kInf && (lb[bi] < t0 || (lb[bi] == t0 && bi < b0))) rows.push_back(bi);
+            fill_run(rows);
         }
     }
     orders_finish<<<dim3(1), dim3(kOrderFinishThreads), 0, s>>>(P, lv, w.masks, w.rank, w.g.gcnt, w.g.ent_c,
                                                                 w.g.ent_d, w.g.ent_i, w.X, w.Pst, w.rootF,
-                                                                w.rootKey, w.argF, w.argG, w.res);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(s);  // the b list above must outlive its copy
-    return e;
+                                                                w.rootKey, w.argF, w.argG, w.res,
+                                                                host ? host->res_dev : nullptr);
+    return hipGetLastError();
 }
 
 }  // namespace tg

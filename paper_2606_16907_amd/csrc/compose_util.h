@@ -2,6 +2,8 @@
 // of the candidate list and the resolution of a plan stage's candidate.
 #pragma once
 
+#include <cstddef>
+
 #include "tg_device.h"
 
 #pragma clang fp contract(off)
@@ -114,6 +116,16 @@ __device__ inline void resolve_stage(const DevProblem &P, const int32_t *gcnt, c
     // in flight: min(d, m) micro-batches, one when offloaded
     sg.mem_bytes = state + (fmin(c.of ? 1.0 : (double)d, c.m_real) * A1);
     sg.link_out = link;
+}
+
+// A result's header and its S stages into host memory, by one block (8-byte words).
+__device__ inline void store_result(const ComposeResult *res, ComposeResult *res_host, int S) {
+    static_assert(offsetof(ComposeResult, plan) % 8 == 0 && offsetof(tg_plan, stage) % 8 == 0 &&
+                      sizeof(tg_stage) % 8 == 0, "result words");
+    const int n = (int)((offsetof(ComposeResult, plan) + offsetof(tg_plan, stage) + sizeof(tg_stage) * S) / 8);
+    const uint64_t *src = (const uint64_t *)res;
+    uint64_t *dst = (uint64_t *)res_host;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) dst[k] = src[k];
 }
 
 }  // namespace tg

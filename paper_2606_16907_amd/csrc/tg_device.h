@@ -171,11 +171,13 @@ struct ComposeResult {
     tg_plan plan;
 };
 // Pinned host memory, each block seen from the host and from the device (the
-// address kernels store to).  The kernels store the fill depth limits (at
-// least nb int32) and the result straight into it, and the host waits on the
-// event `ev` (on the current device) for the limits while the first fill
-// levels run.  Without it (null) the limits are copied back by a stream
-// synchronisation and the result stays on the device alone.
+// address kernels store to).  The kernels store the fill depth limits (nb
+// int32, in room for nb doubles) and the result straight into it, and the host
+// waits on the event `ev` (on the current device) for the limits while the
+// first fill levels run.  Without it (null) the limits are copied back by a
+// stream synchronisation and the result stays on the device alone.  The
+// all-orders composition stores its bottlenecks, then a fill's values (nb
+// doubles) in the place of the limits and needs no event.
 struct ComposeHost {
     int32_t *dlim, *dlim_dev;
     ComposeResult *res, *res_dev;
@@ -234,7 +236,7 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
 size_t compose_orders_ws_bytes(const DevProblem &P, int64_t n_surv);
 hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host, const int64_t *surv, int64_t n_surv,
                                  const double *cost, const uint8_t *dmax, void *ws, hipStream_t s,
-                                 ComposeResult **result_dev);
+                                 ComposeResult **result_dev, const ComposeHost *host = nullptr);
 // Synchronises the stream several times (once per search round).  On
 // success the result is also stored into the stage at *result_host (host
 // view), read once the stream is synchronised.

@@ -114,3 +114,32 @@ def test_all_orders_rejects_more_than_16_islands():
     with pytest.raises(ValueError, match="at least"):
         p.tg_compose_pipeline_all_orders(torch.empty(0, dtype=torch.int64, device="cuda"), cost, dmax,
                                          workspace=ws)
+
+
+def _banded(seed, L, K, memory, eps, tight):
+    """Large enough (7 b x K 2^(K-1) states x rows) for the bounds from a few
+    island orders and the bands of rows they leave."""
+    inst = scaled(random_tiny(seed, L_range=(L, L), K_range=(K, K), tight=tight), memory=memory)
+    inst["space"].update(global_batch=24, mb=[1, 2, 3, 4], imbalance_eps=eps)
+    return inst
+
+
+@pytest.mark.parametrize("seed,L,K,memory,eps,tight", [
+    (4101, 28, 12, 4.0, 0.0, False),   # uneven layers, some links absent
+    (4102, 30, 12, 3.0, 0.0, True),    # depth limits bind
+    (4103, 31, 12, 8.0, 3.0, False),   # imbalance pruning: stage costs not monotone from the first cut
+    (4104, 60, 11, 20.0, 0.0, False),
+    (4105, 28, 12, 1.0, 0.0, True)])   # few plans: the memory order alone has none
+def test_all_orders_bands(seed, L, K, memory, eps, tight):
+    say("banded", seed)
+    inst = _banded(seed, L, K, memory, eps, tight)
+    o, p = Oracle(inst), T.Problem(inst)
+    assert p.n_b * K * 2 ** (K - 1) * (L + 1) >= 1 << 22
+    ost, oplan, _ = o.compose_all_orders(o.prune())
+    surv, cost, dmax = _gpu(p)
+    ws = p.compose_all_orders_workspace(int(surv.numel()))
+    for rep in range(2):
+        st, plan = p.tg_compose_pipeline_all_orders(surv, cost, dmax, workspace=ws)
+        assert st == (T.TG_ENOPLAN if ost != 0 else 0)
+        if ost == 0:
+            plan_equal(plan, oplan)
