@@ -14,19 +14,29 @@
 // it, else marked, until every pair is marked.  A union's Eq. 3 outcome
 // depends only on its own nodes, so a failed pair stays failed while both
 // clusters last, and the next merge is the highest pair whose union passes.
-// One block per group runs it in rounds: each cluster's row keeps its best
-// unmarked partner, known to pass (clean) or untested (dirty); when the best
-// clean pair is above every dirty one it is merged, else every dirty pair
-// above it is tested at once (a wave each) and the failures marked.  The
-// group's linkage, marks and per-cluster least links (for each cluster and
-// node, the node's slowest link into the cluster) sit in matrices over the
-// group's own node numbering; a cluster's members are one contiguous range
-// of a permutation, so a test gives each lane a member: its slowest link
-// inside the union from its own cluster's value and the other cluster's
-// entry, its fastest link leaving from its bandwidth row sorted once (the
-// first entry outside the union, from where its own cluster ends).  A finish
-// pass numbers islands by their smallest node and reduces the island
-// attributes and island-to-island bandwidths (least over node pairs).
+// The clustering runs in stages of falling thresholds.  Pairs linked at least
+// as fast as a threshold lie in one component of the graph of such links, and
+// what happens among them (linkages, marks, Eq. 3) touches no other component;
+// the pairs above the threshold all come before the rest.  So a stage runs
+// every component on a block of its own, over the pairs above its threshold
+// only, and the next stage goes on from the clusters and marks it left: the
+// same merges in the same order within each component as one serial run, most
+// of them side by side (a leaf switch's nodes first, then a pod's, then what is
+// left of the group).  A block works in rounds: each cluster's row keeps its
+// best unmarked partner, known to pass (clean) or untested (dirty); when the
+// best clean pair is above every dirty one it is merged, else every dirty pair
+// above it is tested at once (a wave each) and the failures marked.  Linkage,
+// marks and per-cluster least links (for each cluster and node, the node's
+// slowest link into the cluster) sit in matrices over the group's node
+// numbering; a cluster's members are one contiguous range of a permutation, so
+// a test gives each lane a member: its slowest link inside the union from its
+// own cluster's value and the other cluster's entry, its fastest link leaving
+// from its bandwidth row sorted once (the first entry outside the union, from
+// where its own cluster ends).  A finish pass numbers islands by their smallest
+// node and reduces the island attributes and island-to-island bandwidths (least
+// over node pairs).  Bound by the rounds' chains of dependent loads and
+// barriers, so by the number of rounds in a row: 1024 nodes took 6.1 ms of
+// clustering with a block per group, 0.57 ms in stages.
 #include <stdint.h>
 
 #include <vector>
@@ -39,8 +49,18 @@ namespace tg {
 
 constexpr int kMaxNodes = 4096;
 constexpr int kGroupThreads = 1024;
+// Merge blocks: eight waves for a component of up to kSmallComp nodes (a leaf's
+// pairs are tested at once, a wave each; one wave took 158 us over 1024 nodes'
+// leaves, eight 91), sixteen above.
+constexpr int kSmallComp = 64;
+constexpr int kSmallThreads = 512;
 constexpr int kMergeThreads = 1024;
-constexpr int kMergeWaves = kMergeThreads / 64;
+// The stages' thresholds, as shares of the fastest link between nodes of one
+// group: fabric levels differ by more than 2, so the first separates the
+// fastest level (leaves) and the second the next (pods); the last stage takes
+// every pair of a group.  Any shares give the same islands.
+constexpr double kStageShare[] = {0.5, 0.125};
+constexpr int kStages = 3;
 constexpr double kNoPair = -__builtin_huge_val();
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -64,6 +84,13 @@ struct IslandWs {
     int32_t *nxl;       // [n] that entry's number inside the group (-1: another group, or none)
     double *outv;       // [n] the node's bandwidth to it (-inf: none)
     int32_t *cl;        // [n] cluster (its smallest node) of each node
+    unsigned long long *lmax;  // [1] fastest link between nodes of one group (bits of a double)
+    int32_t *uf;        // [n] union-find parents of a stage's components
+    int32_t *comp;      // [n] component of each node
+    int32_t *lc;        // [n] its number inside the component
+    int32_t *cstart;    // [n + 1] component c's nodes are cnodes[cstart[c] .. cstart[c + 1])
+    int32_t *cnodes;    // [n]
+    int32_t *ncomp;     // [1]
     int32_t *err;       // [2] a merge loop overran its round bound (an internal error); first bad node_bw entry
     int32_t *island_of; // [n]
     int32_t *out_k;     // [1]
@@ -100,6 +127,13 @@ static IslandWs carve_islands(int64_t n, void *base) {
     w.nxl = (int32_t *)take(4 * n);
     w.outv = (double *)take(8 * n);
     w.cl = (int32_t *)take(4 * n);
+    w.lmax = (unsigned long long *)take(8);
+    w.uf = (int32_t *)take(4 * n);
+    w.comp = (int32_t *)take(4 * n);
+    w.lc = (int32_t *)take(4 * n);
+    w.cstart = (int32_t *)take(4 * (n + 1));
+    w.cnodes = (int32_t *)take(4 * n);
+    w.ncomp = (int32_t *)take(4);
     w.err = (int32_t *)take(8);
     w.island_of = (int32_t *)take(4 * n);
     w.out_k = (int32_t *)take(4);
@@ -292,31 +326,179 @@ __global__ __launch_bounds__(256) void islands_link_init(int n, const double *__
                                                          const int32_t *__restrict__ gstart,
                                                          const int32_t *__restrict__ lq,
                                                          const int64_t *__restrict__ goff, double *L, uint8_t *M,
-                                                         double *XT, double *inown, int32_t *cl) {
+                                                         double *XT, double *inown, int32_t *pos, int32_t *cl,
+                                                         int32_t *uf, unsigned long long *lmax) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)n * n) return;
-    const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);
-    if (v == 0) {
-        cl[u] = u;
-        inown[u] = __builtin_huge_val();
+    // the block's fastest link between nodes of one group, reduced per wave, then
+    // one update a block
+    __shared__ double wmax[256 / kWave];
+    double fastest = 0.0;
+    auto link = [&]() {
+        if (t >= (int64_t)n * n) return;
+        const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);
+        if (v == 0) {
+            cl[u] = u;
+            inown[u] = __builtin_huge_val();
+            pos[u] = 0;
+            uf[u] = u;
+        }
+        const int g = grp[u];
+        if (grp[v] != g) return;
+        const int64_t nm = gstart[g + 1] - gstart[g];
+        const int64_t qu = lq[u], qv = lq[v], base = goff[g];
+        double l = kNoPair, x = __builtin_huge_val();
+        if (u != v) {
+            x = e[t];
+            const double y = e[(int64_t)v * n + u];
+            l = x < y ? x : y;
+        }
+        L[base + qu * nm + qv] = l;
+        M[base + qu * nm + qv] = 0;
+        XT[base + qv * nm + qu] = x;
+        if (u != v) fastest = l == 0.0 ? 0.0 : l;
+    };
+    link();
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) fastest = fmax(fastest, __shfl_xor(fastest, off));
+    if (wave_lane() == 0) wmax[threadIdx.x / kWave] = fastest;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < 256 / kWave; ++w) fastest = fmax(fastest, wmax[w]);
+        // links are non-negative: their bits order like the values; a plain
+        // look first, so that few blocks update
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(fastest);
+        if (bits > __hip_atomic_load(lmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(lmax, bits);
     }
-    const int g = grp[u];
-    if (grp[v] != g) return;
-    const int64_t nm = gstart[g + 1] - gstart[g];
-    const int64_t qu = lq[u], qv = lq[v], base = goff[g];
-    double l = kNoPair, x = __builtin_huge_val();
-    if (u != v) {
-        x = e[t];
-        const double y = e[(int64_t)v * n + u];
-        l = x < y ? x : y;
-    }
-    L[base + qu * nm + qv] = l;
-    M[base + qu * nm + qv] = 0;
-    XT[base + qv * nm + qu] = x;
 }
 
 // ---------------------------------------------------------------------------
-// step (3): agglomerative clustering, one block per group
+// a stage's components
+// ---------------------------------------------------------------------------
+// Root of u; parents only ever move towards smaller nodes of the same
+// component, so a stale read costs a step, not the result.
+__device__ inline int uf_find(int32_t *uf, int u) {
+    for (;;) {
+        const int p = __hip_atomic_load(uf + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (p == u) return u;
+        u = p;
+    }
+}
+
+// Joins the nodes of every pair of a group linked at least as fast as the
+// stage's threshold.  Parents decrease, so each retry works on a smaller root:
+// the loop ends.
+__global__ __launch_bounds__(256) void islands_unite(int n, double share, const unsigned long long *__restrict__ lmax,
+                                                     const double *__restrict__ e, const int32_t *__restrict__ grp,
+                                                     int32_t *uf) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * n) return;
+    const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);
+    if (u >= v || grp[u] != grp[v]) return;
+    const double tau = share * __longlong_as_double((long long)*lmax);
+    if (!(e[t] >= tau) || !(e[(int64_t)v * n + u] >= tau)) return;
+    int a = uf_find(uf, u), b = uf_find(uf, v);
+    while (a != b) {
+        if (a < b) {
+            const int x = a;
+            a = b;
+            b = x;
+        }
+        const int old = atomicCAS(&uf[a], a, b);
+        if (old == a) break;
+        a = uf_find(uf, old);
+        b = uf_find(uf, b);
+    }
+}
+
+// Component lists from the roots (one block).
+__global__ __launch_bounds__(kGroupThreads) void islands_components(int n, int32_t *uf, int32_t *comp, int32_t *lc,
+                                                                    int32_t *cstart, int32_t *cnodes,
+                                                                    int32_t *ncomp) {
+    __shared__ int32_t cnt[kMaxNodes];   // nodes of a root's component, then where its list starts
+    __shared__ int32_t id[kMaxNodes];    // its number
+    __shared__ int32_t scan_lds[kGroupThreads / kWave + 1];
+    for (int u = threadIdx.x; u < n; u += kGroupThreads) cnt[u] = 0;
+    __syncthreads();
+    for (int u = threadIdx.x; u < n; u += kGroupThreads) {
+        const int r = uf_find(uf, u);
+        comp[u] = r;
+        lc[u] = atomicAdd(&cnt[r], 1);
+    }
+    __syncthreads();
+    int32_t carry = 0, numbered = 0;
+    for (int base = 0; base < n; base += kGroupThreads) {
+        const int u = base + (int)threadIdx.x;
+        const int32_t c = u < n ? cnt[u] : 0;
+        int32_t tot, roots;
+        const int32_t at = block_excl_scan<int32_t>(c, scan_lds, &tot);
+        const int32_t k = block_excl_scan<int32_t>(c > 0 ? 1 : 0, scan_lds, &roots);
+        if (c > 0) {
+            id[u] = numbered + k;
+            cnt[u] = carry + at;
+            cstart[numbered + k] = carry + at;
+        }
+        carry += tot;
+        numbered += roots;
+    }
+    if (threadIdx.x == 0) {
+        *ncomp = numbered;
+        cstart[numbered] = n;
+    }
+    __syncthreads();
+    for (int u = threadIdx.x; u < n; u += kGroupThreads) {
+        const int r = comp[u];
+        cnodes[cnt[r] + lc[u]] = u;
+        comp[u] = id[r];
+    }
+}
+
+// Linkage and least links between the clusters a stage starts from, for pairs
+// inside one component: no pair has any yet, then each node pair lowers its
+// clusters' entries (links are non-negative: their bits order like the
+// values).
+__global__ __launch_bounds__(256) void islands_stage_clear(int n, const int32_t *__restrict__ grp,
+                                                           const int32_t *__restrict__ gstart,
+                                                           const int32_t *__restrict__ lq,
+                                                           const int64_t *__restrict__ goff,
+                                                           const int32_t *__restrict__ comp,
+                                                           const int32_t *__restrict__ cl, double *L, double *XT) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * n) return;
+    const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);
+    if (comp[u] != comp[v] || cl[u] != u) return;
+    const int g = grp[u];
+    const int64_t nm = gstart[g + 1] - gstart[g], at = goff[g] + (int64_t)lq[u] * nm + lq[v];
+    XT[at] = __builtin_huge_val();
+    if (cl[v] == v) L[at] = u == v ? kNoPair : __builtin_huge_val();
+}
+
+__global__ __launch_bounds__(256) void islands_stage_links(int n, const double *__restrict__ e,
+                                                           const int32_t *__restrict__ grp,
+                                                           const int32_t *__restrict__ gstart,
+                                                           const int32_t *__restrict__ lq,
+                                                           const int64_t *__restrict__ goff,
+                                                           const int32_t *__restrict__ comp,
+                                                           const int32_t *__restrict__ cl, double *L, double *XT) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * n) return;
+    const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);  // the link from u to v
+    if (u == v || comp[u] != comp[v]) return;
+    const int g = grp[u], c = cl[u], d = cl[v];
+    const int64_t nm = gstart[g + 1] - gstart[g], base = goff[g];
+    const double x = e[t] == 0.0 ? 0.0 : e[t];
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
+    unsigned long long *xt = (unsigned long long *)&XT[base + (int64_t)lq[d] * nm + lq[u]];
+    if (bits < __hip_atomic_load(xt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(xt, bits);
+    if (c == d) return;
+    unsigned long long *l1 = (unsigned long long *)&L[base + (int64_t)lq[c] * nm + lq[d]];
+    unsigned long long *l2 = (unsigned long long *)&L[base + (int64_t)lq[d] * nm + lq[c]];
+    if (bits < __hip_atomic_load(l1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(l1, bits);
+    if (bits < __hip_atomic_load(l2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(l2, bits);
+}
+
+// ---------------------------------------------------------------------------
+// step (3): agglomerative clustering, one block per component
 // ---------------------------------------------------------------------------
 // Pairs are ordered by linkage (higher first), then by the smaller node id of
 // the pair's two clusters, then by the larger one: key (l, x, y), x < y the
@@ -329,11 +511,13 @@ __device__ inline bool pair_before(double l1, int x1, int y1, double l2, int x2,
     return key_before(l1, min(x1, y1), max(x1, y1), l2, min(x2, y2), max(x2, y2));
 }
 
-// The group's state in LDS, by node number inside the group (q < nm).  A
-// cluster is named by its representative, its node with the least id; its
-// members are perm[st[c] .. st[c] + sz[c]).
+// The component's state in LDS, by node number inside it (q < nm).  A cluster is
+// named by its representative, its node with the least id; its members are
+// perm[st[c] .. st[c] + sz[c]).
+template <int kMaxNodes, int kMergeWaves>
 struct MergeLds {
     int32_t gid[kMaxNodes];  // node id of q
+    int16_t mq[kMaxNodes];   // its number inside the group (the matrices' numbering)
     int16_t rep[kMaxNodes];  // representative of q's cluster
     int16_t perm[kMaxNodes];
     int16_t tmp[kMaxNodes];  // rotation buffer of perm
@@ -350,11 +534,20 @@ struct MergeLds {
     int32_t cnt;
 };
 
-// Row c's best unmarked partner among the group's clusters, by one wave.
-__device__ inline void merge_row_best(MergeLds &S, int c, int nm, const double *__restrict__ L,
-                                      const uint8_t *__restrict__ M, int lane) {
-    const double *Lr = L + (int64_t)c * nm;
-    const uint8_t *Mr = M + (int64_t)c * nm;
+// The group's matrices.
+struct MergeMat {
+    double *L;   // linkage, row and column: cluster
+    uint8_t *M;  // marked pairs
+    double *XT;  // row: cluster, column: node
+    int64_t nm;  // the group's nodes
+};
+
+// Row c's best unmarked partner among the component's clusters, linked at least
+// as fast as tau, by one wave.
+template <typename Lds>
+__device__ inline void merge_row_best(Lds &S, int c, int nm, const MergeMat &A, double tau, int lane) {
+    const double *Lr = A.L + (int64_t)S.mq[c] * A.nm;
+    const uint8_t *Mr = A.M + (int64_t)S.mq[c] * A.nm;
     constexpr int kBatch = 16;  // row entries per lane with their loads in flight together
     double b = kNoPair;
     int a = -1;
@@ -364,13 +557,14 @@ __device__ inline void merge_row_best(MergeLds &S, int c, int nm, const double *
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             const int v = v0 + k * kWave;
-            l[k] = v < nm ? Lr[v] : kNoPair;
-            mk[k] = v < nm ? Mr[v] : 1;
+            const int q = v < nm ? S.mq[v] : 0;
+            l[k] = v < nm ? Lr[q] : kNoPair;
+            mk[k] = v < nm ? Mr[q] : 1;
         }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             const int v = v0 + k * kWave;
-            if (v < nm && v != c && S.rep[v] == v && !mk[k] && l[k] != kNoPair &&
+            if (v < nm && v != c && S.rep[v] == v && !mk[k] && l[k] != kNoPair && l[k] >= tau &&
                 (a < 0 || l[k] > b || (l[k] == b && S.gid[v] < S.gid[a]))) {
                 b = l[k];
                 a = v;
@@ -393,9 +587,10 @@ __device__ inline void merge_row_best(MergeLds &S, int c, int nm, const double *
 }
 
 // Eq. 3 for the union of clusters c and d, by one wave: a lane per member.
-__device__ inline bool merge_eq3(const MergeLds &S, int c, int d, int g, int n, int nm, const double *__restrict__ e,
-                                 const int32_t *__restrict__ srt, const int32_t *__restrict__ grp,
-                                 const int32_t *__restrict__ lq, const double *__restrict__ XT,
+template <typename Lds>
+__device__ inline bool merge_eq3(const Lds &S, int c, int d, int g, int n, const MergeMat &A,
+                                 const double *__restrict__ e, const int32_t *__restrict__ srt,
+                                 const int32_t *__restrict__ grp, const int32_t *__restrict__ lq,
                                  const double *__restrict__ inown, const int32_t *__restrict__ pos,
                                  const int32_t *__restrict__ nxl, const double *__restrict__ outv, int lane) {
     bool pass = true;
@@ -405,7 +600,7 @@ __device__ inline bool merge_eq3(const MergeLds &S, int c, int d, int g, int n, 
         for (int t = t0 + lane; t < t1; t += kWave) {
             const int m = S.perm[t];
             const int gm = S.gid[m];
-            const double x = XT[(int64_t)oth * nm + m];
+            const double x = A.XT[(int64_t)S.mq[oth] * A.nm + S.mq[m]];
             const double io = inown[gm];
             const double in = x < io ? x : io;
             // the fastest link leaving the union: the first entry past the own
@@ -435,43 +630,77 @@ __device__ inline bool merge_eq3(const MergeLds &S, int c, int d, int g, int n, 
     return __ballot(!pass) == 0;
 }
 
-__global__ __launch_bounds__(kMergeThreads) void islands_merge(int n, const double *__restrict__ e,
-                                                               const int32_t *__restrict__ srt,
-                                                               const int32_t *__restrict__ grp,
-                                                               const int32_t *__restrict__ lq,
-                                                               const int32_t *__restrict__ gstart,
-                                                               const int32_t *__restrict__ gnodes,
-                                                               const int32_t *__restrict__ ngroups,
-                                                               const int64_t *__restrict__ goff, double *Lg,
-                                                               uint8_t *Mg, double *XTg, double *inown, int32_t *pos,
-                                                               int32_t *nxl, double *outv, int32_t *cl, int32_t *err) {
-    __shared__ MergeLds S;
+// A stage's components: lists, and each node's component and number inside it.
+struct StageComps {
+    const int32_t *of, *num, *start, *nodes, *count;
+};
+
+// One component of a stage (components of kMinNodes to kNodes nodes; the others
+// leave).  grp, lq: the component and the number inside it of each node.
+template <int kMergeThreads, int kMinNodes, int kNodes>
+__global__ __launch_bounds__(kMergeThreads) void islands_merge(
+    int n, double share, const unsigned long long *__restrict__ lmax, const double *__restrict__ e,
+    const int32_t *__restrict__ srt, StageComps comps, const int32_t *__restrict__ ggrp,
+    const int32_t *__restrict__ glq, const int32_t *__restrict__ gstart, const int64_t *__restrict__ goff, double *Lg,
+    uint8_t *Mg, double *XTg, double *inown, int32_t *pos, int32_t *nxl, double *outv, int32_t *cl, int32_t *err) {
+    constexpr int kMergeWaves = kMergeThreads / kWave;
+    __shared__ MergeLds<kNodes, kMergeWaves> S;
+    __shared__ int32_t scan_lds[kMergeWaves + 1];
     const int g = blockIdx.x;
-    if (g >= *ngroups) return;
-    const int nm = gstart[g + 1] - gstart[g];
-    if (nm < 2) return;
-    double *L = Lg + goff[g];
-    uint8_t *M = Mg + goff[g];
-    double *XT = XTg + goff[g];
+    if (g >= *comps.count) return;
+    const int c0 = comps.start[g], nm = comps.start[g + 1] - c0;
+    if (nm < kMinNodes || nm > kNodes) return;
+    const int32_t *grp = comps.of, *lq = comps.num;
+    const int gg0 = ggrp[comps.nodes[c0]];
+    const MergeMat A{Lg + goff[gg0], Mg + goff[gg0], XTg + goff[gg0], gstart[gg0 + 1] - gstart[gg0]};
+    auto at = [&](int c, int v) { return (int64_t)S.mq[c] * A.nm + S.mq[v]; };  // entry (c, v) of a matrix
+    const double tau = share > 0.0 ? share * __longlong_as_double((long long)*lmax) : kNoPair;
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+    int32_t *cur = (int32_t *)S.rb;  // scratch until the rows are set
     for (int q = threadIdx.x; q < nm; q += kMergeThreads) {
-        const int gm = gnodes[gstart[g] + q];
+        const int gm = comps.nodes[c0 + q];
         S.gid[q] = gm;
-        S.rep[q] = (int16_t)q;
-        S.perm[q] = (int16_t)q;
-        S.st[q] = (int16_t)q;
-        S.sz[q] = 1;
+        S.mq[q] = (int16_t)glq[gm];
         S.vp[q] = -1;
         S.redo[q] = 0;
-        // alone in its cluster: the first entry of its sorted row (which
-        // leaves the node itself out) is outside
-        const int w = srt[(int64_t)gm * n];
-        pos[gm] = 0;
-        nxl[gm] = grp[w] == g ? lq[w] : -1;
-        outv[gm] = e[(int64_t)gm * n + w];
+        S.ra[q] = -1;
+        cur[q] = 0;
     }
     __syncthreads();
-    for (int q = wv; q < nm; q += kMergeWaves) merge_row_best(S, q, nm, L, M, lane);
+    // the clusters so far: representatives, sizes, member ranges
+    for (int q = threadIdx.x; q < nm; q += kMergeThreads) {
+        const int r = lq[cl[S.gid[q]]];
+        S.rep[q] = (int16_t)r;
+        S.tmp[q] = (int16_t)atomicAdd(&cur[r], 1);  // its place in the range
+        // the first entry of its sorted row outside its own cluster
+        const int gm = S.gid[q], p = pos[gm];
+        if (p < n - 1) {
+            const int w = srt[(int64_t)gm * n + p];
+            nxl[gm] = grp[w] == g ? lq[w] : -1;
+            outv[gm] = e[(int64_t)gm * n + w];
+        } else {
+            nxl[gm] = -1;
+            outv[gm] = kNoPair;
+        }
+    }
+    __syncthreads();
+    int32_t carry = 0;
+    for (int base = 0; base < nm; base += kMergeThreads) {
+        const int q = base + (int)threadIdx.x;
+        const int32_t z = q < nm ? cur[q] : 0;
+        int32_t tot;
+        const int32_t ex = block_excl_scan<int32_t>(z, scan_lds, &tot);
+        if (q < nm) {
+            S.sz[q] = (int16_t)z;
+            S.st[q] = (int16_t)(carry + ex);
+        }
+        carry += tot;
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < nm; q += kMergeThreads) S.perm[S.st[S.rep[q]] + S.tmp[q]] = (int16_t)q;
+    __syncthreads();
+    for (int q = wv; q < nm; q += kMergeWaves)
+        if (S.rep[q] == q) merge_row_best(S, q, nm, A, tau, lane);
     __syncthreads();
     // every round merges two clusters, or marks a pair or finds one that
     // passes (a row then stays clean until a merge touches it): at most nm - 1
@@ -535,14 +764,14 @@ __global__ __launch_bounds__(kMergeThreads) void islands_merge(int n, const doub
         if (nl > 0) {
             for (int k = wv; k < nl; k += kMergeWaves) {
                 const int c = S.list[k], d = S.ra[c];
-                const bool pass = merge_eq3(S, c, d, g, n, nm, e, srt, grp, lq, XT, inown, pos, nxl, outv, lane);
+                const bool pass = merge_eq3(S, c, d, g, n, A, e, srt, grp, lq, inown, pos, nxl, outv, lane);
                 if (lane == 0) {
                     if (pass) {
                         S.ok[c] = 1;
                         S.vp[c] = (int16_t)d;
                     } else {
-                        M[(int64_t)c * nm + d] = 1;
-                        M[(int64_t)d * nm + c] = 1;
+                        A.M[at(c, d)] = 1;
+                        A.M[at(d, c)] = 1;
                         // the rows whose best partner this pair was look again
                         S.redo[c] = 1;
                         if (S.ra[d] == c) S.redo[d] = 1;
@@ -558,7 +787,7 @@ __global__ __launch_bounds__(kMergeThreads) void islands_merge(int n, const doub
                 }
             __syncthreads();
             const int nr = S.cnt;
-            for (int k = wv; k < nr; k += kMergeWaves) merge_row_best(S, S.list[k], nm, L, M, lane);
+            for (int k = wv; k < nr; k += kMergeWaves) merge_row_best(S, S.list[k], nm, A, tau, lane);
             __syncthreads();
             continue;
         }
@@ -574,7 +803,7 @@ __global__ __launch_bounds__(kMergeThreads) void islands_merge(int n, const doub
         // slowest links into the grown cluster, before its column of XT changes
         for (int t = threadIdx.x; t < zc + zd; t += kMergeThreads) {
             const int m = S.perm[t < zc ? sc + t : sd + t - zc];
-            const double x = XT[(int64_t)(t < zc ? d : c) * nm + m];
+            const double x = A.XT[at(t < zc ? d : c, m)];
             const int gm = S.gid[m];
             if (x < inown[gm]) inown[gm] = x;
         }
@@ -582,17 +811,17 @@ __global__ __launch_bounds__(kMergeThreads) void islands_merge(int n, const doub
         // cluster are new pairs
         for (int v = threadIdx.x; v < nm; v += kMergeThreads) {
             if (v == c || v == d) continue;
-            const double lc = L[(int64_t)c * nm + v], ld = L[(int64_t)d * nm + v];
+            const double lc = A.L[at(c, v)], ld = A.L[at(d, v)];
             const double l = lc < ld ? lc : ld;
-            L[(int64_t)c * nm + v] = l;
-            L[(int64_t)v * nm + c] = l;
-            M[(int64_t)c * nm + v] = 0;
-            M[(int64_t)v * nm + c] = 0;
+            A.L[at(c, v)] = l;
+            A.L[at(v, c)] = l;
+            A.M[at(c, v)] = 0;
+            A.M[at(v, c)] = 0;
         }
         __syncthreads();
         for (int v = threadIdx.x; v < nm; v += kMergeThreads) {
-            const double xc = XT[(int64_t)c * nm + v], xd = XT[(int64_t)d * nm + v];
-            XT[(int64_t)c * nm + v] = xc < xd ? xc : xd;
+            const double xc = A.XT[at(c, v)], xd = A.XT[at(d, v)];
+            A.XT[at(c, v)] = xc < xd ? xc : xd;
         }
         for (int t = threadIdx.x; t < zd; t += kMergeThreads) S.rep[S.perm[sd + t]] = (int16_t)c;
         // the two member ranges side by side: rotate the stretch between them
@@ -662,8 +891,8 @@ __global__ __launch_bounds__(kMergeThreads) void islands_merge(int n, const doub
             if (q == c || S.ra[q] == c || S.ra[q] == d) {
                 S.list[atomicAdd(&S.cnt, 1)] = (int16_t)q;
             } else {
-                const double l = L[(int64_t)q * nm + c];
-                if (l != kNoPair &&
+                const double l = A.L[at(q, c)];
+                if (l != kNoPair && l >= tau &&
                     (S.ra[q] < 0 || pair_before(l, S.gid[q], S.gid[c], S.rb[q], S.gid[q], S.gid[S.ra[q]]))) {
                     S.rb[q] = l;
                     S.ra[q] = (int16_t)c;
@@ -673,7 +902,7 @@ __global__ __launch_bounds__(kMergeThreads) void islands_merge(int n, const doub
         }
         __syncthreads();
         const int nr = S.cnt;
-        for (int k = wv; k < nr; k += kMergeWaves) merge_row_best(S, S.list[k], nm, L, M, lane);
+        for (int k = wv; k < nr; k += kMergeWaves) merge_row_best(S, S.list[k], nm, A, tau, lane);
         __syncthreads();
     }
     for (int q = threadIdx.x; q < nm; q += kMergeThreads) cl[S.gid[q]] = S.gid[S.rep[q]];
@@ -766,7 +995,9 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
     if (e == hipSuccess) e = hipMemcpyAsync(w.val, hv.data(), 8 * 4 * (size_t)n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w.e, e_host, 8 * (size_t)n * n, hipMemcpyHostToDevice, s);
     const int32_t none[2] = {0, INT32_MAX};
+    const unsigned long long no_link = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(w.err, none, sizeof(none), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(w.lmax, &no_link, sizeof(no_link), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     const int64_t nn = (int64_t)n * n;
     islands_check<<<dim3((unsigned)std::min<int64_t>((nn + 255) / 256, 2048)), dim3(256), 0, s>>>(nn, w.e, w.err + 1);
@@ -778,12 +1009,34 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
     if (bad != INT32_MAX) return hipSuccess;
     islands_groups<<<dim3(1), dim3(kGroupThreads), 0, s>>>(n, w.gpus, w.val, eps_c, eps_m, eps_i, w.grp, w.gstart,
                                                            w.gnodes, w.ngroups, w.lq, w.goff);
-    islands_link_init<<<dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s>>>(
-        n, w.e, w.grp, w.gstart, w.lq, w.goff, w.L, w.M, w.XT, w.inown, w.cl);
+    const dim3 pairs((unsigned)((nn + 255) / 256));
+    islands_link_init<<<pairs, dim3(256), 0, s>>>(n, w.e, w.grp, w.gstart, w.lq, w.goff, w.L, w.M, w.XT, w.inown,
+                                                  w.pos, w.cl, w.uf, w.lmax);
     islands_sort_rows<<<dim3((unsigned)n), dim3(1024), 0, s>>>(n, w.e, w.srt);
-    islands_merge<<<dim3((unsigned)n), dim3(kMergeThreads), 0, s>>>(n, w.e, w.srt, w.grp, w.lq, w.gstart, w.gnodes,
-                                                                     w.ngroups, w.goff, w.L, w.M, w.XT, w.inown,
-                                                                     w.pos, w.nxl, w.outv, w.cl, w.err);
+    for (int st = 0; st < kStages; ++st) {
+        const bool last = st == kStages - 1;
+        const double share = last ? 0.0 : kStageShare[st];
+        StageComps comps{w.comp, w.lc, w.cstart, w.cnodes, w.ncomp};
+        if (last) {
+            comps = StageComps{w.grp, w.lq, w.gstart, w.gnodes, w.ngroups};
+        } else {
+            islands_unite<<<pairs, dim3(256), 0, s>>>(n, share, w.lmax, w.e, w.grp, w.uf);
+            islands_components<<<dim3(1), dim3(kGroupThreads), 0, s>>>(n, w.uf, w.comp, w.lc, w.cstart, w.cnodes,
+                                                                       w.ncomp);
+        }
+        if (st > 0) {
+            islands_stage_clear<<<pairs, dim3(256), 0, s>>>(n, w.grp, w.gstart, w.lq, w.goff, comps.of, w.cl, w.L,
+                                                            w.XT);
+            islands_stage_links<<<pairs, dim3(256), 0, s>>>(n, w.e, w.grp, w.gstart, w.lq, w.goff, comps.of, w.cl,
+                                                            w.L, w.XT);
+        }
+        islands_merge<kSmallThreads, 2, kSmallComp><<<dim3((unsigned)n), dim3(kSmallThreads), 0, s>>>(
+            n, share, w.lmax, w.e, w.srt, comps, w.grp, w.lq, w.gstart, w.goff, w.L, w.M, w.XT, w.inown, w.pos, w.nxl,
+            w.outv, w.cl, w.err);
+        islands_merge<kMergeThreads, kSmallComp + 1, kMaxNodes><<<dim3((unsigned)n), dim3(kMergeThreads), 0, s>>>(
+            n, share, w.lmax, w.e, w.srt, comps, w.grp, w.lq, w.gstart, w.goff, w.L, w.M, w.XT, w.inown, w.pos, w.nxl,
+            w.outv, w.cl, w.err);
+    }
     islands_number<<<dim3(1), dim3(1024), 0, s>>>(n, w.cl, w.gpus, w.val, w.island_of, w.out_k, w.isl_gpus,
                                                   w.isl_val);
     e = hipGetLastError();

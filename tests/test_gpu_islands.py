@@ -124,3 +124,36 @@ def test_islands_invalid_rejected(bad):
     with pytest.raises(T.TangramError) as e:
         T.build_islands(cl, workspace=torch.empty(1 << 20, dtype=torch.uint8, device="cuda"))
     assert e.value.status == T.TG_EINVAL
+
+
+def staged_links(seed, n):
+    """One group of n nodes in leaves and pods, a few links changed at random:
+    link speeds at exactly a half and an eighth of the fastest, just below
+    them, and zero, so that pairs sit on the thresholds between which the
+    clustering is staged."""
+    rng = np.random.default_rng(2000 + seed)
+    u = rng.permutation(n)
+    leaf, pod = u // int(rng.integers(2, 9)), u // int(rng.integers(12, 40))
+    e = np.where(leaf[:, None] == leaf[None, :], 800e9, np.where(pod[:, None] == pod[None, :], 400e9, 100e9))
+    speeds = np.array([0.0, 50e9, 99.999e9, 100e9, 399.999e9, 400e9, 800e9])
+    odd = rng.random((n, n)) < (0.02 if seed % 2 else 0.0015)
+    e = np.where(odd, speeds[rng.integers(0, len(speeds), size=(n, n))], e)
+    if seed % 3 == 0:
+        e = np.minimum(e, e.T)
+    np.fill_diagonal(e, 0.0)
+    return cluster([8] * n, [100e12] * n, e.tolist())
+
+
+@pytest.mark.parametrize("seed,n", [(s, n) for s, n in enumerate((20, 33, 64, 65, 66, 90, 128, 150, 64, 65, 200, 96))])
+def test_islands_stages(seed, n):
+    say("staged", seed, n)
+    c = staged_links(seed, n)
+    same(T.build_islands(c), oracle_islands(c))
+
+
+@pytest.mark.parametrize("bw", [0.0, 25e9])
+def test_islands_one_link_speed(bw):
+    """Every link alike (or none): each stage's component is the whole group."""
+    e = [[0.0 if a == b else bw for b in range(70)] for a in range(70)]
+    c = cluster([8] * 70, [100e12] * 70, e)
+    same(T.build_islands(c), oracle_islands(c))
