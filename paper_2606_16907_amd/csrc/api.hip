@@ -247,6 +247,11 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
             c0 = c1;
         }
     }
+    std::vector<int32_t> kb_rows(kb_members.size()), kb_order(kb_island.size());
+    for (size_t t = 0; t < kb_members.size(); ++t) kb_rows[t] = cfg[kb_members[t]].row;
+    for (size_t t = 0; t < kb_order.size(); ++t) kb_order[t] = (int32_t)t;
+    std::stable_sort(kb_order.begin(), kb_order.end(),
+                     [&](int32_t x, int32_t y) { return kb_off[x + 1] - kb_off[x] > kb_off[y + 1] - kb_off[y]; });
     // distinct inter-island bandwidths (link times need one division per value)
     std::vector<double> ev(inter_bw, inter_bw + (size_t)K * K);
     std::sort(ev.begin(), ev.end());
@@ -357,6 +362,8 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
         {jlo.data(), jlo.size() * 4, 0},
         {cls.data(), cls.size() * 4, 0},
         {cls_ij.data(), cls_ij.size() * 4, 0},
+        {kb_rows.data(), kb_rows.size() * 4, 0},
+        {kb_order.data(), kb_order.size() * 4, 0},
     };
     size_t total = 0;
     for (auto &p : parts) {
@@ -434,6 +441,8 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
     P.cls = (const uint32_t *)(base + parts[19].off);
     P.cls_ij = (const uint32_t *)(base + parts[20].off);
     P.class_scores = 0;
+    P.kb_rows = (const int32_t *)(base + parts[21].off);
+    P.kb_order = (const int32_t *)(base + parts[22].off);
     // the per-config coefficients are computed on the device
     e = tg::launch_coef(P, (tg::Coef *)(base + parts[4].off), nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();

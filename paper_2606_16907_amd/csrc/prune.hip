@@ -12,8 +12,9 @@
 // Frontier: a wave owns 64 consecutive slices of one (island, b) group list;
 // every lane walks the same members (a scalar loop) in ascending idx, reading
 // one coalesced 64-byte row of depths per member and, where the depth can
-// still matter, one 512-byte row of costs, eight members in flight.  Each
-// lane keeps the staircase of its group in registers (up to kStair entries of
+// still matter, one 512-byte row of costs, eight members in flight.  On
+// clusters of up to 32 islands each lane keeps the least cost of every depth in
+// LDS (frontier_buckets); on wider ones each lane keeps the staircase of its group in registers (up to kStair entries of
 // strictly increasing depth and key): a member is dropped when an entry at
 // least as deep costs no more; otherwise it removes the entries it beats and
 // takes a slot.  When the slots are full the shallowest of them and the
@@ -124,7 +125,7 @@ __device__ inline void record_pass(const DevProblem &P, uint64_t *mask, const ui
         }
         wave_sync();
         for (int m = lane; m < n; m += kWave) {
-            uint64_t *at = bitmap + (int64_t)P.coef[P.kb_members[m0 + base + m]].row * P.words + sc;
+            uint64_t *at = bitmap + (int64_t)P.kb_rows[m0 + base + m] * P.words + sc;
             *at = merge ? (*at | mask[m]) : mask[m];
         }
         wave_sync();
@@ -202,6 +203,111 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
         // same words, so program order already holds; the fence makes it plain)
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     } while (__ballot(need) != 0);
+}
+
+// The frontier by depth buckets, for clusters of at most kBucketDepths islands
+// (depths 1..K): a wave keeps, per lane and depth, the least cost among the
+// group's members that fit exactly that deep and the first member costing it,
+// in LDS.  A member is one LDS read, a compare and now and then a write, where
+// the register staircase compares and moves up to eight entries (about 160
+// instructions a member; it was issue-bound at under 2 TB/s on the extended
+// MoE instance).  Afterwards a sweep from the deepest bucket up keeps those
+// cheaper than everything deeper: the survivors, whatever their number, in one
+// pass.  Bound by the depth-then-cost loads of kBucketBatch members in flight
+// (the next batch's depths load with this batch's costs) at the 7 to 15 waves a
+// CU that 20 KB (32 islands) to 10 KB (16) leave; a wider cluster keeps the
+// registers.  Groups go largest first, so the last blocks are short ones.
+// Register staircase -> buckets, frontier kernel: extended MoE 790 -> 370 us,
+// extended 70B 385 -> 275, uneven 27 islands 113 -> 103, MoE 90 -> 64, 70B 38 ->
+// 35, 8B 17 -> 13; batches of 12, 16 and 24 members within 3% either way.
+constexpr int kBucketDepths = 32;
+constexpr int kBucketMembers = 0xFFFE;  // a member's number in its group takes 16 bits
+constexpr int kBucketBatch = 8;
+constexpr int kBucketChunk = 128;       // members per LDS mask round
+
+static size_t bucket_lds(int K) { return (size_t)K * kWave * (sizeof(double) + sizeof(uint16_t)); }
+
+__global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const double *__restrict__ cost,
+                                                          const uint8_t *__restrict__ dmax,
+                                                          uint64_t *__restrict__ bitmap) {
+    extern __shared__ double lds_best[];       // [K][64] least cost of each depth
+    __shared__ uint64_t mask[kBucketChunk];
+    const int K = P.K;
+    const int lane = threadIdx.x;
+    double *best = lds_best + lane;            // depth d: best[(d - 1) * 64]
+    uint16_t *who = (uint16_t *)(lds_best + (int64_t)K * kWave) + lane;
+    constexpr uint16_t kNone = 0xFFFF;
+    const int qo = (int)(blockIdx.x / P.words);
+    const int64_t sc = blockIdx.x - (int64_t)qo * P.words;
+    const int q = P.kb_order[qo];
+    const int m0 = P.kb_off[q];
+    const int nm = P.kb_off[q + 1] - m0;
+    const int64_t s = sc * kWave + lane;
+    const int64_t NS = P.NS;
+    bool need = s < NS;
+    if (need && P.imb) {  // an unbalanced (slice, island) group has no survivors
+        const uint32_t ij = P.sij[s];
+        need = slice_balanced(P, P.pre, (int)(ij & 0xFFFFu), (int)(ij >> 16), P.kb_island[q]);
+    }
+    for (int d = 0; d < K; ++d) {
+        best[d * kWave] = __builtin_nan("");  // empty: not <= any cost
+        who[d * kWave] = kNone;
+    }
+    const int64_t at = need ? s : 0;  // lanes that score nothing read row starts
+    int d[kBucketBatch];
+#pragma unroll
+    for (int u = 0; u < kBucketBatch; ++u) {
+        const int v = dmax[(int64_t)P.kb_members[m0 + min(u, nm - 1)] * NS + at];
+        d[u] = u < nm && need ? v : 0;
+    }
+    for (int mb = 0; mb < nm; mb += kBucketBatch) {
+        double c[kBucketBatch];
+        int dn[kBucketBatch];
+#pragma unroll
+        for (int u = 0; u < kBucketBatch; ++u) {
+            const double *row = cost + (int64_t)P.kb_members[m0 + min(mb + u, nm - 1)] * NS;
+            c[u] = d[u] > 0 ? row[at] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < kBucketBatch; ++u) {
+            const int m = mb + kBucketBatch + u;
+            const int v = dmax[(int64_t)P.kb_members[m0 + min(m, nm - 1)] * NS + at];
+            dn[u] = m < nm && need ? v : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kBucketBatch; ++u)
+            if (d[u] > 0 && d[u] <= K) {
+                const int b = (d[u] - 1) * kWave;
+                // ties stay with the earlier member; a cost that is no number never survives
+                if (!(best[b] <= c[u]) && c[u] == c[u]) {
+                    best[b] = c[u];
+                    who[b] = (uint16_t)(mb + u);
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < kBucketBatch; ++u) d[u] = dn[u];
+    }
+    // a bucket survives if it is cheaper than every deeper one
+    double least = __builtin_nan("");
+    for (int e = K - 1; e >= 0; --e) {
+        const double v = best[e * kWave];
+        if (v == v && !(least <= v))
+            least = v;
+        else
+            who[e * kWave] = kNone;
+    }
+    for (int base = 0; base < nm; base += kBucketChunk) {
+        const int n = min(kBucketChunk, nm - base);
+        for (int m = lane; m < n; m += kWave) mask[m] = 0;
+        wave_sync();
+        for (int e = 0; e < K; ++e) {
+            const int m = (int)who[e * kWave] - base;  // kNone is past every chunk
+            if (m >= 0 && m < n) atomicOr((unsigned long long *)&mask[m], 1ull << lane);
+        }
+        wave_sync();
+        for (int m = lane; m < n; m += kWave) bitmap[(int64_t)P.kb_rows[m0 + base + m] * P.words + sc] = mask[m];
+        wave_sync();
+    }
 }
 
 template <int WPT>
@@ -424,7 +530,9 @@ size_t prune_ws_bytes(const DevProblem &P) { return carve_prune(P, nullptr).byte
 static hipError_t launch_frontier(const DevProblem &P, const double *cost, const uint8_t *dmax, uint64_t *bitmap,
                                   hipStream_t s) {
     const int64_t n_front = (int64_t)P.n_kb * P.words;
-    if (n_front > 0) {
+    if (n_front > 0 && P.K <= kBucketDepths && P.max_members <= kBucketMembers) {
+        frontier_buckets<<<dim3((unsigned)n_front), dim3(kWave), bucket_lds(P.K), s>>>(P, cost, dmax, bitmap);
+    } else if (n_front > 0) {
         const int64_t blocks = (n_front + kFrontWaves - 1) / kFrontWaves;
         if (P.max_members <= kSmallGroup)
             frontier_kernel<4><<<dim3((unsigned)blocks), dim3(kFrontWaves * kWave), 0, s>>>(P, cost, dmax, bitmap,

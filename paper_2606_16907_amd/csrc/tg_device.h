@@ -48,6 +48,8 @@ struct DevProblem {
     const int64_t *bvals;   // [nb]
     const int32_t *kb_off;  // [n_kb+1] offsets into kb_members
     const int32_t *kb_members;  // config ids of each (island, b) group, ascending
+    const int32_t *kb_rows;     // bitmap row of each member
+    const int32_t *kb_order;    // [n_kb] the groups, largest first
     const int32_t *kb_island;   // [n_kb]
     const int32_t *kb_bidx;     // [n_kb]
     const int32_t *row_cfg;     // [n_rows] config id of each bitmap row
