@@ -671,10 +671,10 @@ size_t tg_compose_all_orders_workspace_bytes(const tg_problem *p, int64_t n_surv
 
 }  // extern "C"
 
-// Argument checks shared by both compositions; uploads the island order.
+// Argument checks shared by the compositions.
 static tg_status compose_begin(const tg_problem *p, const int64_t *d_survivors, int64_t n_survivors,
                                const double *d_cost, const uint8_t *d_dmax, const int32_t *island_order,
-                               tg_plan *out, void *d_ws, size_t ws_bytes, size_t need, hipStream_t s) {
+                               tg_plan *out, void *d_ws, size_t ws_bytes, size_t need) {
     if (!p || !out) return fail(TG_EINVAL, "NULL argument");
     std::memset(out, 0, sizeof(*out));
     out->P = out->F = out->T = HUGE_VAL;
@@ -694,10 +694,6 @@ static tg_status compose_begin(const tg_problem *p, const int64_t *d_survivors, 
     if (check_alignment(n_survivors > 0 ? d_cost : nullptr, d_survivors, d_ws) != TG_OK) return TG_EINVAL;
     if (tg_status st = check_device(p); st != TG_OK) return st;
     if (p->P.nb == 0) return fail(TG_ENOPLAN, "no micro-batch size divides the global batch");
-    if (!island_order) return TG_OK;
-    hipError_t e = hipMemcpyAsync((char *)d_ws + tg::compose_order_offset(p->P, n_survivors), island_order,
-                                  sizeof(int32_t) * K, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return hip_fail(e, "order upload");
     return TG_OK;
 }
 
@@ -741,7 +737,7 @@ tg_status tg_compose_pipeline(const tg_problem *p, const int64_t *d_survivors, i
     if (!island_order) return fail(TG_EINVAL, "NULL argument");
     const size_t need = p && n_survivors >= 0 ? tg::compose_ws_bytes(p->P, n_survivors) : 0;
     tg_status st = compose_begin(p, d_survivors, n_survivors, d_cost, d_dmax, island_order, out, d_ws, ws_bytes,
-                                 need, s);
+                                 need);
     if (st != TG_OK) return st;
     tg::ComposeResult *res_dev = nullptr;
     // the handle's pinned read-back words, when no other call holds them: the
@@ -759,7 +755,7 @@ tg_status tg_compose_pipeline(const tg_problem *p, const int64_t *d_survivors, i
                                (tg::ComposeResult *)pw->ptr, (tg::ComposeResult *)pw->dev, p->compose_ev};
         if (!host.ev) host.dlim = host.dlim_dev = nullptr;
     }
-    hipError_t e = tg::launch_compose(p->P, d_survivors, n_survivors, d_cost, d_dmax, nullptr, d_ws, s, &res_dev,
+    hipError_t e = tg::launch_compose(p->P, d_survivors, n_survivors, d_cost, d_dmax, island_order, d_ws, s, &res_dev,
                                       pw ? &host : nullptr);
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(s);  // nothing queued may store into the words once they are let go
@@ -775,12 +771,12 @@ tg_status tg_compose_pipeline_classes(const tg_problem *p, const int64_t *d_surv
     if (!island_order) return fail(TG_EINVAL, "NULL argument");
     const size_t need = p && n_survivors >= 0 ? tg::compose_ws_bytes(p->P, n_survivors) : 0;
     tg_status st = compose_begin(p, d_survivors, n_survivors, d_cost, d_dmax, island_order, out, d_ws, ws_bytes,
-                                 need, s);
+                                 need);
     if (st != TG_OK) return st;
     tg::DevProblem P = p->P;
     P.class_scores = 1;
     tg::ComposeResult *res_dev = nullptr;
-    hipError_t e = tg::launch_compose(P, d_survivors, n_survivors, d_cost, d_dmax, nullptr, d_ws, s, &res_dev);
+    hipError_t e = tg::launch_compose(P, d_survivors, n_survivors, d_cost, d_dmax, island_order, d_ws, s, &res_dev);
     if (e != hipSuccess) return hip_fail(e, "compose kernels");
     return compose_end(res_dev, out, s);
 }
@@ -792,7 +788,7 @@ tg_status tg_compose_pipeline_relaxed(const tg_problem *p, const int64_t *d_surv
     if (!island_order) return fail(TG_EINVAL, "NULL argument");
     const size_t need = p && n_survivors >= 0 ? tg::compose_relaxed_ws_bytes(p->P, n_survivors) : 0;
     tg_status st = compose_begin(p, d_survivors, n_survivors, d_cost, d_dmax, island_order, out, d_ws, ws_bytes,
-                                 need, s);
+                                 need);
     if (st != TG_OK) return st;
     return no_throw([&] {
         std::lock_guard<std::mutex> lock(p->relax_mu);  // one relaxed call at a time uses the handle's staging
@@ -859,7 +855,8 @@ tg_status tg_compose_pipeline_all_orders(const tg_problem *p, const int64_t *d_s
     if (p && p->P.K > 16) return fail(TG_EINVAL, "composition over all island orders takes at most 16 islands");
     if (p && p->P.nb > 65535) return fail(TG_EINVAL, "more than 65535 micro-batch sizes");
     const size_t need = p && n_survivors >= 0 ? tg::compose_orders_ws_bytes(p->P, n_survivors) : 0;
-    tg_status st = compose_begin(p, d_survivors, n_survivors, d_cost, d_dmax, nullptr, out, d_ws, ws_bytes, need, s);
+    tg_status st = compose_begin(p, d_survivors, n_survivors, d_cost, d_dmax, nullptr, out, d_ws, ws_bytes,
+                                 need);
     if (st != TG_OK) return st;
     return no_throw([&] {
         tg::ComposeResult *res_dev = nullptr;

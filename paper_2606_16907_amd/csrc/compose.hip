@@ -177,12 +177,29 @@ struct Ws {
     int32_t *RO;       // [D][nb] its first position (least on ties), -1 if none
     int32_t *dlim;     // [nb] deepest level whose root bottleneck reaches P* (0: no plan)
     int64_t *tmp;      // scan tiles
+    double *Td;        // [D][nb][NS][K] stage table of every depth (small problems)
     size_t bytes;
 };
 
 __host__ __device__ inline int64_t n_groups(const DevProblem &P) { return (int64_t)P.nb * P.NS * P.K; }
 static int levels(const DevProblem &P) { return P.K < P.L ? P.K : P.L; }
 static int64_t n_rowev(const DevProblem &P) { return (int64_t)P.nb * P.L * (levels(P) + 1); }
+
+// Small problems are composed by one block per b with everything it reads
+// again and again in LDS: two level rows and the link times between every pair
+// of positions, for every cut.
+constexpr size_t kSmallLds = 60 * 1024;
+constexpr int64_t kSmallCells = 256 * 1024;  // entries of the stage table of every depth (2 MB)
+constexpr int kSmallMatches = 2048;          // entries the plan's groups may hold together
+constexpr int64_t kSmallList = 32768;
+
+static size_t small_lds(const DevProblem &P) {
+    return sizeof(double) * (size_t)(P.L + 1) * (2 * P.K + P.K * (P.K - 1) / 2);
+}
+static bool small_problem(const DevProblem &P) {
+    return small_lds(P) <= kSmallLds && n_groups(P) * levels(P) <= kSmallCells &&
+           (int64_t)P.max_members * levels(P) <= kSmallMatches;
+}
 
 static Ws carve(const DevProblem &P, int64_t n, void *base) {
     Ws w{};
@@ -230,16 +247,12 @@ static Ws carve(const DevProblem &P, int64_t n, void *base) {
     w.RO = (int32_t *)take(sizeof(int32_t) * D * P.nb);
     w.dlim = (int32_t *)take(sizeof(int32_t) * P.nb);
     w.tmp = (int64_t *)take(sizeof(int64_t) * tiles);
+    w.Td = (double *)take(small_problem(P) ? sizeof(double) * G * D : 1);
     w.bytes = off;
     return w;
 }
 
 size_t compose_ws_bytes(const DevProblem &P, int64_t n_surv) { return carve(P, n_surv, nullptr).bytes; }
-size_t compose_order_offset(const DevProblem &P, int64_t n_surv) {
-    (void)P;
-    (void)n_surv;
-    return align256(sizeof(ComposeResult));
-}
 
 // The stage table keeps the DP's layout [b][slice][position].
 __host__ __device__ inline int64_t cell_id(const DevProblem &P, int64_t bi, int64_t s, int64_t o) {
@@ -249,14 +262,30 @@ __host__ __device__ inline int64_t cell_id(const DevProblem &P, int64_t bi, int6
 // Index of the pair of positions (o, o2), o < o2, in a packed triangle.
 __host__ __device__ inline int tri(int o, int o2) { return o2 * (o2 - 1) / 2 + o; }
 
-__global__ __launch_bounds__(256) void prep_kernel(DevProblem P, const int32_t *order, int32_t *pos, double *EoT,
-                                                   uint8_t *EiT, ComposeResult *res, int32_t *ev_total) {
+// The caller's island order, a kernel argument (an upload from pageable memory
+// would hold up the launches behind it).
+struct OrderArg {
+    uint8_t k[256];  // K <= 255
+};
+
+static OrderArg order_arg(const int32_t *order, int K) {
+    OrderArg a{};
+    for (int o = 0; o < K; ++o) a.k[o] = (uint8_t)order[o];
+    return a;
+}
+
+__global__ __launch_bounds__(256) void prep_kernel(DevProblem P, OrderArg ord, int32_t *order, int32_t *pos,
+                                                   double *EoT, uint8_t *EiT, ComposeResult *res,
+                                                   int32_t *ev_total) {
     const int K = P.K;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < K) pos[order[t]] = t;
+    if (t < K) {
+        order[t] = ord.k[t];
+        pos[ord.k[t]] = t;
+    }
     if (t < K * K) {
         const int o2 = t / K, o = t - o2 * K;
-        const int64_t e = (int64_t)order[o] * K + order[o2];
+        const int64_t e = (int64_t)ord.k[o] * K + ord.k[o2];
         EoT[t] = P.E[e];
         if (o < o2) EiT[tri(o, o2)] = P.n_ev ? (uint8_t)P.Eidx[e] : 0;
     }
@@ -282,13 +311,28 @@ __global__ __launch_bounds__(256) void jlo_kernel(DevProblem P, const int32_t *o
 // reads walk the score arrays forward) and counts the group sizes.  A thread
 // takes kGatherPer entries, a block's threads apart, with all their loads in
 // flight together.
+// The lesser of *at and v into *at (any sign; a v that is no number changes
+// nothing).  A retry means another thread lowered it: the loop ends.
+__device__ inline void lower(double *at, double v) {
+    unsigned long long *p = (unsigned long long *)at;
+    unsigned long long old = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (v < __longlong_as_double((long long)old)) {
+        const unsigned long long seen = atomicCAS(p, old, (unsigned long long)__double_as_longlong(v));
+        if (seen == old) break;
+        old = seen;
+    }
+}
+
 constexpr int kGatherPer = 4;
 constexpr int kGatherBlock = 256 * kGatherPer;
 
+// kTable: instead of counting, an entry lowers its group's stage costs Td[d]
+// ([d][b][slice][position]) at every depth it fits, up to D.
+template <bool kTable>
 __global__ __launch_bounds__(256) void gather_kernel(DevProblem P, const int64_t *surv, int64_t n,
                                                      const double *cost, const uint8_t *dmax, const int32_t *pos,
                                                      int32_t *rec_g, double *rec_c, uint8_t *rec_d, int32_t *gcnt,
-                                                     ComposeResult *res) {
+                                                     ComposeResult *res, int D, double *Td) {
     const int64_t r0 = (int64_t)blockIdx.x * kGatherBlock + threadIdx.x;
     int64_t idx[kGatherPer], prev[kGatherPer];
 #pragma unroll
@@ -336,7 +380,14 @@ __global__ __launch_bounds__(256) void gather_kernel(DevProblem P, const int64_t
         if (G[u] >= 0) {
             rec_c[r] = cv[u];
             rec_d[r] = d[u];
-            atomicAdd(&gcnt[G[u]], 1);
+            if (kTable) {
+                const int64_t s = G[u] % P.NS, ob = G[u] / P.NS;  // G = (position * nb + b) * NS + slice
+                const int64_t o = ob / P.nb, bi = ob - o * P.nb;
+                for (int q = 0; q < min((int)d[u], D); ++q)
+                    lower(&Td[((q * (int64_t)P.nb + bi) * P.NS + s) * P.K + o], cv[u]);
+            } else {
+                atomicAdd(&gcnt[G[u]], 1);
+            }
         }
         rec_g[r] = G[u];
     }
@@ -365,8 +416,8 @@ void launch_grouping(const DevProblem &P, const int64_t *surv, int64_t n, const 
     fill<int32_t>(g.gcnt, G, 0, s);
     if (n > 0) {
         const int64_t blocks = (n + kGatherBlock - 1) / kGatherBlock;
-        gather_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(P, surv, n, cost, dmax, pos, g.rec_g, g.rec_c,
-                                                                    g.rec_d, g.gcnt, res);
+        gather_kernel<false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(P, surv, n, cost, dmax, pos, g.rec_g,
+                                                                           g.rec_c, g.rec_d, g.gcnt, res, 0, nullptr);
         scan_i32(g.gcnt, G, g.tmp, s);
         const int64_t sblocks = std::min<int64_t>((n + 255) / 256, 65536);
         scatter_kernel<<<dim3((unsigned)sblocks), dim3(256), 0, s>>>(surv, n, g.rec_g, g.rec_c, g.rec_d, g.gcnt,
@@ -1196,20 +1247,28 @@ struct LevelKernels {
 constexpr int kFinishThreads = 1024;
 
 
-__global__ __launch_bounds__(kFinishThreads) void finish_kernel(DevProblem P, const int32_t *gcnt,
-                                                                const double *ent_c, const uint8_t *ent_d,
-                                                                const int64_t *ent_i, const int32_t *order,
-                                                                const double *EoT, const double *Pst,
-                                                                const double *rootF, const int32_t *root_o,
-                                                                const int32_t *root_d, const uint16_t *argF,
-                                                                const uint8_t *argG, ComposeResult *res,
-                                                                ComposeResult *res_host) {
-    __shared__ int32_t st_i[256], st_j[256], st_o[256], st_on[256];
-    __shared__ int32_t sh_S, sh_bb;
+// The chosen plan: each stage's first layer, end, position and the next
+// stage's position, in LDS.
+struct PlanWalk {
+    int32_t i[256], j[256], o[256], on[256];
+    int32_t S, bb;
+};
+
+// Transfer time of one micro-batch (activations and gradients) after layer
+// j - 1 over a link of E bytes/s.
+__device__ inline double link_time(const DevProblem &P, int64_t b, int j, double E) {
+    return E == 0.0 ? kInf : ((2.0 * (double)b) * (double)P.outact[j - 1]) / E;
+}
+
+// Chooses b, writes the plan's header and walks its argmins (one block, which
+// has to synchronise before it reads W).
+__device__ inline void choose_and_walk(const DevProblem &P, const double *Pst, const double *rootF,
+                                       const int32_t *root_o, const int32_t *root_d, const uint16_t *argF,
+                                       const uint8_t *argG, ComposeResult *res, PlanWalk &W) {
     const int L = P.L, K = P.K;
     tg_plan &plan = res->plan;
     if (threadIdx.x == 0) {
-        sh_S = 0;
+        W.S = 0;
         plan.b = 0;
         plan.m = 0;
         plan.S = 0;
@@ -1239,17 +1298,17 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(DevProblem P, co
             plan.F = rootF[bb];
             plan.T = bestT;
             res->status = TG_OK;
-            sh_S = S;
-            sh_bb = bb;
+            W.S = S;
+            W.bb = bb;
         }
     }
     __syncthreads();
     // The walk, by wave 0: once a stage's cut j is known, the next stage's
     // whole argmin row argF[d-2][b][j][.] is loaded with argG[d-2][b][j][o],
     // so the next cut needs no further load (one dependent load per stage).
-    if (threadIdx.x < kWave && sh_S > 0) {
+    if (threadIdx.x < kWave && W.S > 0) {
         const int lane = threadIdx.x;
-        const int S = sh_S, bb = sh_bb;
+        const int S = W.S, bb = W.bb;
         int i = 0, o = root_o[bb];
         bool ok = S >= 1 && S <= 255;
         int j = L;
@@ -1278,41 +1337,301 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(DevProblem P, co
                 }
             }
             if (lane == 0) {
-                st_i[t] = i;
-                st_j[t] = j;
-                st_o[t] = o;
-                st_on[t] = o_next;
+                W.i[t] = i;
+                W.j[t] = j;
+                W.o[t] = o;
+                W.on[t] = o_next;
             }
             i = j;
             o = o_next;
             j = jn;
         }
         if (!ok && lane == 0) {
-            sh_S = 0;
+            W.S = 0;
             res->err = 4;
             res->status = TG_ENOPLAN;
         }
     }
+}
+
+__global__ __launch_bounds__(kFinishThreads) void finish_kernel(DevProblem P, const int32_t *gcnt,
+                                                                const double *ent_c, const uint8_t *ent_d,
+                                                                const int64_t *ent_i, const int32_t *order,
+                                                                const double *EoT, const double *Pst,
+                                                                const double *rootF, const int32_t *root_o,
+                                                                const int32_t *root_d, const uint16_t *argF,
+                                                                const uint8_t *argG, ComposeResult *res,
+                                                                ComposeResult *res_host) {
+    __shared__ PlanWalk W;
+    const int K = P.K;
+    tg_plan &plan = res->plan;
+    choose_and_walk(P, Pst, rootF, root_o, root_d, argF, argG, res, W);
     __syncthreads();
-    const int S = sh_S;
+    const int S = W.S;
     const int wv = threadIdx.x / kWave;
     if (S > 0) {
-        const int bb = sh_bb;
+        const int bb = W.bb;
         const int64_t b = P.bvals[bb];
         for (int t = wv; t < S; t += kFinishThreads / kWave) {
-            const int d = S - t, i = st_i[t], j = st_j[t], o = st_o[t], o_next = st_on[t];
-            double link = 0.0;
-            if (d > 1) {
-                const double E = EoT[(int64_t)o_next * K + o];
-                link = E == 0.0 ? kInf : ((2.0 * (double)b) * (double)P.outact[j - 1]) / E;
-            }
-            resolve_stage(P, gcnt, ent_c, ent_d, ent_i, group_id(P, o, bb, slice_of(L, i, j)), i, j, order[o], d,
+            const int d = S - t, i = W.i[t], j = W.j[t], o = W.o[t], o_next = W.on[t];
+            const double link = d > 1 ? link_time(P, b, j, EoT[(int64_t)o_next * K + o]) : 0.0;
+            resolve_stage(P, gcnt, ent_c, ent_d, ent_i, group_id(P, o, bb, slice_of(P.L, i, j)), i, j, order[o], d,
                           link, plan.stage[t], res);
         }
     }
     if (!res_host) return;
     __syncthreads();
     store_result(res, res_host, S);
+}
+
+// ---------------------------------------------------------------------------
+// small problems
+// ---------------------------------------------------------------------------
+// A small composition is bound by launches: about 20 of 2 to 5 us each for
+// grouping, tables, 2 D levels and the plan, most of them idle machine.  Here it
+// is four: clear, list -> stage table of every depth, the whole dynamic program
+// (a block per b, both phases, rows and links in LDS), plan.  Composition of the
+// 2-island and the 4-island instance: @t2@ and @t4@ us a search less.
+__global__ __launch_bounds__(256) void small_init(DevProblem P, OrderArg ord, int32_t *order, int32_t *pos,
+                                                  double *Td, int64_t n, ComposeResult *res) {
+    const int t0 = blockIdx.x * 256 + threadIdx.x;
+    for (int64_t t = t0; t < n; t += (int64_t)gridDim.x * 256) Td[t] = kInf;
+    if (t0 < P.K) {
+        order[t0] = ord.k[t0];
+        pos[ord.k[t0]] = t0;
+    }
+    if (t0 == 0) {
+        res->err = 0;
+        res->status = TG_ENOPLAN;
+    }
+}
+
+constexpr int kSmallThreads = 512;
+
+// Block b: the bottleneck levels, P*_b, then the fill levels at P*_b up to the
+// deepest level whose whole-plan bottleneck reaches it, with argmins, and the
+// root (least fill, ties to the least first position, then the least depth).
+__global__ __launch_bounds__(kSmallThreads) void small_levels(DevProblem P, int D, const int32_t *__restrict__ order,
+                                                              const double *__restrict__ Td, double *Pst,
+                                                              double *rootF, int32_t *root_o, int32_t *root_d,
+                                                              uint16_t *argF, uint8_t *argG) {
+    extern __shared__ double lds_small[];
+    __shared__ double red[kSmallThreads / kWave];
+    __shared__ double s_root[256];  // per level: least whole-plan bottleneck
+    const int bi = blockIdx.x, L = P.L, K = P.K, R = L + 1, nb = P.nb;
+    const int cells = K * R;  // cell (i, o) is i * K + o
+    double *V = lds_small, *W = V + cells, *X = W + cells;  // X[tri(o, o2) * R + j]
+    for (int e = threadIdx.x; e < K * (K - 1) / 2 * R; e += kSmallThreads) {
+        const int q = e / R, j = e - q * R;
+        int o2 = 1;
+        while ((o2 + 1) * o2 / 2 <= q) ++o2;
+        const int o = q - o2 * (o2 - 1) / 2;
+        X[e] = j >= 1 && j < L ? link_time(P, P.bvals[bi], j, P.E[(int64_t)order[o] * K + order[o2]]) : kInf;
+    }
+    auto stage = [&](int d) { return Td + ((int64_t)(d - 1) * nb + bi) * P.NS * K; };
+    // the first cut a scan starts at: the first balanced one with imbalance pruning
+    auto first_cut = [&](int i, int o) { return P.jlo ? max(i + 1, P.jlo[order[o] * L + i]) : i + 1; };
+    auto level_root = [&](int d, double mine) {  // least of the row-0 cells
+        mine = wave_min(mine);
+        if (wave_lane() == 0) red[threadIdx.x / kWave] = mine;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double m = red[0];
+            for (int u = 1; u < kSmallThreads / kWave; ++u) m = fmin(m, red[u]);
+            s_root[d - 1] = m;
+        }
+    };
+    for (int d = 1; d <= D; ++d) {
+        const double *T = stage(d);
+        const int jmax = L - d + 1;
+        double mine = kInf;
+        for (int e = threadIdx.x; e < cells; e += kSmallThreads) {
+            const int i = e / K, o = e - i * K;
+            double v = kInf;
+            if (d == 1 && i < L) v = T[slice_of(L, i, L) * K + o];
+            if (d > 1 && i <= L - d) {
+                const double *Ti = T + slice_of(L, i, i + 1) * K + o;
+                bool go = true;
+                for (int j0 = first_cut(i, o); go && j0 <= jmax; j0 += kAhead) {
+                    double t[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) t[u] = Ti[(min(j0 + u, jmax) - i - 1) * K];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        go = go && t[u] < v;  // T never decreases in j (a repeated last cut changes nothing)
+                        if (go) v = fmin(v, fmax(t[u], W[min(j0 + u, jmax) * K + o]));
+                    }
+                }
+            }
+            V[e] = v;
+            if (i == 0) mine = fmin(mine, v);
+        }
+        level_root(d, mine);  // synchronises: V is complete, W is read
+        if (d == D) break;
+        for (int e = threadIdx.x; e < cells; e += kSmallThreads) {
+            const int j = e / K, o = e - j * K;
+            double w = kInf;
+            if (j >= 1 && j <= L - d)
+                for (int q = o + 1; q < K; ++q) w = fmin(w, fmax(X[tri(o, q) * R + j], V[j * K + q]));
+            W[e] = w;
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+    double ps = kInf;
+    int top = 0;
+    for (int d = 1; d <= D; ++d) ps = fmin(ps, s_root[d - 1]);
+    for (int d = 1; d <= D; ++d)
+        if (ps < kInf && s_root[d - 1] <= ps) top = d;
+    double best = kInf;
+    int best_o = -1, best_d = -1;
+    for (int d = 1; d <= top; ++d) {
+        const double *T = stage(d);
+        const int jmax = L - d + 1;
+        __syncthreads();
+        for (int e = threadIdx.x; e < cells; e += kSmallThreads) {
+            const int i = e / K, o = e - i * K;
+            double v = kInf;
+            int arg = 0xFFFF;
+            if (d == 1 && i < L) {
+                const double t = T[slice_of(L, i, L) * K + o];
+                if (t <= ps) {
+                    v = t;
+                    arg = L;
+                }
+            }
+            if (d > 1 && i <= L - d) {
+                const double *Ti = T + slice_of(L, i, i + 1) * K + o;
+                bool go = true;
+                for (int j0 = first_cut(i, o); go && j0 <= jmax; j0 += kAhead) {
+                    double t[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) t[u] = Ti[(min(j0 + u, jmax) - i - 1) * K];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int j = min(j0 + u, jmax);
+                        go = go && t[u] <= ps && t[u] < v && j0 + u <= jmax;
+                        const double c = t[u] + W[j * K + o];
+                        if (go && c < v) {
+                            v = c;
+                            arg = j;
+                        }
+                    }
+                }
+            }
+            V[e] = v;
+            if (i < L) argF[(((int64_t)(d - 1) * nb + bi) * L + i) * K + o] = (uint16_t)(v < kInf ? arg : 0xFFFF);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int o = 0; o < K; ++o)
+                if (V[o] < best || (V[o] == best && best < kInf && o < best_o)) {
+                    best = V[o];
+                    best_o = o;
+                    best_d = d;
+                }
+        if (d == top) break;
+        for (int e = threadIdx.x; e < cells; e += kSmallThreads) {
+            const int j = e / K, o = e - j * K;
+            double w = kInf;
+            int arg = 0xFF;
+            if (j >= 1 && j <= L - d)
+                for (int q = o + 1; q < K; ++q) {
+                    const double x = X[tri(o, q) * R + j];
+                    const double c = x + V[j * K + q];
+                    if (x <= ps && c < w) {
+                        w = c;
+                        arg = q;
+                    }
+                }
+            W[e] = w;
+            argG[(((int64_t)(d - 1) * nb + bi) * R + j) * K + o] = (uint8_t)(w < kInf ? arg : 0xFF);
+        }
+    }
+    if (threadIdx.x == 0) {
+        Pst[bi] = ps;
+        rootF[bi] = best;
+        root_o[bi] = best < kInf ? best_o : -1;
+        root_d[bi] = best < kInf ? best_d : -1;
+    }
+}
+
+// The plan: one block chooses b and walks the argmins, picks the entries of the
+// plan's groups out of the list (small_problem bounds their number), then a
+// wave per stage finds its candidate among them.
+__global__ __launch_bounds__(kFinishThreads) void small_finish(DevProblem P, const int64_t *__restrict__ surv,
+                                                               int64_t n, const int32_t *__restrict__ rec_g,
+                                                               const double *__restrict__ rec_c,
+                                                               const uint8_t *__restrict__ rec_d,
+                                                               const int32_t *order, const double *Pst,
+                                                               const double *rootF, const int32_t *root_o,
+                                                               const int32_t *root_d, const uint16_t *argF,
+                                                               const uint8_t *argG, ComposeResult *res,
+                                                               ComposeResult *res_host) {
+    __shared__ PlanWalk W;
+    __shared__ int32_t s_group[256];  // by position: the stage's group
+    __shared__ double m_c[kSmallMatches];
+    __shared__ int64_t m_i[kSmallMatches];
+    __shared__ uint8_t m_d[kSmallMatches];
+    __shared__ int16_t m_o[kSmallMatches];
+    __shared__ int32_t s_n;
+    choose_and_walk(P, Pst, rootF, root_o, root_d, argF, argG, res, W);
+    if (threadIdx.x < 256) s_group[threadIdx.x] = -1;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const int S = W.S, bb = S > 0 ? W.bb : 0;
+    if ((int)threadIdx.x < S) {
+        const int t = threadIdx.x;
+        s_group[W.o[t]] = (int32_t)group_id(P, W.o[t], bb, slice_of(P.L, W.i[t], W.j[t]));
+    }
+    __syncthreads();
+    if (S > 0)
+        for (int64_t r = threadIdx.x; r < n; r += kFinishThreads) {
+            const int32_t G = rec_g[r];
+            if (G < 0) continue;
+            const int o = (int)(G / ((int64_t)P.nb * P.NS));
+            if (s_group[o] != G) continue;
+            const int at = atomicAdd(&s_n, 1);
+            if (at < kSmallMatches) {
+                m_c[at] = rec_c[r];
+                m_i[at] = surv[r];
+                m_d[at] = rec_d[r];
+                m_o[at] = (int16_t)o;
+            }
+        }
+    __syncthreads();
+    const int nm = min(s_n, kSmallMatches);
+    const int wv = threadIdx.x / kWave;
+    for (int t = wv; t < S; t += kFinishThreads / kWave) {
+        const int d = S - t, o = W.o[t], j = W.j[t];
+        const int64_t b = P.bvals[bb];
+        const double link =
+            d > 1 ? link_time(P, b, j, P.E[(int64_t)order[o] * P.K + order[W.on[t]]]) : 0.0;
+        resolve_entries(P, nm, [&](int e) { return m_o[e] == o; }, m_c, m_d, m_i, 0, W.i[t], j, order[o], d, link,
+                        res->plan.stage[t], res);
+    }
+    if (!res_host) return;
+    __syncthreads();
+    store_result(res, res_host, S);
+}
+
+static hipError_t launch_small(const DevProblem &P, const int64_t *surv, int64_t n, const double *cost,
+                               const uint8_t *dmax, const int32_t *order, void *ws, hipStream_t s,
+                               ComposeResult *res_host) {
+    const Ws w = carve(P, n, ws);
+    const int D = levels(P);
+    const int64_t cells = n_groups(P) * D;
+    const unsigned blocks = (unsigned)std::min<int64_t>((cells + 255) / 256 + 1, 256);
+    small_init<<<dim3(blocks), dim3(256), 0, s>>>(P, order_arg(order, P.K), w.order, w.pos, w.Td, cells, w.res);
+    if (n > 0)
+        gather_kernel<true><<<dim3((unsigned)((n + kGatherBlock - 1) / kGatherBlock)), dim3(256), 0, s>>>(
+            P, surv, n, cost, dmax, w.pos, w.rec_g, w.rec_c, w.rec_d, nullptr, w.res, D, w.Td);
+    small_levels<<<dim3((unsigned)P.nb), dim3(kSmallThreads), small_lds(P), s>>>(
+        P, D, w.order, w.Td, w.Pst, w.rootF, w.root_o, w.root_d, w.argF, w.argG);
+    small_finish<<<dim3(1), dim3(kFinishThreads), 0, s>>>(P, surv, n, w.rec_g, w.rec_c, w.rec_d, w.order, w.Pst,
+                                                          w.rootF, w.root_o, w.root_d, w.argF, w.argG, w.res,
+                                                          res_host);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -1595,9 +1914,9 @@ struct Driver {
 
     // candidate list -> grouped entries -> starting tables (one copy per
     // phase) and per-row, per-level table changes
-    void setup(const int64_t *surv, int64_t n_surv, const double *cost, const uint8_t *dmax) {
-        prep_kernel<<<dim3((unsigned)((P.K * P.K + 255) / 256)), dim3(256), 0, s>>>(P, w.order, w.pos, w.EoT,
-                                                                                     w.EiT, w.res, w.ev_total);
+    void setup(const int32_t *order, const int64_t *surv, int64_t n_surv, const double *cost, const uint8_t *dmax) {
+        prep_kernel<<<dim3((unsigned)((P.K * P.K + 255) / 256)), dim3(256), 0, s>>>(
+            P, order_arg(order, P.K), w.order, w.pos, w.EoT, w.EiT, w.res, w.ev_total);
         if (P.imb)
             jlo_kernel<<<dim3((unsigned)((P.K * P.L + 255) / 256)), dim3(256), 0, s>>>(P, w.order, w.jlo_pos);
         const Groups g{w.rec_g, w.rec_c, w.rec_d, w.gcnt, w.ent_c, w.ent_d, w.ent_i, w.tmp};
@@ -1798,12 +2117,15 @@ struct Driver {
 };
 
 hipError_t launch_compose(const DevProblem &P, const int64_t *surv, int64_t n_surv, const double *cost,
-                          const uint8_t *dmax, const int32_t *order_dev, void *ws, hipStream_t s,
+                          const uint8_t *dmax, const int32_t *order_host, void *ws, hipStream_t s,
                           ComposeResult **result_dev, const ComposeHost *host) {
-    (void)order_dev;
+    if (small_problem(P) && n_surv <= kSmallList) {
+        *result_dev = carve(P, n_surv, ws).res;
+        return launch_small(P, surv, n_surv, cost, dmax, order_host, ws, s, host ? host->res_dev : nullptr);
+    }
     Driver dr(P, n_surv, ws, s);
     *result_dev = dr.w.res;
-    dr.setup(surv, n_surv, cost, dmax);
+    dr.setup(order_host, surv, n_surv, cost, dmax);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the overlapped read-back pays at any depth past the lead: the GPU keeps
@@ -1885,7 +2207,7 @@ hipError_t launch_compose_relaxed(const DevProblem &P, const RelaxHost &H, const
     for (int bi = 0; bi < nb; ++bi) h_mm1[bi] = (double)(H.B / H.bvals[bi] - 1);
     hipError_t e = hipMemcpyAsync(r.mm1, h_mm1, sizeof(double) * nb, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
-    dr.setup(surv, n_surv, cost, dmax);
+    dr.setup(order_host, surv, n_surv, cost, dmax);
     e = hipGetLastError();
     if (e == hipSuccess)
         e = hipMemcpyAsync(r.Tp, dr.w.T0, sizeof(double) * n_groups(P), hipMemcpyDeviceToDevice, s);

@@ -53,18 +53,20 @@ void launch_grouping(const DevProblem &P, const int64_t *surv, int64_t n, const 
 // with no fitting candidate sets res->err = 4 (the stage table said one fits).
 // G is the group's index in the grouped entries (callers number groups their
 // own way).
-__device__ inline void resolve_stage(const DevProblem &P, const int32_t *gcnt, const double *ent_c,
-                                     const uint8_t *ent_d, const int64_t *ent_i, int64_t G, int i, int j,
-                                     int island, int d, double link, tg_stage &sg, ComposeResult *res) {
+// resolve_entries: the same over entries [st, en) of which `mine` tells the
+// group's own.
+template <typename Mine>
+__device__ inline void resolve_entries(const DevProblem &P, int32_t en, Mine mine, const double *ent_c,
+                                       const uint8_t *ent_d, const int64_t *ent_i, int32_t st, int i, int j,
+                                       int island, int d, double link, tg_stage &sg, ComposeResult *res) {
     const int L = P.L;
     const int lane = threadIdx.x % kWave;
-    const int32_t st = G ? gcnt[G - 1] : 0, en = gcnt[G];
     int64_t best = -1;
     double bc = kInf;
     int bd = 0;
     for (int32_t e = st + lane; e < en; e += kWave) {
         const int dd = ent_d[e];
-        if (dd < d) continue;
+        if (dd < d || !mine(e)) continue;
         const double c = ent_c[e];
         const int64_t ie = ent_i[e];
         if (cand_less(c, dd, ie, bc, bd, best)) {
@@ -116,6 +118,13 @@ __device__ inline void resolve_stage(const DevProblem &P, const int32_t *gcnt, c
     // in flight: min(d, m) micro-batches, one when offloaded
     sg.mem_bytes = state + (fmin(c.of ? 1.0 : (double)d, c.m_real) * A1);
     sg.link_out = link;
+}
+
+__device__ inline void resolve_stage(const DevProblem &P, const int32_t *gcnt, const double *ent_c,
+                                     const uint8_t *ent_d, const int64_t *ent_i, int64_t G, int i, int j,
+                                     int island, int d, double link, tg_stage &sg, ComposeResult *res) {
+    resolve_entries(P, gcnt[G], [](int) { return true; }, ent_c, ent_d, ent_i, G ? gcnt[G - 1] : 0, i, j, island, d,
+                    link, sg, res);
 }
 
 // A result's header and its S stages into host memory, by one block (8-byte words).

@@ -186,9 +186,8 @@ struct ComposeHost {
     hipEvent_t ev;
 };
 hipError_t launch_compose(const DevProblem &P, const int64_t *surv, int64_t n_surv, const double *cost,
-                          const uint8_t *dmax, const int32_t *order_dev, void *ws, hipStream_t s,
+                          const uint8_t *dmax, const int32_t *order_host, void *ws, hipStream_t s,
                           ComposeResult **result_dev, const ComposeHost *host = nullptr);
-size_t compose_order_offset(const DevProblem &P, int64_t n_surv);  // where the order table lives in ws
 
 // Host tables the relaxed search reads (link times are enumerated on the host).
 // Pinned host memory owned by a caller and reused across calls (small
