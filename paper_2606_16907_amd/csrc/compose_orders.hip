@@ -747,15 +747,18 @@ __global__ __launch_bounds__(256) void orders_reduce_part(SetLevels lv, const in
 }
 
 // No plan known and no fill root yet for any b (a b whose fill does not run
-// keeps none).
-__global__ __launch_bounds__(256) void orders_clear_b(int nb, unsigned long long *cut, double *rootF,
-                                                      uint32_t *rootKey) {
+// keeps none).  A small search gets no bounds either: every band is whole, as
+// if an island could take every layer (and so every state's root is written).
+__global__ __launch_bounds__(256) void orders_clear_b(DevProblem P, int D, bool whole, unsigned long long *cut,
+                                                      double *tau, int32_t *ml, double *rootF, uint32_t *rootKey) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < nb) {
+    if (t < P.nb) {
         cut[t] = 0x7FF0000000000000ull;
+        tau[t] = kInf;
         rootF[t] = kInf;
         rootKey[t] = kNoKey;
     }
+    if (whole && t < P.nb * (D + 2) * P.K) ml[t] = (t / P.K) % (D + 2) <= D ? P.L : 0;
 }
 
 __global__ __launch_bounds__(256) void orders_reduce_final(const double *__restrict__ part_v,
@@ -871,15 +874,16 @@ __global__ __launch_bounds__(kOrderFinishThreads) void orders_finish(
 // ---------------------------------------------------------------------------
 // host-side sequencing
 // ---------------------------------------------------------------------------
-// One phase's levels for nrow b, those of the list.
+// One phase's levels for nrow b, those of the list; whole: every band is whole.
 template <bool kFill>
 static void run_levels(const DevProblem &P, const SetLevels &lv, const OrdersWs &w, hipStream_t s, int nrow,
-                       const BList &blist) {
+                       const BList &blist, bool whole) {
     const int L = P.L;
     const double *bounds = kFill ? w.Pst : w.tau;
     // a level writes the roots of its sets whose band reaches layer 0
-    orders_reset<<<dim3((unsigned)std::min<int64_t>((lv.total + 1023) / 1024, 1024), (unsigned)nrow), dim3(256), 0,
-                   s>>>(w.root, lv.total, blist);
+    if (!whole)
+        orders_reset<<<dim3((unsigned)std::min<int64_t>((lv.total + 1023) / 1024, 1024), (unsigned)nrow), dim3(256), 0,
+                       s>>>(w.root, lv.total, blist);
     const dim3 g1((unsigned)(((int64_t)P.K * (L + 1) + 255) / 256), (unsigned)nrow);
     orders_level1<kFill><<<g1, dim3(256), 0, s>>>(P, lv, w.T, w.Pst, w.Vb[1], w.root, blist);
     for (int d = 2; d <= lv.D; ++d) {
@@ -920,22 +924,25 @@ hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host,
     // a small search skips the bounds and fills every b: host and device round
     // trips would cost more than they save
     const bool small = (int64_t)nb * lv.total * (P.L + 1) < kPruneCells;
-    orders_clear_b<<<dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s>>>(nb, w.cut, w.rootF, w.rootKey);
-    if (!small)
+    const int n_clear = nb * (lv.D + 2) * P.K;
+    orders_clear_b<<<dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, s>>>(P, lv.D, small, w.cut, w.tau, w.ml,
+                                                                                w.rootF, w.rootKey);
+    if (!small) {
         orders_cutoff<<<dim3(kCutOrders, (unsigned)nb), dim3(kCutThreads), 0, s>>>(P, lv.D, w.T, w.X, w.fixed, w.cut);
-    orders_bound<<<dim3(1), dim3(256), 0, s>>>(P, lv.D, w.cut, w.tau);
+        orders_bound<<<dim3(1), dim3(256), 0, s>>>(P, lv.D, w.cut, w.tau);
+    }
     auto longest = [&](const double *bound) {
         const int64_t n = (int64_t)nb * (lv.D + 2) * P.K;
         orders_longest<<<dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s>>>(P, lv.D, w.T, bound, w.ml);
     };
-    longest(w.tau);
-    run_levels<false>(P, lv, w, s, nb, every);
+    if (!small) longest(w.tau);
+    run_levels<false>(P, lv, w, s, nb, every, small);
     double *hv = host && host->dlim ? (double *)host->dlim : nullptr;  // nb pinned words, and their device view
     double *hv_dev = hv ? (double *)host->dlim_dev : nullptr;
     orders_reduce_part<false><<<dim3(kReduceChunks, (unsigned)nb), dim3(256), 0, s>>>(lv, w.masks, w.root, w.part_v,
                                                                                      w.part_k, every);
     orders_reduce_final<<<dim3((unsigned)nb), dim3(256), 0, s>>>(w.part_v, w.part_k, w.Pst, nullptr, hv_dev, every);
-    longest(w.Pst);
+    if (!small) longest(w.Pst);
     // the values of the nb words at `dev`, through the pinned words or a copy
     auto read_back = [&](const double *dev, double *out) -> hipError_t {
         hipError_t e = hv ? hipSuccess : hipMemcpyAsync(out, dev, sizeof(double) * nb, hipMemcpyDeviceToHost, s);
@@ -948,7 +955,7 @@ hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host,
             BList list{};
             list.n = (int32_t)std::min<size_t>(kRunB, bl.size() - at);
             std::copy(bl.begin() + at, bl.begin() + at + list.n, list.b);
-            run_levels<true>(P, lv, w, s, list.n, list);
+            run_levels<true>(P, lv, w, s, list.n, list, small);
             orders_reduce_part<true><<<dim3(kReduceChunks, (unsigned)list.n), dim3(256), 0, s>>>(
                 lv, w.masks, w.root, w.part_v, w.part_k, list);
             orders_reduce_final<<<dim3((unsigned)list.n), dim3(256), 0, s>>>(w.part_v, w.part_k, w.rootF, w.rootKey,

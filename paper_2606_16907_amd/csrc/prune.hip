@@ -225,6 +225,15 @@ constexpr int kBucketMembers = 0xFFFE;  // a member's number in its group takes 
 constexpr int kBucketBatch = 8;
 constexpr int kBucketChunk = 128;       // members per LDS mask round
 
+// Buckets pay for setting up and sweeping K depths a group, so they take
+// clusters whose groups average at least 1.5 K members: at 1.5 to 1.8 (uneven,
+// 70B, MoE) they gain 8 to 40%, at 1.0 (18 islands, 125 layers, 18 members a
+// group) the staircase took 123 us a call against 142.
+static bool use_buckets(const DevProblem &P) {
+    return P.K <= kBucketDepths && P.max_members <= kBucketMembers &&
+           2 * (int64_t)P.n_rows >= 3 * (int64_t)P.K * P.n_kb;
+}
+
 static size_t bucket_lds(int K) { return (size_t)K * kWave * (sizeof(double) + sizeof(uint16_t)); }
 
 __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const double *__restrict__ cost,
@@ -530,7 +539,7 @@ size_t prune_ws_bytes(const DevProblem &P) { return carve_prune(P, nullptr).byte
 static hipError_t launch_frontier(const DevProblem &P, const double *cost, const uint8_t *dmax, uint64_t *bitmap,
                                   hipStream_t s) {
     const int64_t n_front = (int64_t)P.n_kb * P.words;
-    if (n_front > 0 && P.K <= kBucketDepths && P.max_members <= kBucketMembers) {
+    if (n_front > 0 && use_buckets(P)) {
         frontier_buckets<<<dim3((unsigned)n_front), dim3(kWave), bucket_lds(P.K), s>>>(P, cost, dmax, bitmap);
     } else if (n_front > 0) {
         const int64_t blocks = (n_front + kFrontWaves - 1) / kFrontWaves;

@@ -49,7 +49,8 @@ def _survivors(p, batch, cost, dmax):
 
 @pytest.mark.parametrize("L,K,gpus,batch,cp", [
     (3, 1, 2, 4, (1,)), (11, 2, 4, 8, (1,)), (12, 5, 3, 6, (1, 2)), (4, 31, 4, 4, (1,)), (4, 32, 4, 4, (1,)),
-    (4, 33, 4, 4, (1,)), (3, 64, 3, 4, (1,)), (11, 3, 64, 64, (1, 2, 4, 8))])
+    (4, 33, 4, 4, (1,)), (3, 64, 3, 4, (1,)), (11, 3, 64, 64, (1, 2, 4, 8)), (2, 32, 32, 64, (1, 2, 4)),
+    (2, 33, 32, 64, (1, 2, 4))])
 @pytest.mark.parametrize("seed", range(3))
 def test_frontier(L, K, gpus, batch, cp, seed):
     print("case", L, K, gpus, batch, seed, flush=True)
