@@ -106,14 +106,14 @@ __device__ inline void wave_sync() {
 }
 
 // Writes the bitmap words of every member of the wave's group for its slice
-// chunk: the lanes' entries set their bits in an LDS mask, kMaskChunk members
+// chunk: the lanes' entries set their bits in an LDS mask, kChunk members
 // at a time.  After the first pass a word also keeps the bits it already
 // has.
-template <int kStair>
+template <int kStair, int kChunk>
 __device__ inline void record_pass(const DevProblem &P, uint64_t *mask, const uint32_t (&pk)[kStair], bool mine,
                                    int lane, int m0, int nm, int64_t sc, bool merge, uint64_t *bitmap) {
-    for (int base = 0; base < nm; base += kMaskChunk) {
-        const int n = min(kMaskChunk, nm - base);
+    for (int base = 0; base < nm; base += kChunk) {
+        const int n = min(kChunk, nm - base);
         for (int m = lane; m < n; m += kWave) mask[m] = 0;
         wave_sync();
         if (mine) {
@@ -132,26 +132,36 @@ __device__ inline void record_pass(const DevProblem &P, uint64_t *mask, const ui
     }
 }
 
-template <int kStair>
-__global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const double *__restrict__ cost,
-                                                       const uint8_t *__restrict__ dmax, uint64_t *bitmap,
-                                                       int64_t n_tiles) {
-    __shared__ uint64_t smask[kFrontWaves][kMaskChunk];
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t tile = (int64_t)blockIdx.x * kFrontWaves + wv;
-    if (tile >= n_tiles) return;  // whole waves leave; nothing below synchronises the block
-    const int q = (int)(tile / P.words);
-    const int64_t sc = tile - (int64_t)q * P.words;
-    const int m0 = P.kb_off[q];
-    const int nm = P.kb_off[q + 1] - m0;
-    const int64_t s = sc * kWave + lane;
-    const int64_t NS = P.NS;
-    bool need = s < NS;
-    if (need && P.imb) {  // an unbalanced (slice, island) group has no survivors
-        const uint32_t ij = P.sij[s];
-        need = slice_balanced(P, P.pre, (int)(ij & 0xFFFFu), (int)(ij >> 16), P.kb_island[q]);
+// Members whose cost is no number (scores of this library are numbers; a
+// caller's arrays may hold anything) survive where they fit at all and beat
+// nobody: their bits are added to the words already recorded, by the lane that
+// wrote them.
+__device__ inline void nan_pass(const DevProblem &P, const double *__restrict__ cost,
+                                const uint8_t *__restrict__ dmax, uint64_t *bitmap, bool need, int lane, int m0,
+                                int nm, int64_t s, int64_t sc) {
+    for (int m = 0; m < nm; ++m) {
+        const int64_t at = (int64_t)P.kb_members[m0 + m] * P.NS + s;
+        bool mine = false;
+        if (need && dmax[at] > 0) {
+            const double c = cost[at];
+            mine = c != c;
+        }
+        const uint64_t word = __ballot(mine);
+        if (word && lane == (m & (kWave - 1))) bitmap[(int64_t)P.kb_rows[m0 + m] * P.words + sc] |= word;
     }
+}
+
+// The register staircase of a wave: its 64 slices' groups (members m0 .. m0 + nm
+// - 1) in as many passes as their survivors need, each recorded in the bitmap.
+// `need` lanes have a group.  A cost that is no number is not offered (several
+// of one depth would fill the slots in every pass, without end).
+template <int kStair, int kChunk>
+__device__ inline void stair_passes(const DevProblem &P, uint64_t *mask, const double *__restrict__ cost,
+                                    const uint8_t *__restrict__ dmax, uint64_t *bitmap, bool need, int lane, int m0,
+                                    int nm, int64_t s, int64_t sc) {
+    const int64_t NS = P.NS;
+    const bool grouped = need;
+    bool nan = false;
     int hi = 1 << 30;  // members deeper than hi are settled (by an earlier pass)
     double cap = 0.0;  // least cost among the settled members, once there are any
     bool capped = false;
@@ -179,10 +189,14 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
             for (int u = 0; u < 8; ++u) c[u] = (d[u] > floor && d[u] <= hi) ? crow[u][s] : 0.0;
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (d[u] > floor && d[u] <= hi && !(capped && cap <= c[u]))
-                    stair_offer<kStair>(cv, pk, c[u], d[u], mb + u, floor);
+                if (d[u] > floor && d[u] <= hi && !(capped && cap <= c[u])) {
+                    if (c[u] == c[u])
+                        stair_offer<kStair>(cv, pk, c[u], d[u], mb + u, floor);
+                    else
+                        nan = true;
+                }
         }
-        record_pass<kStair>(P, smask[wv], pk, need, lane, m0, nm, sc, merge, bitmap);
+        record_pass<kStair, kChunk>(P, mask, pk, need, lane, m0, nm, sc, merge, bitmap);
         merge = true;
         if (need) {
             if (floor == 0) {
@@ -203,6 +217,29 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
         // same words, so program order already holds; the fence makes it plain)
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     } while (__ballot(need) != 0);
+    if (__builtin_expect(__ballot(nan) != 0, 0)) nan_pass(P, cost, dmax, bitmap, grouped, lane, m0, nm, s, sc);
+}
+
+template <int kStair>
+__global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const double *__restrict__ cost,
+                                                       const uint8_t *__restrict__ dmax, uint64_t *bitmap,
+                                                       int64_t n_tiles) {
+    __shared__ uint64_t smask[kFrontWaves][kMaskChunk];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t tile = (int64_t)blockIdx.x * kFrontWaves + wv;
+    if (tile >= n_tiles) return;  // whole waves leave; nothing below synchronises the block
+    const int q = (int)(tile / P.words);
+    const int64_t sc = tile - (int64_t)q * P.words;
+    const int m0 = P.kb_off[q];
+    const int nm = P.kb_off[q + 1] - m0;
+    const int64_t s = sc * kWave + lane;
+    bool need = s < P.NS;
+    if (need && P.imb) {  // an unbalanced (slice, island) group has no survivors
+        const uint32_t ij = P.sij[s];
+        need = slice_balanced(P, P.pre, (int)(ij & 0xFFFFu), (int)(ij >> 16), P.kb_island[q]);
+    }
+    stair_passes<kStair, kMaskChunk>(P, smask[wv], cost, dmax, bitmap, need, lane, m0, nm, s, sc);
 }
 
 // The frontier by depth buckets, for clusters of at most kBucketDepths islands
@@ -217,6 +254,9 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
 // (the next batch's depths load with this batch's costs) at the 7 to 15 waves a
 // CU that 20 KB (32 islands) to 10 KB (16) leave; a wider cluster keeps the
 // registers.  Groups go largest first, so the last blocks are short ones.
+// This library's depths are at most K; a wave that meets a deeper one in a
+// caller's arrays starts over with the staircase, which has no such limit (the
+// LDS bounds the waves a CU holds, so its registers are free here).
 // Register staircase -> buckets, frontier kernel: extended MoE 790 -> 370 us,
 // extended 70B 385 -> 275, uneven 27 islands 113 -> 103, MoE 90 -> 64, 70B 38 ->
 // 35, 8B 17 -> 13; batches of 12, 16 and 24 members within 3% either way.
@@ -263,6 +303,8 @@ __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const do
         who[d * kWave] = kNone;
     }
     const int64_t at = need ? s : 0;  // lanes that score nothing read row starts
+    int deepest = 0;
+    bool nan = false;
     int d[kBucketBatch];
 #pragma unroll
     for (int u = 0; u < kBucketBatch; ++u) {
@@ -284,17 +326,29 @@ __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const do
             dn[u] = m < nm && need ? v : 0;
         }
 #pragma unroll
-        for (int u = 0; u < kBucketBatch; ++u)
+        for (int u = 0; u < kBucketBatch; ++u) {
+            deepest = max(deepest, d[u]);
             if (d[u] > 0 && d[u] <= K) {
                 const int b = (d[u] - 1) * kWave;
-                // ties stay with the earlier member; a cost that is no number never survives
-                if (!(best[b] <= c[u]) && c[u] == c[u]) {
-                    best[b] = c[u];
-                    who[b] = (uint16_t)(mb + u);
+                if (!(best[b] <= c[u])) {  // ties stay with the earlier member
+                    if (c[u] == c[u]) {
+                        best[b] = c[u];
+                        who[b] = (uint16_t)(mb + u);
+                    } else {
+                        nan = true;
+                    }
                 }
             }
+        }
 #pragma unroll
         for (int u = 0; u < kBucketBatch; ++u) d[u] = dn[u];
+    }
+    if (__builtin_expect(__ballot(deepest > K) != 0, 0)) {
+        if (P.max_members <= kSmallGroup)
+            stair_passes<4, kBucketChunk>(P, mask, cost, dmax, bitmap, need, lane, m0, nm, s, sc);
+        else
+            stair_passes<8, kBucketChunk>(P, mask, cost, dmax, bitmap, need, lane, m0, nm, s, sc);
+        return;
     }
     // a bucket survives if it is cheaper than every deeper one
     double least = __builtin_nan("");
@@ -316,6 +370,10 @@ __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const do
         wave_sync();
         for (int m = lane; m < n; m += kWave) bitmap[(int64_t)P.kb_rows[m0 + base + m] * P.words + sc] = mask[m];
         wave_sync();
+    }
+    if (__builtin_expect(__ballot(nan) != 0, 0)) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        nan_pass(P, cost, dmax, bitmap, need, lane, m0, nm, s, sc);
     }
 }
 

@@ -67,3 +67,26 @@ def test_frontier(L, K, gpus, batch, cp, seed):
         dmax[rng.random(n) < 0.9] = 0
     got = p.tg_prune(torch.from_numpy(cost).cuda(), torch.from_numpy(dmax).cuda()).cpu().numpy()
     assert np.array_equal(got, _survivors(p, batch, cost, dmax))
+
+
+@pytest.mark.parametrize("L,K,gpus,batch", [(11, 3, 64, 64), (4, 5, 6, 12), (4, 33, 4, 4)])
+def test_scores_out_of_the_model(L, K, gpus, batch):
+    """Depths past the island count are compared like any other; members whose
+    cost is no number all survive where they fit, many to a group and depth
+    among them, and beat nobody."""
+    print("case", L, K, gpus, batch, flush=True)
+    p = _problem(L, K, gpus, batch)
+    rng = np.random.default_rng([7, L, K])
+    n = p.N
+    cost = rng.integers(0, 40, size=n) * 0.25
+    dmax = rng.integers(0, 256, size=n).astype(np.uint8)
+    got = p.tg_prune(torch.from_numpy(cost).cuda(), torch.from_numpy(dmax).cuda()).cpu().numpy()
+    assert np.array_equal(got, _survivors(p, batch, cost, dmax))
+    dmax = np.minimum(dmax, K).astype(np.uint8)
+    nan = rng.random(n) < 0.5
+    pairs = p.tg_enumerate_pairs().cpu().numpy()
+    fits = (batch % (pairs[:, 5].astype(np.int64) * pairs[:, 10]) == 0) & (dmax > 0)
+    want = np.union1d(_survivors(p, batch, cost, np.where(nan, 0, dmax).astype(np.uint8)), np.nonzero(nan & fits)[0])
+    cost[nan] = np.nan
+    got = p.tg_prune(torch.from_numpy(cost).cuda(), torch.from_numpy(dmax).cuda()).cpu().numpy()
+    assert np.array_equal(got, want)
