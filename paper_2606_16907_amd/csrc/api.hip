@@ -263,6 +263,7 @@ static tg_status problem_create(const tg_layer *layers, int32_t L, const tg_isla
     }
     std::vector<int32_t> kb_rows(kb_members.size()), kb_order(kb_island.size());
     for (size_t t = 0; t < kb_members.size(); ++t) kb_rows[t] = cfg[kb_members[t]].row;
+    kb_members.insert(kb_members.end(), tg::kMemberPad, 0);
     for (size_t t = 0; t < kb_order.size(); ++t) kb_order[t] = (int32_t)t;
     std::stable_sort(kb_order.begin(), kb_order.end(),
                      [&](int32_t x, int32_t y) { return kb_off[x + 1] - kb_off[x] > kb_off[y + 1] - kb_off[y]; });

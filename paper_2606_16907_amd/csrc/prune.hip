@@ -245,14 +245,16 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
 // The frontier by depth buckets, for clusters of at most kBucketDepths islands
 // (depths 1..K): a wave keeps, per lane and depth, the least cost among the
 // group's members that fit exactly that deep and the first member costing it,
-// in LDS.  A member is one LDS read, a compare and now and then a write, where
-// the register staircase compares and moves up to eight entries (about 160
-// instructions a member; it was issue-bound at under 2 TB/s on the extended
-// MoE instance).  Afterwards a sweep from the deepest bucket up keeps those
-// cheaper than everything deeper: the survivors, whatever their number, in one
+// in LDS.  A member is one LDS minimum that returns the value before it, now and
+// then a write, and a batch's eight are in flight together (a read, a compare
+// and a write one after the other: 433 us a prune of the extended MoE instance,
+// this way 394); the register staircase compares and moves up to eight entries
+// (about 160 instructions a member; it was issue-bound at under 2 TB/s on the
+// extended MoE instance).  Afterwards a sweep from the deepest bucket up keeps
+// those cheaper than everything deeper: the survivors, whatever their number, in one
 // pass.  Bound by the depth-then-cost loads of kBucketBatch members in flight
 // (the next batch's depths load with this batch's costs) at the 7 to 15 waves a
-// CU that 20 KB (32 islands) to 10 KB (16) leave; a wider cluster keeps the
+// CU that 21 KB (32 islands) to 11 KB (16) leave; a wider cluster keeps the
 // registers.  Groups go largest first, so the last blocks are short ones.
 // This library's depths are at most K; a wave that meets a deeper one in a
 // caller's arrays starts over with the staircase, which has no such limit (the
@@ -263,6 +265,7 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
 constexpr int kBucketDepths = 32;
 constexpr int kBucketMembers = 0xFFFE;  // a member's number in its group takes 16 bits
 constexpr int kBucketBatch = 8;
+static_assert(kMemberPad >= kBucketBatch - 1, "a batch reads past its group");
 constexpr int kBucketChunk = 128;       // members per LDS mask round
 
 // Buckets pay for setting up and sweeping K depths a group, so they take
@@ -274,18 +277,21 @@ static bool use_buckets(const DevProblem &P) {
            2 * (int64_t)P.n_rows >= 3 * (int64_t)P.K * P.n_kb;
 }
 
-static size_t bucket_lds(int K) { return (size_t)K * kWave * (sizeof(double) + sizeof(uint16_t)); }
+static size_t bucket_lds(int K) { return (size_t)(K + 1) * kWave * (sizeof(double) + sizeof(uint16_t)); }
 
 __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const double *__restrict__ cost,
                                                           const uint8_t *__restrict__ dmax,
                                                           uint64_t *__restrict__ bitmap) {
-    extern __shared__ double lds_best[];       // [K][64] least cost of each depth
+    extern __shared__ double lds_best[];       // [K + 1][64] least cost of each depth; 0: what counts for nothing
     __shared__ uint64_t mask[kBucketChunk];
     const int K = P.K;
     const int lane = threadIdx.x;
-    double *best = lds_best + lane;            // depth d: best[(d - 1) * 64]
-    uint16_t *who = (uint16_t *)(lds_best + (int64_t)K * kWave) + lane;
+    double *least_at = lds_best + lane;
+    uint16_t *who_at = (uint16_t *)(lds_best + (int64_t)(K + 1) * kWave) + lane;
+    double *best = least_at + kWave;           // depth d: best[(d - 1) * 64]
+    uint16_t *who = who_at + kWave;
     constexpr uint16_t kNone = 0xFFFF;
+    constexpr double kNever = __builtin_huge_val();
     const int qo = (int)(blockIdx.x / P.words);
     const int64_t sc = blockIdx.x - (int64_t)qo * P.words;
     const int q = P.kb_order[qo];
@@ -298,46 +304,57 @@ __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const do
         const uint32_t ij = P.sij[s];
         need = slice_balanced(P, P.pre, (int)(ij & 0xFFFFu), (int)(ij >> 16), P.kb_island[q]);
     }
-    for (int d = 0; d < K; ++d) {
-        best[d * kWave] = __builtin_nan("");  // empty: not <= any cost
-        who[d * kWave] = kNone;
+    for (int d = 0; d <= K; ++d) {
+        least_at[d * kWave] = kNever;
+        who_at[d * kWave] = kNone;
     }
     const int64_t at = need ? s : 0;  // lanes that score nothing read row starts
+    // the list has kMemberPad more entries: rows past this group's are read and
+    // ignored, so a batch's members load together, with no end to check
+    const int32_t *list = P.kb_members + m0;
+    auto row = [&](int m) { return (int64_t)((uint64_t)(uint32_t)list[m] * (uint32_t)NS); };
     int deepest = 0;
-    bool nan = false;
+    uint64_t nan = 0;  // lanes that met one
     int d[kBucketBatch];
+    const int left = need ? nm : 0;
 #pragma unroll
     for (int u = 0; u < kBucketBatch; ++u) {
-        const int v = dmax[(int64_t)P.kb_members[m0 + min(u, nm - 1)] * NS + at];
-        d[u] = u < nm && need ? v : 0;
+        const int v = (dmax + row(u))[at];
+        d[u] = u < left ? v : 0;
     }
     for (int mb = 0; mb < nm; mb += kBucketBatch) {
         double c[kBucketBatch];
         int dn[kBucketBatch];
 #pragma unroll
-        for (int u = 0; u < kBucketBatch; ++u) {
-            const double *row = cost + (int64_t)P.kb_members[m0 + min(mb + u, nm - 1)] * NS;
-            c[u] = d[u] > 0 ? row[at] : 0.0;
-        }
+        for (int u = 0; u < kBucketBatch; ++u) c[u] = d[u] > 0 ? (cost + row(mb + u))[at] : 0.0;
+        const int next = mb + kBucketBatch < nm ? mb + kBucketBatch : mb;  // the last batch reads itself again
 #pragma unroll
         for (int u = 0; u < kBucketBatch; ++u) {
-            const int m = mb + kBucketBatch + u;
-            const int v = dmax[(int64_t)P.kb_members[m0 + min(m, nm - 1)] * NS + at];
-            dn[u] = m < nm && need ? v : 0;
+            const int v = (dmax + row(next + u))[at];
+            dn[u] = mb + kBucketBatch + u < left ? v : 0;
         }
+        // a wave's LDS operations take effect in order: each member's atomic
+        // returns the least cost before it, this batch's earlier members'
+        // included, and all eight are in flight together
+        double before[kBucketBatch];
+        int slot[kBucketBatch];
+        uint64_t odd = 0;
 #pragma unroll
         for (int u = 0; u < kBucketBatch; ++u) {
             deepest = max(deepest, d[u]);
-            if (d[u] > 0 && d[u] <= K) {
-                const int b = (d[u] - 1) * kWave;
-                if (!(best[b] <= c[u])) {  // ties stay with the earlier member
-                    if (c[u] == c[u]) {
-                        best[b] = c[u];
-                        who[b] = (uint16_t)(mb + u);
-                    } else {
-                        nan = true;
-                    }
-                }
+            odd |= __ballot(!(c[u] < kNever));
+            slot[u] = (c[u] == c[u] ? min(d[u], K) : 0) * kWave;
+            before[u] = __hip_atomic_fetch_min(&least_at[slot[u]], c[u] == c[u] ? c[u] : 0.0, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WAVEFRONT);
+        }
+#pragma unroll
+        for (int u = 0; u < kBucketBatch; ++u)
+            if (!(before[u] <= c[u])) who_at[slot[u]] = (uint16_t)(mb + u);  // ties stay with the earlier member
+        if (__builtin_expect(odd != 0, 0)) {  // an infinite cost takes a depth that has no member yet
+#pragma unroll
+            for (int u = 0; u < kBucketBatch; ++u) {
+                nan |= __ballot(c[u] != c[u]);
+                if (c[u] == kNever && who_at[slot[u]] == kNone) who_at[slot[u]] = (uint16_t)(mb + u);
             }
         }
 #pragma unroll
@@ -354,7 +371,7 @@ __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const do
     double least = __builtin_nan("");
     for (int e = K - 1; e >= 0; --e) {
         const double v = best[e * kWave];
-        if (v == v && !(least <= v))
+        if (who[e * kWave] != kNone && !(least <= v))
             least = v;
         else
             who[e * kWave] = kNone;
@@ -371,7 +388,7 @@ __global__ __launch_bounds__(kWave) void frontier_buckets(DevProblem P, const do
         for (int m = lane; m < n; m += kWave) bitmap[(int64_t)P.kb_rows[m0 + base + m] * P.words + sc] = mask[m];
         wave_sync();
     }
-    if (__builtin_expect(__ballot(nan) != 0, 0)) {
+    if (__builtin_expect(nan != 0, 0)) {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         nan_pass(P, cost, dmax, bitmap, need, lane, m0, nm, s, sc);
     }

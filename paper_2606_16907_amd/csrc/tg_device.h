@@ -37,6 +37,8 @@ struct alignas(32) Config {
 };
 static_assert(sizeof(Config) == 32, "Config must be 32 bytes");
 
+constexpr int kMemberPad = 8;  // entries of kb_members past its last group (any valid config)
+
 // All device tables of one problem.  Passed to kernels by value.
 struct DevProblem {
     int32_t L, K, nb, dense;
