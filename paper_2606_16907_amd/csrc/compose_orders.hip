@@ -21,7 +21,7 @@
 // the same smaller set for each k' in it, so a block owns one (d-1)-set U'
 // (and b) and runs the states (k, U' + {k}) for the islands k outside U' one
 // after the other: the rows come from HBM once, into LDS where they fit
-// (13 KB with the two continuation rows), else from the cache after that.
+// (5 KB with the continuation rows), else from the cache after that.
 // Where a level has few sets, the islands outside U' are split over several
 // blocks.  Per state the block writes its continuation row W_d(., k, U) to
 // LDS, then one thread per first layer i scans the cuts j.  As in the
