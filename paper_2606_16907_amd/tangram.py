@@ -182,21 +182,32 @@ def _dws(t, what, device=None):
     return ctypes.c_void_p(t.data_ptr()), t.numel() * t.element_size()
 
 
-def _fill_table(table, struct, columns):
-    """Fill a ctypes array of structs from columns of host values, each with
-    its conversion (int or float).  A column goes in as one strided copy:
-    field by field through ctypes, 1024 nodes took 0.9 ms, this way 0.2.
-    Columns numpy does not read as plain numbers are converted one by one."""
+def _fill_table(table, struct, source, fields):
+    """Fill a ctypes array of structs from host columns: fields are (struct
+    field, int or float, key of the column in source).  A list goes in as one
+    strided copy: field by field through ctypes, 1024 nodes took 0.9 ms, this
+    way 0.2.  Columns numpy does not read as plain numbers are converted one by
+    one, and a field keeps a whole number's low bits, as a ctypes field does."""
     n = len(table)
     if not n:
         return
     view = np.frombuffer(table, dtype=struct)
-    for field, conv, column in columns:
-        values = np.array(column[:n]) if type(column) is list else None
+    for field, conv, key in fields:
+        column = source[key]
+        values = None
+        if type(column) is list:
+            try:
+                values = np.array(column[:n])
+            except Exception:  # numpy refuses some lists of values that int() or float() takes
+                pass
         if values is None or values.shape != (n,) or values.dtype.kind not in ("i" if conv is int else "if"):
-            values = np.fromiter(map(conv, map(column.__getitem__, range(n))),
-                                 np.int64 if conv is int else np.float64, n)
+            value, dtype = (_wrapped, np.int64) if conv is int else (float, np.float64)
+            values = np.fromiter(map(value, map(column.__getitem__, range(n))), dtype, n)
         view[field] = values
+
+
+def _wrapped(x):
+    return ctypes.c_int64(int(x)).value
 
 
 class Problem:
@@ -207,12 +218,12 @@ class Problem:
         lay = inst["layers"]
         L = len(lay["fwd_flops"])
         layers = (TgLayer * L)()
-        _fill_table(layers, TgLayer, [(f, int, lay[f]) for f in LAYER_FIELDS if f in lay])
+        _fill_table(layers, TgLayer, lay, [(f, int, f) for f in LAYER_FIELDS if f in lay])
         isl = inst["islands"]
         K = len(isl["n_gpus"])
         islands = (TgIsland * K)()
-        _fill_table(islands, TgIsland, [("n_gpus", int, isl["n_gpus"])] + [
-            (f, float, isl[f]) for f in ISLAND_RATES if f != "host_bw" or f in isl])
+        _fill_table(islands, TgIsland, isl, [("n_gpus", int, "n_gpus")] + [
+            (f, float, f) for f in ISLAND_RATES if f != "host_bw" or f in isl])
         inter = (ctypes.c_double * (K * K))(*[float(x) for row in inst["inter_bw"] for x in row])
         sp = inst["space"]
         space = TgSpace()
@@ -480,7 +491,7 @@ def build_islands(cluster, workspace=None):
     nd = cluster["nodes"]
     n = len(nd["gpus"])
     nodes = (TgIsland * n)()
-    _fill_table(nodes, TgIsland, [("n_gpus", int, nd["gpus"])] + [(f, float, nd[f]) for f in ISLAND_RATES])
+    _fill_table(nodes, TgIsland, nd, [("n_gpus", int, "gpus")] + [(f, float, f) for f in ISLAND_RATES])
     e_arr = np.ascontiguousarray(np.asarray(cluster["node_bw"], dtype=np.float64).reshape(n * n))
     e = e_arr.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
     ws = workspace
