@@ -21,7 +21,7 @@
 // the same smaller set for each k' in it, so a block owns one (d-1)-set U'
 // (and b) and runs the states (k, U' + {k}) for the islands k outside U' one
 // after the other: the rows come from HBM once, into LDS where they fit
-// (5 KB with the continuation rows), else from the cache after that.
+// (beside the continuation rows), else from the cache after that.
 // Where a level has few sets, the islands outside U' are split over several
 // blocks.  Per state the block writes its continuation row W_d(., k, U) to
 // LDS, then one thread per first layer i scans the cuts j.  As in the
@@ -39,15 +39,22 @@ namespace tg {
 
 constexpr int kMaxSetIslands = 16;
 constexpr int kMaxLayers = 512;
-constexpr int kLevelLds = 640;  // LDS doubles per level block (one row of the longest model fits): staged rows
-                                // and continuation rows
-constexpr int kLevelThreads = 64;
-static_assert(kLevelLds >= kMaxLayers + 1, "one continuation row");
+// LDS doubles of a level block (one row of the longest model fits), staged rows
+// and continuation rows: with bands, and with whole rows.
+constexpr int kBandLds = 640, kBandThreads = 64;
+constexpr int kWholeLds = 1536, kWholeThreads = 128;
+static_assert(kBandLds >= kMaxLayers + 1 && kWholeLds >= kMaxLayers + 1, "one continuation row");
 constexpr int64_t kPruneCells = (int64_t)1 << 22;  // fill cells below which every b runs at once
 constexpr int kOrderFinishThreads = 1024;
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 constexpr int64_t kTargetBlocks = 8192;  // blocks per level launch worth splitting for
 constexpr int kReduceChunks = 64;        // partials per b in the root reductions
+// Islands from which a search that is not small takes the bounds and bands.
+// With fewer the levels hold few sets and the bounds' own passes over every cut
+// cost more than the bands save: 8 islands and 512 layers 2918 us with bands, 1988
+// without, 10 and 200 1201 against 954, 11 and 512 4587 against 4002, but 12 and
+// 512 4999 against 5975, 12 and 48 857 against 1092.
+constexpr int kBandIslands = 12;
 constexpr int kCutOrders = 4;            // island orders tried for the bound
 constexpr int kCutThreads = 1024;
 constexpr int kAheadCut = 5;             // islands or cuts read at a time there
@@ -448,9 +455,14 @@ __global__ __launch_bounds__(256) void orders_level1(DevProblem P, SetLevels lv,
 // every state, are staged in LDS first where they leave room for two states.
 // A level is bound by the blocks' chains of dependent loads (set, caps, rows,
 // links, costs; about 6 us), so it needs many blocks in flight: one wave and
-// 5 KB of LDS each, 31 to a CU: the 16-island 70B instance's levels took 0.69 +
-// 0.64 ms, against 1.10 + 0.85 with two waves and 12 KB (12 to a CU).
-template <int NT, bool kFill>
+// 5 KB of LDS each: the 16-island 70B instance's levels took 0.69 + 0.64 ms,
+// against 1.10 + 0.85 with two waves and 12 KB.  Without bands the rows are long
+// and neither a bound nor caps are read; there two waves and up to 12 KB, with
+// or without the staged rows, are better: 8 islands and 160 layers 18.6 + 16.6 us
+// a level against 29.2 + 21.7, 16 layers 7.1 + 6.4 against 9.1 + 7.6.
+enum class Rows { kBand, kWhole, kWholeStaged };
+
+template <int NT, bool kFill, Rows kRows>
 __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, int d, int nsplit, int lds_n,
                                                    const int32_t *__restrict__ masks,
                                                    const uint16_t *__restrict__ rank, const double *__restrict__ T,
@@ -474,11 +486,12 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
     const int per = (nk + nsplit - 1) / nsplit;
     const int q0 = part * per, q1 = min(nk, q0 + per);
     const int nu = d - 1;
-    const double bound = bounds[bb];
+    constexpr bool kWhole = kRows != Rows::kBand, kBounded = kFill || !kWhole;
+    const double bound = kBounded ? bounds[bb] : kInf;
     // the band of U' and what the bands of U' + {k} need (each wave by itself)
     const int32_t *mlb = ml + (int64_t)bb * (lv.D + 2) * K;
     int own = 0, out = 0, next = 0, m1max = 0, mdmin = 1 << 20;
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; !kWhole && k < K; ++k) {
         const int m1 = mlb[K + k], md = mlb[d * K + k], mn = mlb[(d + 1) * K + k];
         if (Up >> k & 1u) {
             own += m1;
@@ -489,10 +502,13 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
             mdmin = min(mdmin, mn);
         }
     }
-    const int jlo = max(1, L - own), jhi = min(L - d + 1, out);
-    const int ilo = max(0, L - own - m1max), ihi = min(L - d, next - mdmin);  // covers every state's band
+    const int jlo = kWhole ? 1 : max(1, L - own), jhi = kWhole ? L - d + 1 : min(L - d + 1, out);
+    // cover every state's band (of the last level only whole plans are of use)
+    const int ilo = kWhole ? 0 : max(0, L - own - m1max);
+    const int ihi = kWhole ? (d < lv.D ? L - d : 0) : min(L - d, next - mdmin);
     if (ilo > ihi) return;  // no state has a row in its band
     const int Bj = jhi - jlo + 1;
+    const int jrow = kWhole ? 0 : jlo, Wr = kWhole ? R : Bj;  // an LDS row: its first cut, its length
     const double *Vp = prev + ((int64_t)bb * lv.n[d - 1] + (int64_t)rp * nu) * R;
     // the islands of U' in ascending order (the same for every thread), and
     // each one's row offset in an X block
@@ -506,7 +522,7 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
             r2 &= r2 - 1;
         }
     }
-    constexpr int kIsl = 8;  // islands' link loads in flight
+    constexpr int kIsl = kRows == Rows::kWhole ? 4 : 8;  // islands' link loads in flight
     // the block's states: island k (the q-th outside U', from q0 on) and the
     // state number of (k, U' + {k})
     if ((int)threadIdx.x < q1 - q0) {
@@ -516,12 +532,14 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
         const uint32_t U = Up | (1u << k);
         s_k[threadIdx.x] = (int16_t)k;
         s_st[threadIdx.x] = (int)rank[U] * d + __builtin_popcount(U & ((1u << k) - 1u));
-        s_lo[threadIdx.x] = (int16_t)max(0, L - own - mlb[K + k]);
-        s_hi[threadIdx.x] = (int16_t)min(L - d, next - mlb[(d + 1) * K + k]);
+        if (!kWhole) {
+            s_lo[threadIdx.x] = (int16_t)max(0, L - own - mlb[K + k]);
+            s_hi[threadIdx.x] = (int16_t)min(L - d, next - mlb[(d + 1) * K + k]);
+        }
         s_jlo[threadIdx.x] = INT_MAX;
         s_jhi[threadIdx.x] = -1;
     }
-    if (Bj <= 0) {  // nothing continues: the states' bands hold no plan
+    if (!kWhole && Bj <= 0) {  // nothing continues: the states' bands hold no plan
         __syncthreads();
         const int w = ihi - ilo + 1;
         for (int p = threadIdx.x; p < (q1 - q0) * w; p += NT) {
@@ -530,16 +548,18 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
         }
         return;
     }
-    const bool stage = (nu + 2) * Bj <= lds_n;
-    if (stage)
+    const bool stage = kWhole ? kRows == Rows::kWholeStaged : (nu + 2) * Bj <= lds_n;
+    if (stage && kWhole)
+        for (int t = threadIdx.x; t < nu * R; t += NT) lds_rows[t] = Vp[t];
+    else if (stage)
         for (int t = threadIdx.x; t < nu * Bj; t += NT) {
             const int r = t / Bj;
             lds_rows[t] = Vp[(int64_t)r * R + jlo + t - r * Bj];
         }
     // (offsets from the LDS array itself keep these accesses LDS instructions)
     const double *Vs = lds_rows;
-    double *Wl = lds_rows + (stage ? nu * Bj : 0);
-    const int C = min(q1 - q0, (lds_n - (stage ? nu * Bj : 0)) / Bj);  // states per chunk, at least one
+    double *Wl = lds_rows + (stage ? nu * Wr : 0);
+    const int C = min(q1 - q0, (lds_n - (stage ? nu * Wr : 0)) / Wr);  // states per chunk, at least one
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
     for (int c0 = 0; c0 < q1 - q0; c0 += C) {
@@ -550,8 +570,7 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
             const int p = p0 + (int)threadIdx.x;
             const bool act = p < nwork;
             const int s = act ? p / Bj : nst;  // lanes past the end: a state of their own
-            const int jr = act ? p - s * Bj : 0;
-            const int j = jlo + jr;
+            const int j = act ? jlo + p - s * Bj : 0;
             int jf = INT_MAX;  // j if W is finite
             if (act) {
                 const int qs = c0 + s;
@@ -566,7 +585,7 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
 #pragma unroll
                     for (int u = 0; u < kIsl; ++u) {
                         const int t = min(t0 + u, nu - 1);
-                        vv[u] = stage ? Vs[t * Bj + jr] : Vp[(int64_t)t * R + j];
+                        vv[u] = stage ? Vs[t * Wr + j - jrow] : Vp[(int64_t)t * R + j];
                     }
 #pragma unroll
                     for (int u = 0; u < kIsl; ++u) {
@@ -592,8 +611,8 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
                         }
                     }
                 }
-                if (!kFill && !(w <= bound)) w = kInf;
-                Wl[p] = w;
+                if (!kFill && !kWhole && !(w <= bound)) w = kInf;
+                Wl[s * Wr + j - jrow] = w;
                 if (kFill) {
                     const int64_t gst = (int64_t)bb * lv.total + lv.soff[d] + s_st[qs];
                     argG[gst * R + j] = (uint8_t)arg;
@@ -625,11 +644,11 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
         for (int p = threadIdx.x; p < nrow; p += NT) {
             const int s = p / Bi, i = ilo + p - s * Bi;
             const int qs = c0 + s;
-            if (i < s_lo[qs] || i > s_hi[qs]) continue;
+            if (!kWhole && (i < s_lo[qs] || i > s_hi[qs])) continue;
             const int k = s_k[qs];
             const int st = s_st[qs];
             const int64_t gst = (int64_t)bb * lv.total + lv.soff[d] + st;
-            const double *Wrow = Wl + s * Bj - jlo;
+            const double *Wrow = Wl + s * Wr - jrow;
             double best = kInf;
             int bj = 0;
             const int jend = s_jhi[qs];
@@ -656,7 +675,7 @@ __global__ __launch_bounds__(NT) void orders_level(DevProblem P, SetLevels lv, i
                 for (int u = 0; u < 4; ++u) {
                     const int j = j0 + u;
                     const bool live = go && j <= jend;
-                    const bool stop = live && (tv[u] > bound || tv[u] >= best);
+                    const bool stop = live && ((kBounded && tv[u] > bound) || tv[u] >= best);
                     const double y = kFill ? tv[u] + wv[u] : (tv[u] > wv[u] ? tv[u] : wv[u]);
                     const bool take = live && !stop && y < best;
                     best = take ? y : best;
@@ -747,10 +766,9 @@ __global__ __launch_bounds__(256) void orders_reduce_part(SetLevels lv, const in
 }
 
 // No plan known and no fill root yet for any b (a b whose fill does not run
-// keeps none).  A small search gets no bounds either: every band is whole, as
-// if an island could take every layer (and so every state's root is written).
-__global__ __launch_bounds__(256) void orders_clear_b(DevProblem P, int D, bool whole, unsigned long long *cut,
-                                                      double *tau, int32_t *ml, double *rootF, uint32_t *rootKey) {
+// keeps none).
+__global__ __launch_bounds__(256) void orders_clear_b(DevProblem P, unsigned long long *cut, double *tau,
+                                                      double *rootF, uint32_t *rootKey) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < P.nb) {
         cut[t] = 0x7FF0000000000000ull;
@@ -758,7 +776,6 @@ __global__ __launch_bounds__(256) void orders_clear_b(DevProblem P, int D, bool 
         rootF[t] = kInf;
         rootKey[t] = kNoKey;
     }
-    if (whole && t < P.nb * (D + 2) * P.K) ml[t] = (t / P.K) % (D + 2) <= D ? P.L : 0;
 }
 
 __global__ __launch_bounds__(256) void orders_reduce_final(const double *__restrict__ part_v,
@@ -874,7 +891,8 @@ __global__ __launch_bounds__(kOrderFinishThreads) void orders_finish(
 // ---------------------------------------------------------------------------
 // host-side sequencing
 // ---------------------------------------------------------------------------
-// One phase's levels for nrow b, those of the list; whole: every band is whole.
+// One phase's levels for nrow b, those of the list; whole: every band is whole,
+// and so every state's root is written.
 template <bool kFill>
 static void run_levels(const DevProblem &P, const SetLevels &lv, const OrdersWs &w, hipStream_t s, int nrow,
                        const BList &blist, bool whole) {
@@ -895,10 +913,24 @@ static void run_levels(const DevProblem &P, const SetLevels &lv, const OrdersWs 
         const dim3 grid((unsigned)(binom(P.K, d - 1) * nsplit), (unsigned)nrow);
         const double *prev = w.Vb[(d - 1) & 1];
         double *cur = w.Vb[d & 1];
-        orders_level<kLevelThreads, kFill>
-            <<<grid, dim3(kLevelThreads), sizeof(double) * kLevelLds, s>>>(
-                P, lv, d, nsplit, kLevelLds, w.masks, w.rank, w.T, w.X, prev, cur, w.root, bounds, w.ml, w.argF,
-                w.argG, blist);
+        auto go = [&](auto nt, auto rows, int lds_n, size_t lds_used) {
+            constexpr int NT = decltype(nt)::value;
+            orders_level<NT, kFill, decltype(rows)::value><<<grid, dim3(NT), sizeof(double) * lds_used, s>>>(
+                P, lv, d, nsplit, lds_n, w.masks, w.rank, w.T, w.X, prev, cur, w.root, bounds, w.ml, w.argF, w.argG,
+                blist);
+        };
+        if (whole) {  // the rows a block keeps at most: the set's, where two more fit, and its states'
+            const int fit = kWholeLds / (L + 1), kept = d < fit ? d - 1 : 0;
+            const int used = (kept + std::min((nk + nsplit - 1) / nsplit, fit - kept)) * (L + 1);
+            const auto nt = std::integral_constant<int, kWholeThreads>{};
+            if (kept)
+                go(nt, std::integral_constant<Rows, Rows::kWholeStaged>{}, kWholeLds, (size_t)used);
+            else
+                go(nt, std::integral_constant<Rows, Rows::kWhole>{}, kWholeLds, (size_t)used);
+        } else {
+            go(std::integral_constant<int, kBandThreads>{}, std::integral_constant<Rows, Rows::kBand>{}, kBandLds,
+               (size_t)kBandLds);
+        }
     }
 }
 
@@ -921,13 +953,11 @@ hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host,
     // where none is looked for, or none can win)
     const int nb = P.nb;
     const BList every{};
-    // a small search skips the bounds and fills every b: host and device round
-    // trips would cost more than they save
+    // a small search fills every b: host round trips would cost more than they save
     const bool small = (int64_t)nb * lv.total * (P.L + 1) < kPruneCells;
-    const int n_clear = nb * (lv.D + 2) * P.K;
-    orders_clear_b<<<dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, s>>>(P, lv.D, small, w.cut, w.tau, w.ml,
-                                                                                w.rootF, w.rootKey);
-    if (!small) {
+    const bool whole = small || P.K < kBandIslands;
+    orders_clear_b<<<dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s>>>(P, w.cut, w.tau, w.rootF, w.rootKey);
+    if (!whole) {
         orders_cutoff<<<dim3(kCutOrders, (unsigned)nb), dim3(kCutThreads), 0, s>>>(P, lv.D, w.T, w.X, w.fixed, w.cut);
         orders_bound<<<dim3(1), dim3(256), 0, s>>>(P, lv.D, w.cut, w.tau);
     }
@@ -935,14 +965,14 @@ hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host,
         const int64_t n = (int64_t)nb * (lv.D + 2) * P.K;
         orders_longest<<<dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s>>>(P, lv.D, w.T, bound, w.ml);
     };
-    if (!small) longest(w.tau);
-    run_levels<false>(P, lv, w, s, nb, every, small);
+    if (!whole) longest(w.tau);
+    run_levels<false>(P, lv, w, s, nb, every, whole);
     double *hv = host && host->dlim ? (double *)host->dlim : nullptr;  // nb pinned words, and their device view
     double *hv_dev = hv ? (double *)host->dlim_dev : nullptr;
     orders_reduce_part<false><<<dim3(kReduceChunks, (unsigned)nb), dim3(256), 0, s>>>(lv, w.masks, w.root, w.part_v,
                                                                                      w.part_k, every);
     orders_reduce_final<<<dim3((unsigned)nb), dim3(256), 0, s>>>(w.part_v, w.part_k, w.Pst, nullptr, hv_dev, every);
-    if (!small) longest(w.Pst);
+    if (!whole) longest(w.Pst);
     // the values of the nb words at `dev`, through the pinned words or a copy
     auto read_back = [&](const double *dev, double *out) -> hipError_t {
         hipError_t e = hv ? hipSuccess : hipMemcpyAsync(out, dev, sizeof(double) * nb, hipMemcpyDeviceToHost, s);
@@ -955,7 +985,7 @@ hipError_t launch_compose_orders(const DevProblem &P, const int64_t *bvals_host,
             BList list{};
             list.n = (int32_t)std::min<size_t>(kRunB, bl.size() - at);
             std::copy(bl.begin() + at, bl.begin() + at + list.n, list.b);
-            run_levels<true>(P, lv, w, s, list.n, list, small);
+            run_levels<true>(P, lv, w, s, list.n, list, whole);
             orders_reduce_part<true><<<dim3(kReduceChunks, (unsigned)list.n), dim3(256), 0, s>>>(
                 lv, w.masks, w.root, w.part_v, w.part_k, list);
             orders_reduce_final<<<dim3((unsigned)list.n), dim3(256), 0, s>>>(w.part_v, w.part_k, w.rootF, w.rootKey,

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 from oracle.oracle import Oracle  # noqa: E402
 from workloads import extended, load_instance, random_tiny  # noqa: E402
-from tests.inst_util import scaled, tiny_tight  # noqa: E402
+from tests.inst_util import instance, scaled, tiny_tight  # noqa: E402
 from tests.golden.make_golden import load as load_golden  # noqa: E402
 from tests.test_gpu_parity import plan_equal  # noqa: E402
 from tests.test_oracle_all_orders import _symmetric  # noqa: E402
@@ -138,6 +138,43 @@ def test_all_orders_bands(seed, L, K, memory, eps, tight):
     ost, oplan, _ = o.compose_all_orders(o.prune())
     surv, cost, dmax = _gpu(p)
     ws = p.compose_all_orders_workspace(int(surv.numel()))
+    for rep in range(2):
+        st, plan = p.tg_compose_pipeline_all_orders(surv, cost, dmax, workspace=ws)
+        assert st == (T.TG_ENOPLAN if ost != 0 else 0)
+        if ost == 0:
+            plan_equal(plan, oplan)
+
+
+def _many_b(K, L):
+    """More micro-batch sizes than one run of the fill covers (32)."""
+    layers = {"fwd_flops": [(7 * l % 5 + 1) * 10**12 for l in range(L)],
+              "dense_params": [10**7 * (l % 3) for l in range(L)], "act_stash_bytes": [10**6] * L,
+              "tp_comm_bytes": [10**6] * L, "out_act_bytes": [10**7] * L}
+    return instance(K=K, layers=layers, n_gpus=[4 + 3 * k for k in range(K)], peak=[(3 + k) * 1e13 for k in range(K)],
+                    hbm=40e9, intra=300e9, inter=25e9, B=720720, mb=(1, 2, 3, 5, 7, 11, 13), tp=(1, 2), zero=(0, 3))
+
+
+@pytest.mark.parametrize("name,make,bounded", [
+    # every b filled at once: rows staged at no level, at some, at all
+    ("unstaged", lambda: scaled(random_tiny(3011, L_range=(512, 512), K_range=(3, 3)), memory=99.0), False),
+    ("staged_some", lambda: scaled(random_tiny(3012, L_range=(306, 306), K_range=(5, 5)), memory=99.0), False),
+    ("staged_all", lambda: random_tiny(3013, L_range=(40, 40), K_range=(9, 9)), False),
+    ("eps", lambda: _banded(3014, 33, 7, 4.0, 1.0, False), False),
+    # rows without bands, the fill only for the b that can win
+    ("whole", lambda: _banded(3015, 118, 10, 40.0, 0.0, False), True),
+    ("whole_eps", lambda: _banded(3016, 60, 11, 40.0, 2.0, False), True),
+    ("whole_tight", lambda: _banded(3017, 57, 11, 2.0, 0.0, True), True),
+    ("many_b", lambda: _many_b(4, 7), False)])
+def test_all_orders_without_bands(name, make, bounded):
+    say("whole rows", name)
+    inst = make()
+    o, p = Oracle(inst), T.Problem(inst)
+    assert (p.n_b * p.K * 2 ** (p.K - 1) * (p.L + 1) >= 1 << 22) == bounded
+    assert name != "many_b" or p.n_b > 32
+    ost, oplan, _ = o.compose_all_orders(o.prune())
+    surv, cost, dmax = _gpu(p)
+    ws = p.compose_all_orders_workspace(int(surv.numel()))
+    ws.fill_(0xFF)
     for rep in range(2):
         st, plan = p.tg_compose_pipeline_all_orders(surv, cost, dmax, workspace=ws)
         assert st == (T.TG_ENOPLAN if ost != 0 else 0)
