@@ -2,7 +2,8 @@
 the class expansion, against the oracle's list: bitmaps just below and above
 the size from which a count pass runs (8192 words), rows that survive on every
 slice, a bitmap of one partial word, and capacities that cut the list inside a
-tile."""
+tile.  And tiles of every density, dealt
+output by output or walked word by word, with one and four words a thread."""
 import numpy as np
 import pytest
 
@@ -11,7 +12,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from oracle.oracle import Oracle  # noqa: E402
-from tests.inst_util import scaled  # noqa: E402
+from tests.inst_util import instance, scaled  # noqa: E402
 from workloads import load_instance, random_tiny  # noqa: E402
 
 if not torch.cuda.is_available():
@@ -46,3 +47,38 @@ def test_compaction(name, make):
         assert err.value.status == T.TG_ECAPACITY and err.value.required == len(want)
         got = buf.cpu().numpy()
         assert np.array_equal(got[:cap], want[:cap]) and (got[cap:] == -7).all()
+
+
+# one config a group, so that what fits survives: 3 rows an island, 30, 129 and
+# 2,052 words a row; 3,600 words (counted by each block), 46,440 (count pass) and
+# 1.05 million (four words a thread)
+@pytest.mark.parametrize("L,K", [(61, 40), (128, 120), (512, 171)])
+def test_compaction_densities(L, K):
+    print("case", L, K, flush=True)
+    one = {"fwd_flops": 10**11, "dense_params": 10**6, "act_stash_bytes": 10**6, "out_act_bytes": 10**5}
+    p = T.Problem(instance(K=K, L=L, layer=one, n_gpus=4, hbm=80e9, B=4, tp=(1,), mb=(1,), zero=(3,)))
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    rows = torch.arange(p.N, device="cuda") // p.NS
+    b = p.tg_enumerate_pairs(0, 1)  # the binding's device is up
+    assert b.shape == (1, 12)
+    cost = torch.ones(p.N, dtype=torch.float64, device="cuda")
+    ok = torch.zeros(p.n_configs, dtype=torch.bool)
+    for g in range(p.n_configs):
+        row = p.tg_enumerate_pairs(g * p.NS, 1)[0].tolist()
+        ok[g] = 4 % (row[5] * row[10]) == 0
+    ok = ok.cuda()[rows]
+    # stretches of every density, among them 8 bits a word and a little to either side
+    share = torch.tensor([0.0, 0.001, 0.05, 0.12, 0.125, 0.13, 0.5, 1.0], device="cuda")
+    for stretch in (64 * 256, 64 * 100 + 7):
+        pick = torch.randint(0, 8, (p.N // stretch + 1,), generator=gen, device="cuda")
+        want_bits = torch.rand(p.N, generator=gen, device="cuda") < share[pick[torch.arange(p.N, device="cuda") // stretch]]
+        dmax = (want_bits & ok).to(torch.uint8)
+        got = p.tg_prune(cost, dmax)
+        want = torch.nonzero(dmax).flatten()
+        assert torch.equal(got, want)
+        cap = int(want.numel()) * 2 // 3
+        buf = torch.full((cap + 64,), -7, dtype=torch.int64, device="cuda")
+        with pytest.raises(T.TangramError) as err:
+            p.tg_prune(cost, dmax, survivors=buf[:cap])
+        assert err.value.status == T.TG_ECAPACITY and err.value.required == want.numel()
+        assert torch.equal(buf[:cap], want[:cap]) and bool((buf[cap:] == -7).all())
