@@ -326,6 +326,21 @@ constexpr int kClassCfg = 4;       // configs per block, at most
 constexpr int kClassRun = 8256;    // candidates a block writes, about (1, 2 and 4 configs on 128, 80 and 48 layers)
 constexpr size_t kClassLds = 60 * 1024;
 constexpr int64_t kClassBlocks = 1024;  // blocks wanted before configs share one
+// Calls the general kernel is the better for.  A block's chain (coefficients,
+// classes, model, barrier, rows) is the same however little it writes: with less
+// than kClassFew candidates a block (three quarters more where the space is
+// extended), once there are more blocks than the machine holds at a time
+// (kClassWave), general -> class: 16 islands and 16 layers (136 slices) extended 61
+// -> 113 us, MoE 36 -> 40, 24 layers (300) extended 117 -> 124, MoE 46 -> 43, 28
+// layers (406) extended 160 -> 128.  And a short range leaves the chain bare: a
+// run of the general kernel's configs (32) is its time too, 129 layers and 12
+// configs 21.1 -> 22.3, 36 configs 25.0 -> 22.7; where NS is a multiple of 64 its
+// aligned rows hold out up to kClassAligned candidates (128 layers, 3.0e6 25.7 ->
+// 28.6, 13.9e6 44 -> 44, 25e6 62 -> 63, 96e6 195 -> 152).
+constexpr int64_t kClassFew = 900;
+constexpr int64_t kClassWave = 4096;
+constexpr int64_t kClassRange = 32;
+constexpr int64_t kClassAligned = 32 << 20;
 
 struct ClassTile {
     int32_t C;          // configs per block
@@ -469,18 +484,22 @@ __global__ __launch_bounds__(256) void score_class_kernel(DevProblem P, ClassTil
 
 // The class kernel's tile, or C = 0 where the general kernel is the better:
 // fewer than four slices a class (the model would be evaluated nearly as often
-// as there are candidates, by blocks that then wait for it), or more classes
-// than a block holds.
+// as there are candidates, by blocks that then wait for it), more classes than
+// a block holds, blocks that write too little, or short ranges.
 static ClassTile class_tile(const DevProblem &P, int64_t n_cfg) {
     ClassTile ct{};
-    if (P.NC > kMaxClasses || P.NC * 4 > P.NS) return ct;
+    if (P.NC > kMaxClasses || P.NC * 4 > P.NS || n_cfg < kClassRange) return ct;
+    if ((P.NS & 63) == 0 && n_cfg * P.NS < kClassAligned) return ct;
     ct.NC = (int32_t)P.NC;
     ct.pieces = (int32_t)((P.NS + kClassSlices - 1) / kClassSlices);
     ct.piece = (int32_t)((P.NS + ct.pieces - 1) / ct.pieces);
     const int64_t spread = n_cfg * ct.pieces / kClassBlocks;
     const int64_t fit = (int64_t)(kClassLds - 2 * (size_t)ct.piece) / (9 * P.NC);
     const int64_t most = std::min<int64_t>(std::min<int64_t>(kClassCfg, kClassRun / P.NS), fit);
-    ct.C = (int32_t)std::max<int64_t>(1, std::min(most, spread));
+    const int64_t C = std::max<int64_t>(1, std::min(most, spread));
+    const int64_t few = P.ext ? kClassFew + kClassFew * 3 / 4 : kClassFew;
+    if (C * ct.piece < few && (n_cfg + C - 1) / C * ct.pieces > kClassWave) return ct;
+    ct.C = (int32_t)C;
     return ct;
 }
 

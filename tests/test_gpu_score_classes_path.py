@@ -2,7 +2,8 @@
 CPU oracle bit for bit: layer patterns with few classes (equal layers, a
 repeating pair, a head and a tail), slice counts of every alignment, one
 configuration per block and several, rows cut into pieces, and score ranges
-that start and end inside rows, into buffers at odd byte offsets."""
+that start and end inside rows, into buffers at odd byte offsets: 31 configs'
+rows and fewer, which the general kernel takes, and more."""
 import numpy as np
 import pytest
 
@@ -59,7 +60,8 @@ def test_score_by_class(L, pattern, moe, ext):
     assert np.array_equal(dmax.cpu().numpy(), od)
     # parts of the range, into buffers 8 bytes (costs) and any byte (depths) off an aligned address
     for first, count, off in ((1, 2 * p.NS + 3, 1), (p.NS - 1, 2, 3), (p.NS // 2, 1, 15), (5 * p.NS, p.NS, 8),
-                              (p.N - p.NS - 5, p.NS + 5, 17)):
+                              (p.N - p.NS - 5, p.NS + 5, 17), (p.NS - 3, 33 * p.NS + 7, 1), (3, 40 * p.NS, 9),
+                              (p.NS // 3, 31 * p.NS, 2)):
         first, count = max(first, 0), min(count, p.N - max(first, 0))
         cbuf = torch.full((count + off + 16,), -1.0, dtype=torch.float64, device="cuda")
         dbuf = torch.full((count + off + 32,), 255, dtype=torch.uint8, device="cuda")
@@ -71,10 +73,13 @@ def test_score_by_class(L, pattern, moe, ext):
         assert (d[:off] == 255).all() and (d[off + count:] == 255).all()
 
 
-def test_score_by_class_shared_blocks():
+# at 24 layers a block of four configs writes 1,200 candidates; at 12 (312), with so
+# many configs, the general kernel takes over
+@pytest.mark.parametrize("L", [12, 24])
+def test_score_by_class_shared_blocks(L):
     """Enough configs that several share a block, in the expert variant."""
     inst = make_moe()
-    inst["layers"] = {f: v[:12] for f, v in inst["layers"].items()}
+    inst["layers"] = {f: v[:L] for f, v in inst["layers"].items()}
     p, o = T.Problem(inst), Oracle(inst)
     assert p.n_configs >= 2 * 4 * 1024 and 4 * p.NC <= p.NS
     oc, od = o.score()
@@ -82,3 +87,19 @@ def test_score_by_class_shared_blocks():
     assert np.array_equal(cost.cpu().numpy().view(np.uint64), oc.view(np.uint64))
     assert np.array_equal(dmax.cpu().numpy(), od)
     assert load_instance("moe")["islands"] == inst["islands"]
+
+
+@pytest.mark.parametrize("L,islands", [(63, 40), (127, 115), (128, 113)])
+def test_score_by_class_large(L, islands):
+    """Slice counts that are a multiple of 64, just past 32 Mi candidates (fewer
+    go to the general kernel), over the whole range and from odd starts."""
+    print("case", L, islands, flush=True)
+    inst = _instance(L, "equal", gpus=(8,) * islands)
+    p, o = T.Problem(inst), Oracle(inst)
+    assert (p.NS % 64 == 0) == (L in (127, 128))
+    assert p.N > 32 << 20 or L not in (127, 128)
+    oc, od = o.score()
+    for first, count in ((0, p.N), (5, p.N - 11)):
+        cost, dmax = p.tg_score_pairs(first, count)
+        assert np.array_equal(cost.cpu().numpy().view(np.uint64), oc[first:first + count].view(np.uint64))
+        assert np.array_equal(dmax.cpu().numpy(), od[first:first + count])
