@@ -552,7 +552,7 @@ __global__ void no_survivors(int64_t *total, int64_t *total_host) {
 // ballot, 64 words go out in one store.  Reading the classes per word from L2
 // and dividing per word took 380 us on the 128-layer instance (4.2M words);
 // this takes 73 us.
-constexpr int kExpandSlices = 8192 + 128;
+constexpr int kExpandSlices = (160 * 1024 / 8 - 256) / 4;  // eight blocks fill a CU; 256 bytes are the vote's
 constexpr int kExpandRows = 8;
 constexpr int kExpandWords = 8;  // words a wave builds at a time, their reads in flight together
 

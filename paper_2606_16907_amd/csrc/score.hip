@@ -318,13 +318,13 @@ __global__ __launch_bounds__(256) void score_kernel(DevProblem P, int64_t first,
 // plan search, general kernel -> this one: 128 layers 1868 -> 1673 us, 70B 109
 // -> 92, extended 70B 718 -> 643, MoE 73 -> 63, uneven 61 layers 129 -> 91, 8B
 // 12.4 -> 6.5 us; half and twice the run lost 13-30% and 5-15% on the 70B pair.
-// Slices are taken kClassSlices at a time (a wider model's rows are cut into
-// pieces, each written by a block of its own).
-constexpr int kClassSlices = 8192 + 128;  // a 128-layer model's slices (8256) are one piece
+// A wider model's rows are cut into pieces, each written by a block of its own.
+// LDS a block aims at: eight blocks of four waves fill a CU's 32 wave slots, 20
+// KB each.  A row's slices that leave more are cut in pieces.
+constexpr size_t kClassLds = 20 * 1024;
 constexpr int kMaxClasses = 512;
 constexpr int kClassCfg = 4;       // configs per block, at most
-constexpr int kClassRun = 8256;    // candidates a block writes, about (1, 2 and 4 configs on 128, 80 and 48 layers)
-constexpr size_t kClassLds = 60 * 1024;
+constexpr int kClassRun = 8192;    // candidates a block writes, about (1, 2 and 4 configs on 128, 80 and 48 layers)
 constexpr int64_t kClassBlocks = 1024;  // blocks wanted before configs share one
 // Calls the general kernel is the better for.  A block's chain (coefficients,
 // classes, model, barrier, rows) is the same however little it writes: with less
@@ -491,10 +491,12 @@ static ClassTile class_tile(const DevProblem &P, int64_t n_cfg) {
     if (P.NC > kMaxClasses || P.NC * 4 > P.NS || n_cfg < kClassRange) return ct;
     if ((P.NS & 63) == 0 && n_cfg * P.NS < kClassAligned) return ct;
     ct.NC = (int32_t)P.NC;
-    ct.pieces = (int32_t)((P.NS + kClassSlices - 1) / kClassSlices);
+    const int64_t fit1 = (int64_t)(kClassLds - sizeof(StagedCoef) * kClassCfg - 9 * (size_t)P.NC) / 2;
+    ct.pieces = (int32_t)((P.NS + fit1 - 1) / fit1);
     ct.piece = (int32_t)((P.NS + ct.pieces - 1) / ct.pieces);
     const int64_t spread = n_cfg * ct.pieces / kClassBlocks;
-    const int64_t fit = (int64_t)(kClassLds - 2 * (size_t)ct.piece) / (9 * P.NC);
+    const int64_t fit =
+        (int64_t)(kClassLds - sizeof(StagedCoef) * kClassCfg - 2 * (size_t)ct.piece) / (9 * P.NC);
     const int64_t most = std::min<int64_t>(std::min<int64_t>(kClassCfg, kClassRun / P.NS), fit);
     const int64_t C = std::max<int64_t>(1, std::min(most, spread));
     const int64_t few = P.ext ? kClassFew + kClassFew * 3 / 4 : kClassFew;

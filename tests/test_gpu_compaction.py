@@ -1,8 +1,8 @@
 """The survivor compaction's three ways of counting the bits before a tile, and
 the class expansion, against the oracle's list: bitmaps just below and above
 the size from which a count pass runs (8192 words), rows that survive on every
-slice, a bitmap of one partial word, and capacities that cut the list inside a
-tile.  And tiles of every density, dealt
+slice, a bitmap of one partial word, rows cut into several pieces, and
+capacities that cut the list inside a tile.  And tiles of every density, dealt
 output by output or walked word by word, with one and four words a thread."""
 import numpy as np
 import pytest
@@ -27,9 +27,22 @@ def _dense8b(L, memory=1.0):
     return scaled(inst, memory=memory)
 
 
+def _long(L, memory=1.0):
+    """Two kinds of layer on three islands, the last too small for any layer."""
+    layers = {"fwd_flops": [10**11 * (1 + l % 2) for l in range(L)], "dense_params": [10**6] * L,
+              "act_stash_bytes": [10**6 * (1 + l % 2) for l in range(L)], "tp_comm_bytes": [10**5] * L,
+              "out_act_bytes": [10**5] * L}
+    return instance(K=3, layers=layers, n_gpus=[4, 2, 3], peak=[1e14, 2e14, 1e14],
+                    hbm=[1e9 * memory, 2e9 * memory, 1e5], intra=300e9, inter=25e9, B=8, tp=(1, 2), mb=(1, 2),
+                    zero=(0, 3))
+
+
 CASES = [("w7680", lambda: _dense8b(38)), ("w8320", lambda: _dense8b(40)), ("dense", lambda: _dense8b(40, 1e6)),
          ("w30000", lambda: _dense8b(77)), ("one_word", lambda: random_tiny(5, L_range=(2, 2), K_range=(1, 1))),
-         ("none", lambda: _dense8b(24, 1e-6))]
+         ("none", lambda: _dense8b(24, 1e-6)),
+         # 5,050, 5,151, 16,110 and 45,150 slices a row: one piece of the expansion, two, four, nine
+         ("pieces100", lambda: _long(100)), ("pieces101", lambda: _long(101)), ("pieces179", lambda: _long(179)),
+         ("pieces300", lambda: _long(300, 0.3))]
 
 
 @pytest.mark.parametrize("name,make", CASES, ids=[n for n, _ in CASES])

@@ -89,10 +89,11 @@ def test_score_by_class_shared_blocks(L):
     assert load_instance("moe")["islands"] == inst["islands"]
 
 
-@pytest.mark.parametrize("L,islands", [(63, 40), (127, 115), (128, 113)])
+@pytest.mark.parametrize("L,islands", [(63, 40), (127, 115), (128, 113), (136, 3), (137, 3)])
 def test_score_by_class_large(L, islands):
     """Slice counts that are a multiple of 64, just past 32 Mi candidates (fewer
-    go to the general kernel), over the whole range and from odd starts."""
+    go to the general kernel), and the longest row of one piece and the next,
+    over the whole range and from odd starts."""
     print("case", L, islands, flush=True)
     inst = _instance(L, "equal", gpus=(8,) * islands)
     p, o = T.Problem(inst), Oracle(inst)
