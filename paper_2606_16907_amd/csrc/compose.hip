@@ -188,16 +188,22 @@ static int64_t n_rowev(const DevProblem &P) { return (int64_t)P.nb * P.L * (leve
 // Small problems are composed by one block per b with everything it reads
 // again and again in LDS: two level rows and the link times between every pair
 // of positions, for every cut.
-constexpr size_t kSmallLds = 60 * 1024;
 constexpr int64_t kSmallCells = 256 * 1024;  // entries of the stage table of every depth (2 MB)
 constexpr int kSmallMatches = 2048;          // entries the plan's groups may hold together
 constexpr int64_t kSmallList = 32768;
+// K^2 (L + 1): the continuation values and links one block reads for a level,
+// twice over.  Level launches share that over the machine and take over here:
+// one block against launches, 20 islands and 12 layers (5.2 K) 199 against 234 us,
+// 24 and 8 (5.2 K) 146 and 164, 28 and 8 (7.1 K) 163 and 173, 24 and 12 (7.5 K)
+// 213 and 194 with ten b, 32 and 8 (9.2 K) 183 and 166, 28 and 12 (10.2 K) 233
+// and 194, 32 and 12 (13.3 K) 262 and 221.
+constexpr int64_t kSmallReads = 7000;
 
-static size_t small_lds(const DevProblem &P) {
+static size_t small_lds(const DevProblem &P) {  // at most 48 KB (4 islands, 436 layers) by the rule below
     return sizeof(double) * (size_t)(P.L + 1) * (2 * P.K + P.K * (P.K - 1) / 2);
 }
 static bool small_problem(const DevProblem &P) {
-    return small_lds(P) <= kSmallLds && n_groups(P) * levels(P) <= kSmallCells &&
+    return (int64_t)P.K * P.K * (P.L + 1) <= kSmallReads && n_groups(P) * levels(P) <= kSmallCells &&
            (int64_t)P.max_members * levels(P) <= kSmallMatches;
 }
 
