@@ -39,6 +39,8 @@
 // clustering with a block per group, 0.57 ms in stages.
 #include <stdint.h>
 
+#include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "tg_device.h"
@@ -61,9 +63,24 @@ constexpr int kMergeThreads = 1024;
 // every pair of a group.  Any shares give the same islands.
 constexpr double kStageShare[] = {0.5, 0.125};
 constexpr int kStages = 3;
+// Below kStagedNodes nodes, and where every link is above the first threshold's
+// share of the fastest, one launch over whole groups does it: the stages took 272 us against 218 with 4 nodes, 326 against 300 with 8
+// (12 and 16 nodes behind levels of 4:1 361 against 374, 371 against 455), and
+// on flat fabrics 1559 against 1450 with 64 nodes, 2215 against 1926 with 128.
+constexpr int kStagedNodes = 16;
+constexpr int kOneSmall = 32;  // nodes up to which that launch has eight waves a group
 constexpr double kNoPair = -__builtin_huge_val();
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// The call's scalars, uploaded and read back as one.
+struct IslandState {
+    int32_t err;               // a merge loop overran its round bound (an internal error)
+    int32_t bad;               // first bad node_bw entry
+    unsigned long long least;  // slowest and fastest link between two nodes (bits of a double)
+    unsigned long long most;
+    unsigned long long lmax;   // fastest between nodes of one group
+};
 
 struct IslandWs {
     int32_t *gpus;      // [n]
@@ -84,14 +101,13 @@ struct IslandWs {
     int32_t *nxl;       // [n] that entry's number inside the group (-1: another group, or none)
     double *outv;       // [n] the node's bandwidth to it (-inf: none)
     int32_t *cl;        // [n] cluster (its smallest node) of each node
-    unsigned long long *lmax;  // [1] fastest link between nodes of one group (bits of a double)
     int32_t *uf;        // [n] union-find parents of a stage's components
     int32_t *comp;      // [n] component of each node
     int32_t *lc;        // [n] its number inside the component
     int32_t *cstart;    // [n + 1] component c's nodes are cnodes[cstart[c] .. cstart[c + 1])
     int32_t *cnodes;    // [n]
     int32_t *ncomp;     // [1]
-    int32_t *err;       // [2] a merge loop overran its round bound (an internal error); first bad node_bw entry
+    IslandState *state; // [1]
     int32_t *island_of; // [n]
     int32_t *out_k;     // [1]
     int32_t *isl_gpus;  // [n]
@@ -127,14 +143,13 @@ static IslandWs carve_islands(int64_t n, void *base) {
     w.nxl = (int32_t *)take(4 * n);
     w.outv = (double *)take(8 * n);
     w.cl = (int32_t *)take(4 * n);
-    w.lmax = (unsigned long long *)take(8);
     w.uf = (int32_t *)take(4 * n);
     w.comp = (int32_t *)take(4 * n);
     w.lc = (int32_t *)take(4 * n);
     w.cstart = (int32_t *)take(4 * (n + 1));
     w.cnodes = (int32_t *)take(4 * n);
     w.ncomp = (int32_t *)take(4);
-    w.err = (int32_t *)take(8);
+    w.state = (IslandState *)take(sizeof(IslandState));
     w.island_of = (int32_t *)take(4 * n);
     w.out_k = (int32_t *)take(4);
     w.isl_gpus = (int32_t *)take(4 * n);
@@ -148,10 +163,43 @@ size_t islands_ws_bytes(int n) { return carve_islands(n, nullptr).bytes; }
 
 // Node bandwidths must be finite and non-negative: the first entry that is not
 // into *bad (INT32_MAX if none; n^2 <= 2^24 entries).
-__global__ __launch_bounds__(256) void islands_check(int64_t nn, const double *__restrict__ e, int32_t *bad) {
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nn; t += (int64_t)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(256) void islands_check(int n, const double *__restrict__ e, IslandState *state) {
+    __shared__ double wlo[256 / kWave], whi[256 / kWave];
+    const uint32_t nn = (uint32_t)n * (uint32_t)n;  // at most 2^24
+    double lo = __builtin_huge_val(), hi = 0.0;
+    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < nn; t += gridDim.x * blockDim.x) {
         const double x = e[t];
-        if (!(x >= 0.0) || !(x < __builtin_huge_val())) atomicMin(bad, (int32_t)t);
+        if (!(x >= 0.0) || !(x < __builtin_huge_val())) {
+            atomicMin(&state->bad, (int32_t)t);
+        } else if (t % (uint32_t)(n + 1) != 0) {  // not a node's own entry
+            lo = fmin(lo, fabs(x));
+            hi = fmax(hi, fabs(x));
+        }
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, off));
+        hi = fmax(hi, __shfl_xor(hi, off));
+    }
+    if (wave_lane() == 0) {
+        wlo[threadIdx.x / kWave] = lo;
+        whi[threadIdx.x / kWave] = hi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < 256 / kWave; ++w) {
+            lo = fmin(lo, wlo[w]);
+            hi = fmax(hi, whi[w]);
+        }
+        // non-negative: the bits order like the values; a plain look first, so
+        // that few blocks update
+        const unsigned long long l = (unsigned long long)__double_as_longlong(lo),
+                                 h = (unsigned long long)__double_as_longlong(hi);
+        if (l < __hip_atomic_load(&state->least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMin(&state->least, l);
+        if (h > __hip_atomic_load(&state->most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&state->most, h);
     }
 }
 
@@ -977,6 +1025,9 @@ __global__ __launch_bounds__(256) void islands_inter(int n, const int32_t *__res
             atomicMin((unsigned long long *)&isl_e[(int64_t)a * K + k], m[k]);
 }
 
+template <int N>
+using Int = std::integral_constant<int, N>;
+
 hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double *e_host, double eps_c,
                                 double eps_m, double eps_i, void *ws, hipStream_t s, int32_t *island_of,
                                 tg_island *islands, double *inter_bw, int32_t *n_islands, int64_t *bad_bw) {
@@ -994,48 +1045,57 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
     hipError_t e = hipMemcpyAsync(w.gpus, hg.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w.val, hv.data(), 8 * 4 * (size_t)n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w.e, e_host, 8 * (size_t)n * n, hipMemcpyHostToDevice, s);
-    const int32_t none[2] = {0, INT32_MAX};
-    const unsigned long long no_link = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(w.err, none, sizeof(none), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(w.lmax, &no_link, sizeof(no_link), hipMemcpyHostToDevice, s);
+    IslandState state{0, INT32_MAX, 0x7FF0000000000000ull, 0, 0};
+    if (e == hipSuccess) e = hipMemcpyAsync(w.state, &state, sizeof(state), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     const int64_t nn = (int64_t)n * n;
-    islands_check<<<dim3((unsigned)std::min<int64_t>((nn + 255) / 256, 2048)), dim3(256), 0, s>>>(nn, w.e, w.err + 1);
-    int32_t bad = INT32_MAX;
-    e = hipMemcpyAsync(&bad, w.err + 1, 4, hipMemcpyDeviceToHost, s);
+    islands_check<<<dim3((unsigned)std::min<int64_t>((nn + 255) / 256, 2048)), dim3(256), 0, s>>>(n, w.e, w.state);
+    e = hipMemcpyAsync(&state, w.state, sizeof(state), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host staging arrays go away
     if (e != hipSuccess) return e;
-    *bad_bw = bad == INT32_MAX ? -1 : bad;
-    if (bad != INT32_MAX) return hipSuccess;
+    *bad_bw = state.bad == INT32_MAX ? -1 : state.bad;
+    if (state.bad != INT32_MAX) return hipSuccess;
+    double least, most;
+    std::memcpy(&least, &state.least, 8);
+    std::memcpy(&most, &state.most, 8);
+    const int first = n < kStagedNodes || least > kStageShare[0] * most ? kStages - 1 : 0;
     islands_groups<<<dim3(1), dim3(kGroupThreads), 0, s>>>(n, w.gpus, w.val, eps_c, eps_m, eps_i, w.grp, w.gstart,
                                                            w.gnodes, w.ngroups, w.lq, w.goff);
     const dim3 pairs((unsigned)((nn + 255) / 256));
     islands_link_init<<<pairs, dim3(256), 0, s>>>(n, w.e, w.grp, w.gstart, w.lq, w.goff, w.L, w.M, w.XT, w.inown,
-                                                  w.pos, w.cl, w.uf, w.lmax);
+                                                  w.pos, w.cl, w.uf, &w.state->lmax);
     islands_sort_rows<<<dim3((unsigned)n), dim3(1024), 0, s>>>(n, w.e, w.srt);
-    for (int st = 0; st < kStages; ++st) {
+    const unsigned long long *lmax = &w.state->lmax;
+    for (int st = first; st < kStages; ++st) {
         const bool last = st == kStages - 1;
         const double share = last ? 0.0 : kStageShare[st];
         StageComps comps{w.comp, w.lc, w.cstart, w.cnodes, w.ncomp};
         if (last) {
             comps = StageComps{w.grp, w.lq, w.gstart, w.gnodes, w.ngroups};
         } else {
-            islands_unite<<<pairs, dim3(256), 0, s>>>(n, share, w.lmax, w.e, w.grp, w.uf);
+            islands_unite<<<pairs, dim3(256), 0, s>>>(n, share, lmax, w.e, w.grp, w.uf);
             islands_components<<<dim3(1), dim3(kGroupThreads), 0, s>>>(n, w.uf, w.comp, w.lc, w.cstart, w.cnodes,
                                                                        w.ncomp);
         }
-        if (st > 0) {
+        if (st > first) {
             islands_stage_clear<<<pairs, dim3(256), 0, s>>>(n, w.grp, w.gstart, w.lq, w.goff, comps.of, w.cl, w.L,
                                                             w.XT);
             islands_stage_links<<<pairs, dim3(256), 0, s>>>(n, w.e, w.grp, w.gstart, w.lq, w.goff, comps.of, w.cl,
                                                             w.L, w.XT);
         }
-        islands_merge<kSmallThreads, 2, kSmallComp><<<dim3((unsigned)n), dim3(kSmallThreads), 0, s>>>(
-            n, share, w.lmax, w.e, w.srt, comps, w.grp, w.lq, w.gstart, w.goff, w.L, w.M, w.XT, w.inown, w.pos, w.nxl,
-            w.outv, w.cl, w.err);
-        islands_merge<kMergeThreads, kSmallComp + 1, kMaxNodes><<<dim3((unsigned)n), dim3(kMergeThreads), 0, s>>>(
-            n, share, w.lmax, w.e, w.srt, comps, w.grp, w.lq, w.gstart, w.goff, w.L, w.M, w.XT, w.inown, w.pos, w.nxl,
-            w.outv, w.cl, w.err);
+        auto merge = [&](auto threads, auto fewest, auto most_nodes) {
+            constexpr int NT = decltype(threads)::value;
+            islands_merge<NT, decltype(fewest)::value, decltype(most_nodes)::value>
+                <<<dim3((unsigned)n), dim3(NT), 0, s>>>(n, share, lmax, w.e, w.srt, comps, w.grp, w.lq, w.gstart,
+                                                        w.goff, w.L, w.M, w.XT, w.inown, w.pos, w.nxl, w.outv, w.cl,
+                                                        &w.state->err);
+        };
+        if (first == kStages - 1 && n > kOneSmall) {
+            merge(Int<kMergeThreads>{}, Int<2>{}, Int<kMaxNodes>{});
+        } else {
+            merge(Int<kSmallThreads>{}, Int<2>{}, Int<kSmallComp>{});
+            if (n > kSmallComp) merge(Int<kMergeThreads>{}, Int<kSmallComp + 1>{}, Int<kMaxNodes>{});
+        }
     }
     islands_number<<<dim3(1), dim3(1024), 0, s>>>(n, w.cl, w.gpus, w.val, w.island_of, w.out_k, w.isl_gpus,
                                                   w.isl_val);
@@ -1043,7 +1103,7 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
     if (e != hipSuccess) return e;
     int32_t K = 0, merr = 0;
     e = hipMemcpyAsync(&K, w.out_k, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&merr, w.err, 4, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&merr, &w.state->err, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
     if (merr) return hipErrorUnknown;

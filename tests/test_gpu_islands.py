@@ -157,3 +157,20 @@ def test_islands_one_link_speed(bw):
     e = [[0.0 if a == b else bw for b in range(70)] for a in range(70)]
     c = cluster([8] * 70, [100e12] * 70, e)
     same(T.build_islands(c), oracle_islands(c))
+
+
+# one launch over whole groups: fewer than 16 nodes (levels 4:1), or every link
+# above half the fastest; and just outside both
+@pytest.mark.parametrize("n", [2, 3, 15, 16, 17, 32, 33, 64, 65, 130])
+@pytest.mark.parametrize("fab", ["levels", "flat", "above_half", "half"])
+def test_islands_one_launch_or_stages(n, fab):
+    say("one launch", n, fab)
+    rng = np.random.default_rng([n, len(fab)])
+    u = np.arange(n)
+    e = {"levels": np.where(u[:, None] // 4 == u // 4, 400e9, np.where(u[:, None] // 12 == u // 12, 100e9, 25e9)),
+         "flat": np.full((n, n), 25e9) * rng.uniform(0.98, 1.02, (n, n)),
+         "above_half": np.where(u[:, None] // 4 == u // 4, 50e9, 25.001e9),
+         "half": np.where(u[:, None] // 4 == u // 4, 50e9, 25e9)}[fab].astype(float)
+    np.fill_diagonal(e, 0.0)
+    c = cluster([8] * n, [100e12 if v % 40 < 33 else 200e12 for v in range(n)], e.tolist())
+    same(T.build_islands(c), oracle_islands(c))
