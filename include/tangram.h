@@ -261,6 +261,10 @@ tg_status tg_score_pairs(const tg_problem *p, int64_t first, int64_t count, doub
  * candidate survives iff its micro-batch b divides the global batch, its
  * d_max >= 1, and it has the least key (cost, -d_max, idx) among the members
  * of its group (same slice, island and b) whose d_max reaches its own d_max.
+ * Scores of this library are numbers and their depths at most K; in arrays of
+ * the caller's, a deeper d_max is compared like any other, and a candidate
+ * whose cost is NaN is compared with none: it survives if its b divides the
+ * global batch and its d_max >= 1, and removes no other.
  * *n_survivors (host) receives the count; if it exceeds `capacity`, nothing
  * past capacity is written and TG_ECAPACITY is returned.  d_ws: caller
  * workspace of at least tg_prune_workspace_bytes(p) bytes (TG_ENOMEM if
@@ -324,9 +328,10 @@ tg_status tg_compose_pipeline_classes(const tg_problem *p, const int64_t *d_surv
  * ascending indices of compatible candidates (anything else is TG_EINVAL;
  * entries with d_max 0 are ignored) and must contain the whole surviving set:
  * tg_prune's output, or any superset of it drawn from the compatible
- * candidates, which composes to the same plan.  island_order (host, a permutation of 0..K-1) fixes the
- * order in which islands may appear from pipeline front to back; islands may
- * be skipped.  For each b the plan minimises the bottleneck P = max of stage
+ * candidates, which composes to the same plan.  island_order (host, a
+ * permutation of 0..K-1, read before the call returns) fixes the order in
+ * which islands may appear from pipeline front to back; islands may be
+ * skipped.  For each b the plan minimises the bottleneck P = max of stage
  * costs and link times, then the fill F = f1 + (x1 + (f2 + ... + fS)) among
  * plans with that bottleneck; across b it minimises T = (m - 1) P + F, ties
  * to the smaller b.  Ties inside a b go to the earliest first island, then
@@ -337,10 +342,12 @@ tg_status tg_compose_pipeline_classes(const tg_problem *p, const int64_t *d_surv
  * store the fill depth limits and the result into the handle's read-back
  * words (those of tg_prune); with more than 8 levels (min(K, L)) the host
  * also waits once part-way, for the depth limits, while the first fill
- * levels run.  A call that finds the words in use by another call on the
- * same handle copies the result back instead, and reads the depth limits by
- * a stream synchronisation when there are 64 levels or more, otherwise
- * launching every fill level.
+ * levels run.  Small problems (a few islands or layers and a short list)
+ * run in four launches that store the result alone and never wait part-way.
+ * A call that finds the words in use by another call on the same handle
+ * copies the result back instead, and reads the depth limits by a stream
+ * synchronisation when there are 64 levels or more, otherwise launching every
+ * fill level.
  */
 size_t tg_compose_workspace_bytes(const tg_problem *p, int64_t n_survivors);
 tg_status tg_compose_pipeline(const tg_problem *p, const int64_t *d_survivors, int64_t n_survivors,
@@ -390,7 +397,14 @@ tg_status tg_compose_pipeline_relaxed(const tg_problem *p, const int64_t *d_surv
  * requirements, scores and errors as for tg_compose_pipeline (no island
  * order).  d_ws: at least tg_compose_all_orders_workspace_bytes(p,
  * n_survivors) bytes, about nb K 2^(K-1) (3L + 8) bytes for the argmin and
- * root tables plus two level buffers.  Synchronises the stream once.
+ * root tables plus two level buffers.  Synchronises the stream at its end;
+ * where the tables are large (4 Mi cells and more) the host also waits after
+ * the bottleneck phase, to fill first the most promising b, and after that
+ * fill, to leave out every b that can no longer win.  The kernels store these
+ * values and the result into the handle's read-back words (those of tg_prune:
+ * allocated at its first prune or composition call, held for the length of
+ * this one); a call that finds them in use by another call on the same handle
+ * copies the values and the result back instead.
  */
 size_t tg_compose_all_orders_workspace_bytes(const tg_problem *p, int64_t n_survivors);
 tg_status tg_compose_pipeline_all_orders(const tg_problem *p, const int64_t *d_survivors, int64_t n_survivors,

@@ -58,15 +58,18 @@ constexpr int kSmallComp = 64;
 constexpr int kSmallThreads = 512;
 constexpr int kMergeThreads = 1024;
 // The stages' thresholds, as shares of the fastest link between nodes of one
-// group: fabric levels differ by more than 2, so the first separates the
+// group.  Where fabric levels differ by more than 2, the first separates the
 // fastest level (leaves) and the second the next (pods); the last stage takes
-// every pair of a group.  Any shares give the same islands.
+// every pair of a group.  Levels of exactly 2:1 fall together two by two, which
+// costs a part of the gain: 1024 nodes 7.8 ms in one stage and 2.2 in three, with
+// levels of 4:1 or 8:1 7.8 and 1.6.  Any shares give the same islands.
 constexpr double kStageShare[] = {0.5, 0.125};
 constexpr int kStages = 3;
 // Below kStagedNodes nodes, and where every link is above the first threshold's
-// share of the fastest, one launch over whole groups does it: the stages took 272 us against 218 with 4 nodes, 326 against 300 with 8
-// (12 and 16 nodes behind levels of 4:1 361 against 374, 371 against 455), and
-// on flat fabrics 1559 against 1450 with 64 nodes, 2215 against 1926 with 128.
+// share of the fastest, one launch over whole groups does it: the stages took
+// 272 us against 218 with 4 nodes, 326 against 300 with 8 (12 and 16 nodes behind
+// levels of 4:1 361 against 374, 371 against 455), and on flat fabrics 1559
+// against 1450 with 64 nodes, 2215 against 1926 with 128.
 constexpr int kStagedNodes = 16;
 constexpr int kOneSmall = 32;  // nodes up to which that launch has eight waves a group
 constexpr double kNoPair = -__builtin_huge_val();

@@ -3,29 +3,29 @@
 //
 // Group G = (slice s, island k, micro-batch b).  A member p survives iff b
 // divides the global batch, (s, k) passes imbalance pruning when it is on,
-// d_max_p >= 1 and p has the least key
-// (cost, -d_max, idx) among members whose d_max reaches d_max_p.  Equivalently
-// the survivors are rep(G, d) for d = 1..K, the least-key member fitting at
-// depth d: a member survives iff no other member at least as deep has a
-// smaller key.
+// d_max_p >= 1 and p has the least key (cost, -d_max, idx) among members whose
+// d_max reaches d_max_p.  Equivalently the survivors are rep(G, d) for d = 1..K,
+// the least-key member fitting at depth d: a member survives iff no other member
+// at least as deep has a smaller key.
 //
 // Frontier: a wave owns 64 consecutive slices of one (island, b) group list;
 // every lane walks the same members (a scalar loop) in ascending idx, reading
 // one coalesced 64-byte row of depths per member and, where the depth can
 // still matter, one 512-byte row of costs, eight members in flight.  On
-// clusters of up to 32 islands each lane keeps the least cost of every depth in
-// LDS (frontier_buckets); on wider ones each lane keeps the staircase of its group in registers (up to kStair entries of
-// strictly increasing depth and key): a member is dropped when an entry at
-// least as deep costs no more; otherwise it removes the entries it beats and
-// takes a slot.  When the slots are full the shallowest of them and the
-// newcomer leaves and the pass ignores every member at or above its depth
-// from then on: survival of a member depends only on members at least as
-// deep, so the entries kept are exactly the survivors deeper than that depth.
-// A further pass (rare: more than kStair survivors in one group) settles the
-// shallower ones, with the least kept entry as a cost cap.  Each pass
-// records its entries in an LDS bit mask per member (lane bit = slice), 512
-// members at a time, written as whole 64-bit words of a bitmap with one row
-// per compatible config (a later pass ORs into the words it wrote).
+// clusters of up to 32 islands with enough members a group each lane keeps the
+// least cost of every depth in LDS (frontier_buckets); elsewhere each lane keeps
+// the staircase of its group in registers (up to kStair entries of strictly
+// increasing depth and key): a member is dropped when an entry at least as deep
+// costs no more; otherwise it removes the entries it beats and takes a slot.
+// When the slots are full the shallowest of them and the newcomer leaves and the
+// pass ignores every member at or above its depth from then on: survival of a
+// member depends only on members at least as deep, so the entries kept are
+// exactly the survivors deeper than that depth.  A further pass (rare: more than
+// kStair survivors in one group) settles the shallower ones, with the least kept
+// entry as a cost cap.  Each pass records its entries in an LDS bit mask per
+// member (lane bit = slice), 512 members at a time, written as whole 64-bit words
+// of a bitmap with one row per compatible config (a later pass ORs into the words
+// it wrote).
 // Compaction: popcounts per tile of words, then each block adds up the counts
 // of the tiles before its own (scanned first where there are many tiles) and
 // writes its candidate indices in ascending order, dealt one by one in sparse
@@ -40,7 +40,7 @@ namespace tg {
 
 constexpr int kFrontWaves = 4;
 // Staircase entries a lane keeps per pass: 4 for groups of up to 64 members
-// (60 VGPRs, 8 waves per SIMD), 8 above (82 VGPRs, 5 waves per SIMD), where
+// (64 VGPRs, 8 waves per SIMD), 8 above (86 VGPRs, 5 waves per SIMD), where
 // staircases grow longer and a second pass would cost more than occupancy.
 constexpr int kSmallGroup = 64;
 constexpr int kMaskChunk = 512;   // members per LDS mask round when a pass is recorded
@@ -259,11 +259,14 @@ __global__ __launch_bounds__(256) void frontier_kernel(DevProblem P, const doubl
 // this way 394); the register staircase compares and moves up to eight entries
 // (about 160 instructions a member; it was issue-bound at under 2 TB/s on the
 // extended MoE instance).  Afterwards a sweep from the deepest bucket up keeps
-// those cheaper than everything deeper: the survivors, whatever their number, in one
-// pass.  Bound by the depth-then-cost loads of kBucketBatch members in flight
-// (the next batch's depths load with this batch's costs) at the 7 to 15 waves a
-// CU that 21 KB (32 islands) to 11 KB (16) leave; a wider cluster keeps the
-// registers.  Groups go largest first, so the last blocks are short ones.
+// those cheaper than everything deeper: the survivors, whatever their number, in
+// one pass.  Bound by the depth-then-cost loads of kBucketBatch members in flight
+// (the next batch's depths load with this batch's costs) at the 7 to 13 waves a
+// CU that 22 KB a wave (32 islands) to 12 KB (16) leave at most.  A wider cluster
+// keeps the registers: with 80 layers of the MoE model a prune takes 299, 316 and
+// 342 us on 36, 40 and 48 islands with the staircase and 329, 414 and 580 with
+// buckets (33 islands: 283 and 271), though models too short to fill the card
+// would gain (8 layers on 40 islands 103 and 67).  Groups go largest first, so the last blocks are short ones.
 // This library's depths are at most K; a wave that meets a deeper one in a
 // caller's arrays starts over with the staircase, which has no such limit (the
 // LDS bounds the waves a CU holds, so its registers are free here).

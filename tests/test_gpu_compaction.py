@@ -72,8 +72,6 @@ def test_compaction_densities(L, K):
     p = T.Problem(instance(K=K, L=L, layer=one, n_gpus=4, hbm=80e9, B=4, tp=(1,), mb=(1,), zero=(3,)))
     gen = torch.Generator(device="cuda").manual_seed(L)
     rows = torch.arange(p.N, device="cuda") // p.NS
-    b = p.tg_enumerate_pairs(0, 1)  # the binding's device is up
-    assert b.shape == (1, 12)
     cost = torch.ones(p.N, dtype=torch.float64, device="cuda")
     ok = torch.zeros(p.n_configs, dtype=torch.bool)
     for g in range(p.n_configs):
@@ -84,7 +82,8 @@ def test_compaction_densities(L, K):
     share = torch.tensor([0.0, 0.001, 0.05, 0.12, 0.125, 0.13, 0.5, 1.0], device="cuda")
     for stretch in (64 * 256, 64 * 100 + 7):
         pick = torch.randint(0, 8, (p.N // stretch + 1,), generator=gen, device="cuda")
-        want_bits = torch.rand(p.N, generator=gen, device="cuda") < share[pick[torch.arange(p.N, device="cuda") // stretch]]
+        odds = share[pick[torch.arange(p.N, device="cuda") // stretch]]
+        want_bits = torch.rand(p.N, generator=gen, device="cuda") < odds
         dmax = (want_bits & ok).to(torch.uint8)
         got = p.tg_prune(cost, dmax)
         want = torch.nonzero(dmax).flatten()
