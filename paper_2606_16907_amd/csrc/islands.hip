@@ -57,12 +57,12 @@ constexpr int kGroupThreads = 1024;
 constexpr int kSmallComp = 64;
 constexpr int kSmallThreads = 512;
 constexpr int kMergeThreads = 1024;
-// The stages' thresholds, as shares of the fastest link between nodes of one
-// group.  Where fabric levels differ by more than 2, the first separates the
-// fastest level (leaves) and the second the next (pods); the last stage takes
-// every pair of a group.  Levels of exactly 2:1 fall together two by two, which
-// costs a part of the gain: 1024 nodes 7.8 ms in one stage and 2.2 in three, with
-// levels of 4:1 or 8:1 7.8 and 1.6.  Any shares give the same islands.
+// The stages' thresholds, as shares of the fastest link between two nodes.
+// Where fabric levels differ by more than 2, the first separates the fastest
+// level (leaves) and the second the next (pods); the last stage takes every pair
+// of a group.  Levels of exactly 2:1 fall together two by two, which costs a part
+// of the gain: 1024 nodes 7.8 ms in one stage and 2.2 in three, with levels of 4:1
+// or 8:1 7.8 and 1.6.  Any shares give the same islands.
 constexpr double kStageShare[] = {0.5, 0.125};
 constexpr int kStages = 3;
 // Below kStagedNodes nodes, and where every link is above the first threshold's
@@ -82,7 +82,6 @@ struct IslandState {
     int32_t bad;               // first bad node_bw entry
     unsigned long long least;  // slowest and fastest link between two nodes (bits of a double)
     unsigned long long most;
-    unsigned long long lmax;   // fastest between nodes of one group
 };
 
 struct IslandWs {
@@ -170,6 +169,7 @@ __global__ __launch_bounds__(256) void islands_check(int n, const double *__rest
     __shared__ double wlo[256 / kWave], whi[256 / kWave];
     const uint32_t nn = (uint32_t)n * (uint32_t)n;  // at most 2^24
     double lo = __builtin_huge_val(), hi = 0.0;
+#pragma unroll 4
     for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < nn; t += gridDim.x * blockDim.x) {
         const double x = e[t];
         if (!(x >= 0.0) || !(x < __builtin_huge_val())) {
@@ -378,49 +378,29 @@ __global__ __launch_bounds__(256) void islands_link_init(int n, const double *__
                                                          const int32_t *__restrict__ lq,
                                                          const int64_t *__restrict__ goff, double *L, uint8_t *M,
                                                          double *XT, double *inown, int32_t *pos, int32_t *cl,
-                                                         int32_t *uf, unsigned long long *lmax) {
+                                                         int32_t *uf) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    // the block's fastest link between nodes of one group, reduced per wave, then
-    // one update a block
-    __shared__ double wmax[256 / kWave];
-    double fastest = 0.0;
-    auto link = [&]() {
-        if (t >= (int64_t)n * n) return;
-        const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);
-        if (v == 0) {
-            cl[u] = u;
-            inown[u] = __builtin_huge_val();
-            pos[u] = 0;
-            uf[u] = u;
-        }
-        const int g = grp[u];
-        if (grp[v] != g) return;
-        const int64_t nm = gstart[g + 1] - gstart[g];
-        const int64_t qu = lq[u], qv = lq[v], base = goff[g];
-        double l = kNoPair, x = __builtin_huge_val();
-        if (u != v) {
-            x = e[t];
-            const double y = e[(int64_t)v * n + u];
-            l = x < y ? x : y;
-        }
-        L[base + qu * nm + qv] = l;
-        M[base + qu * nm + qv] = 0;
-        XT[base + qv * nm + qu] = x;
-        if (u != v) fastest = l == 0.0 ? 0.0 : l;
-    };
-    link();
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) fastest = fmax(fastest, __shfl_xor(fastest, off));
-    if (wave_lane() == 0) wmax[threadIdx.x / kWave] = fastest;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 1; w < 256 / kWave; ++w) fastest = fmax(fastest, wmax[w]);
-        // links are non-negative: their bits order like the values; a plain
-        // look first, so that few blocks update
-        const unsigned long long bits = (unsigned long long)__double_as_longlong(fastest);
-        if (bits > __hip_atomic_load(lmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(lmax, bits);
+    if (t >= (int64_t)n * n) return;
+    const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);
+    if (v == 0) {
+        cl[u] = u;
+        inown[u] = __builtin_huge_val();
+        pos[u] = 0;
+        uf[u] = u;
     }
+    const int g = grp[u];
+    if (grp[v] != g) return;
+    const int64_t nm = gstart[g + 1] - gstart[g];
+    const int64_t qu = lq[u], qv = lq[v], base = goff[g];
+    double l = kNoPair, x = __builtin_huge_val();
+    if (u != v) {
+        x = e[t];
+        const double y = e[(int64_t)v * n + u];
+        l = x < y ? x : y;
+    }
+    L[base + qu * nm + qv] = l;
+    M[base + qu * nm + qv] = 0;
+    XT[base + qv * nm + qu] = x;
 }
 
 // ---------------------------------------------------------------------------
@@ -439,14 +419,12 @@ __device__ inline int uf_find(int32_t *uf, int u) {
 // Joins the nodes of every pair of a group linked at least as fast as the
 // stage's threshold.  Parents decrease, so each retry works on a smaller root:
 // the loop ends.
-__global__ __launch_bounds__(256) void islands_unite(int n, double share, const unsigned long long *__restrict__ lmax,
-                                                     const double *__restrict__ e, const int32_t *__restrict__ grp,
-                                                     int32_t *uf) {
+__global__ __launch_bounds__(256) void islands_unite(int n, double tau, const double *__restrict__ e,
+                                                     const int32_t *__restrict__ grp, int32_t *uf) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)n * n) return;
     const int u = (int)(t / n), v = (int)(t - (int64_t)u * n);
     if (u >= v || grp[u] != grp[v]) return;
-    const double tau = share * __longlong_as_double((long long)*lmax);
     if (!(e[t] >= tau) || !(e[(int64_t)v * n + u] >= tau)) return;
     int a = uf_find(uf, u), b = uf_find(uf, v);
     while (a != b) {
@@ -690,10 +668,10 @@ struct StageComps {
 // leave).  grp, lq: the component and the number inside it of each node.
 template <int kMergeThreads, int kMinNodes, int kNodes>
 __global__ __launch_bounds__(kMergeThreads) void islands_merge(
-    int n, double share, const unsigned long long *__restrict__ lmax, const double *__restrict__ e,
-    const int32_t *__restrict__ srt, StageComps comps, const int32_t *__restrict__ ggrp,
-    const int32_t *__restrict__ glq, const int32_t *__restrict__ gstart, const int64_t *__restrict__ goff, double *Lg,
-    uint8_t *Mg, double *XTg, double *inown, int32_t *pos, int32_t *nxl, double *outv, int32_t *cl, int32_t *err) {
+    int n, double tau, const double *__restrict__ e, const int32_t *__restrict__ srt, StageComps comps,
+    const int32_t *__restrict__ ggrp, const int32_t *__restrict__ glq, const int32_t *__restrict__ gstart,
+    const int64_t *__restrict__ goff, double *Lg, uint8_t *Mg, double *XTg, double *inown, int32_t *pos,
+    int32_t *nxl, double *outv, int32_t *cl, int32_t *err) {
     constexpr int kMergeWaves = kMergeThreads / kWave;
     __shared__ MergeLds<kNodes, kMergeWaves> S;
     __shared__ int32_t scan_lds[kMergeWaves + 1];
@@ -705,7 +683,6 @@ __global__ __launch_bounds__(kMergeThreads) void islands_merge(
     const int gg0 = ggrp[comps.nodes[c0]];
     const MergeMat A{Lg + goff[gg0], Mg + goff[gg0], XTg + goff[gg0], gstart[gg0 + 1] - gstart[gg0]};
     auto at = [&](int c, int v) { return (int64_t)S.mq[c] * A.nm + S.mq[v]; };  // entry (c, v) of a matrix
-    const double tau = share > 0.0 ? share * __longlong_as_double((long long)*lmax) : kNoPair;
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     int32_t *cur = (int32_t *)S.rb;  // scratch until the rows are set
     for (int q = threadIdx.x; q < nm; q += kMergeThreads) {
@@ -1048,11 +1025,13 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
     hipError_t e = hipMemcpyAsync(w.gpus, hg.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w.val, hv.data(), 8 * 4 * (size_t)n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w.e, e_host, 8 * (size_t)n * n, hipMemcpyHostToDevice, s);
-    IslandState state{0, INT32_MAX, 0x7FF0000000000000ull, 0, 0};
+    IslandState state{0, INT32_MAX, 0x7FF0000000000000ull, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(w.state, &state, sizeof(state), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     const int64_t nn = (int64_t)n * n;
-    islands_check<<<dim3((unsigned)std::min<int64_t>((nn + 255) / 256, 2048)), dim3(256), 0, s>>>(n, w.e, w.state);
+    // a block's two updates of the state go one after the other: 2048 blocks took
+    // 22 us over 1024 nodes
+    islands_check<<<dim3((unsigned)std::min<int64_t>((nn + 255) / 256, 256)), dim3(256), 0, s>>>(n, w.e, w.state);
     e = hipMemcpyAsync(&state, w.state, sizeof(state), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host staging arrays go away
     if (e != hipSuccess) return e;
@@ -1066,17 +1045,16 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
                                                            w.gnodes, w.ngroups, w.lq, w.goff);
     const dim3 pairs((unsigned)((nn + 255) / 256));
     islands_link_init<<<pairs, dim3(256), 0, s>>>(n, w.e, w.grp, w.gstart, w.lq, w.goff, w.L, w.M, w.XT, w.inown,
-                                                  w.pos, w.cl, w.uf, &w.state->lmax);
+                                                  w.pos, w.cl, w.uf);
     islands_sort_rows<<<dim3((unsigned)n), dim3(1024), 0, s>>>(n, w.e, w.srt);
-    const unsigned long long *lmax = &w.state->lmax;
     for (int st = first; st < kStages; ++st) {
         const bool last = st == kStages - 1;
-        const double share = last ? 0.0 : kStageShare[st];
+        const double tau = last ? kNoPair : kStageShare[st] * most;
         StageComps comps{w.comp, w.lc, w.cstart, w.cnodes, w.ncomp};
         if (last) {
             comps = StageComps{w.grp, w.lq, w.gstart, w.gnodes, w.ngroups};
         } else {
-            islands_unite<<<pairs, dim3(256), 0, s>>>(n, share, lmax, w.e, w.grp, w.uf);
+            islands_unite<<<pairs, dim3(256), 0, s>>>(n, tau, w.e, w.grp, w.uf);
             islands_components<<<dim3(1), dim3(kGroupThreads), 0, s>>>(n, w.uf, w.comp, w.lc, w.cstart, w.cnodes,
                                                                        w.ncomp);
         }
@@ -1089,8 +1067,8 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
         auto merge = [&](auto threads, auto fewest, auto most_nodes) {
             constexpr int NT = decltype(threads)::value;
             islands_merge<NT, decltype(fewest)::value, decltype(most_nodes)::value>
-                <<<dim3((unsigned)n), dim3(NT), 0, s>>>(n, share, lmax, w.e, w.srt, comps, w.grp, w.lq, w.gstart,
-                                                        w.goff, w.L, w.M, w.XT, w.inown, w.pos, w.nxl, w.outv, w.cl,
+                <<<dim3((unsigned)n), dim3(NT), 0, s>>>(n, tau, w.e, w.srt, comps, w.grp, w.lq, w.gstart, w.goff, w.L,
+                                                        w.M, w.XT, w.inown, w.pos, w.nxl, w.outv, w.cl,
                                                         &w.state->err);
         };
         if (first == kStages - 1 && n > kOneSmall) {
