@@ -169,14 +169,21 @@ __global__ __launch_bounds__(256) void islands_check(int n, const double *__rest
     __shared__ double wlo[256 / kWave], whi[256 / kWave];
     const uint32_t nn = (uint32_t)n * (uint32_t)n;  // at most 2^24
     double lo = __builtin_huge_val(), hi = 0.0;
-#pragma unroll 4
-    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < nn; t += gridDim.x * blockDim.x) {
-        const double x = e[t];
-        if (!(x >= 0.0) || !(x < __builtin_huge_val())) {
-            atomicMin(&state->bad, (int32_t)t);
-        } else if (t % (uint32_t)(n + 1) != 0) {  // not a node's own entry
-            lo = fmin(lo, fabs(x));
-            hi = fmax(hi, fabs(x));
+    const uint32_t step = gridDim.x * blockDim.x;
+    constexpr int kAhead = 8;  // loads in flight
+    for (uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x; t0 < nn; t0 += kAhead * step) {
+        double x[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) x[k] = e[min(t0 + k * step, nn - 1)];  // the last entry is a node's own
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const uint32_t t = min(t0 + k * step, nn - 1);
+            if (!(x[k] >= 0.0) || !(x[k] < __builtin_huge_val())) {
+                atomicMin(&state->bad, (int32_t)t);
+            } else if (t % (uint32_t)(n + 1) != 0) {  // not a node's own entry
+                lo = fmin(lo, fabs(x[k]));
+                hi = fmax(hi, fabs(x[k]));
+            }
         }
     }
 #pragma unroll
