@@ -65,13 +65,19 @@ constexpr int kMergeThreads = 1024;
 // or 8:1 7.8 and 1.6.  Any shares give the same islands.
 constexpr double kStageShare[] = {0.5, 0.125};
 constexpr int kStages = 3;
-// Below kStagedNodes nodes, and where every link is above the first threshold's
-// share of the fastest, one launch over whole groups does it: the stages took
-// 272 us against 218 with 4 nodes, 326 against 300 with 8 (12 and 16 nodes behind
-// levels of 4:1 361 against 374, 371 against 455), and on flat fabrics 1559
-// against 1450 with 64 nodes, 2215 against 1926 with 128.
-constexpr int kStagedNodes = 16;
-constexpr int kOneSmall = 32;  // nodes up to which that launch has eight waves a group
+// The stages cost two more rounds of launches, and a pair of clusters that waits
+// for a slower link is looked for again.  One launch over whole groups it is
+// where the largest group has fewer than kStagedNodes nodes, or kStagedOdd where
+// links were measured one by one (most differ from their neighbour, and most
+// unions fail Eq. 3), and where every link is above the first threshold's share of
+// the fastest.  Stages against one launch: groups of 4 nodes 272 and 218 us, 8 326
+// and 300, 12 and 16 behind levels of 4:1 361 and 374, 371 and 455; flat fabrics of
+// 64 nodes 1559 and 1450, of 128 2215 and 1926; links measured one by one, 100
+// nodes of six GPU types 911 and 720, 64 nodes of two types 789 and 943.  The last
+// stage takes all its groups in one launch of sixteen waves: two launches, one
+// after the other, took 2046 us on 197 nodes of four types, one 1480.
+constexpr int kStagedNodes = 16, kStagedOdd = 48;
+constexpr int kOneSmall = 32;  // nodes of a group up to which that launch has eight waves
 constexpr double kNoPair = -__builtin_huge_val();
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -80,6 +86,8 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct IslandState {
     int32_t err;               // a merge loop overran its round bound (an internal error)
     int32_t bad;               // first bad node_bw entry
+    int32_t group;             // nodes of the largest group
+    int32_t same;              // entries of the bandwidths equal to their right neighbour
     unsigned long long least;  // slowest and fastest link between two nodes (bits of a double)
     unsigned long long most;
 };
@@ -165,24 +173,31 @@ size_t islands_ws_bytes(int n) { return carve_islands(n, nullptr).bytes; }
 
 // Node bandwidths must be finite and non-negative: the first entry that is not
 // into *bad (INT32_MAX if none; n^2 <= 2^24 entries).
+// The first entry that is no bandwidth, the least and the greatest link, and how
+// many entries equal their right neighbour (a wave's 64 entries have 63 pairs).
 __global__ __launch_bounds__(256) void islands_check(int n, const double *__restrict__ e, IslandState *state) {
     __shared__ double wlo[256 / kWave], whi[256 / kWave];
+    __shared__ int32_t wsame[256 / kWave];
     const uint32_t nn = (uint32_t)n * (uint32_t)n;  // at most 2^24
     double lo = __builtin_huge_val(), hi = 0.0;
+    int32_t same = 0;
     const uint32_t step = gridDim.x * blockDim.x;
     constexpr int kAhead = 8;  // loads in flight
-    for (uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x; t0 < nn; t0 += kAhead * step) {
+    for (uint32_t b0 = blockIdx.x * blockDim.x; b0 < nn; b0 += kAhead * step) {  // whole blocks
         double x[kAhead];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) x[k] = e[min(t0 + k * step, nn - 1)];  // the last entry is a node's own
+        for (int k = 0; k < kAhead; ++k) x[k] = e[min(b0 + threadIdx.x + k * step, nn - 1)];
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
-            const uint32_t t = min(t0 + k * step, nn - 1);
+            const uint32_t t = b0 + threadIdx.x + k * step;
+            const double right = __shfl_down(x[k], 1);
+            if (t >= nn) continue;
             if (!(x[k] >= 0.0) || !(x[k] < __builtin_huge_val())) {
                 atomicMin(&state->bad, (int32_t)t);
             } else if (t % (uint32_t)(n + 1) != 0) {  // not a node's own entry
                 lo = fmin(lo, fabs(x[k]));
                 hi = fmax(hi, fabs(x[k]));
+                same += wave_lane() < kWave - 1 && t + 1 < nn && x[k] == right;
             }
         }
     }
@@ -190,10 +205,12 @@ __global__ __launch_bounds__(256) void islands_check(int n, const double *__rest
     for (int off = kWave / 2; off > 0; off >>= 1) {
         lo = fmin(lo, __shfl_xor(lo, off));
         hi = fmax(hi, __shfl_xor(hi, off));
+        same += __shfl_xor(same, off);
     }
     if (wave_lane() == 0) {
         wlo[threadIdx.x / kWave] = lo;
         whi[threadIdx.x / kWave] = hi;
+        wsame[threadIdx.x / kWave] = same;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -201,6 +218,7 @@ __global__ __launch_bounds__(256) void islands_check(int n, const double *__rest
         for (int w = 1; w < 256 / kWave; ++w) {
             lo = fmin(lo, wlo[w]);
             hi = fmax(hi, whi[w]);
+            same += wsame[w];
         }
         // non-negative: the bits order like the values; a plain look first, so
         // that few blocks update
@@ -210,6 +228,7 @@ __global__ __launch_bounds__(256) void islands_check(int n, const double *__rest
             atomicMin(&state->least, l);
         if (h > __hip_atomic_load(&state->most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             atomicMax(&state->most, h);
+        if (same) atomicAdd(&state->same, same);
     }
 }
 
@@ -229,7 +248,7 @@ __global__ __launch_bounds__(kGroupThreads) void islands_groups(int n, const int
                                                                 const double *__restrict__ val, double eps_c,
                                                                 double eps_m, double eps_i, int32_t *grp,
                                                                 int32_t *gstart, int32_t *gnodes, int32_t *ngroups,
-                                                                int32_t *lq, int64_t *goff) {
+                                                                int32_t *lq, int64_t *goff, IslandState *state) {
     __shared__ int32_t ord[kMaxNodes];
     __shared__ int32_t g[kMaxNodes];
     __shared__ double x[kMaxNodes];
@@ -316,13 +335,15 @@ __global__ __launch_bounds__(kGroupThreads) void islands_groups(int n, const int
     __syncthreads();
     if (threadIdx.x == 0) {
         *ngroups = G;
-        int64_t off = 0;
+        int64_t off = 0, most = 0;
         for (int gg = 0; gg < G; ++gg) {
             goff[gg] = off;
             const int64_t nm = gs[gg + 1] - gs[gg];
             off += nm * nm;
+            most = max(most, nm);
         }
         goff[G] = off;
+        state->group = (int32_t)most;
     }
     for (int gg = threadIdx.x; gg <= G; gg += blockDim.x) gstart[gg] = gs[gg];
     for (int t = threadIdx.x; t < n; t += blockDim.x) {
@@ -1032,13 +1053,16 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
     hipError_t e = hipMemcpyAsync(w.gpus, hg.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w.val, hv.data(), 8 * 4 * (size_t)n, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(w.e, e_host, 8 * (size_t)n * n, hipMemcpyHostToDevice, s);
-    IslandState state{0, INT32_MAX, 0x7FF0000000000000ull, 0};
+    IslandState state{0, INT32_MAX, 0, 0, 0x7FF0000000000000ull, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(w.state, &state, sizeof(state), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     const int64_t nn = (int64_t)n * n;
     // a block's two updates of the state go one after the other: 2048 blocks took
     // 22 us over 1024 nodes
     islands_check<<<dim3((unsigned)std::min<int64_t>((nn + 255) / 256, 256)), dim3(256), 0, s>>>(n, w.e, w.state);
+    islands_groups<<<dim3(1), dim3(kGroupThreads), 0, s>>>(n, w.gpus, w.val, eps_c, eps_m, eps_i, w.grp, w.gstart,
+                                                           w.gnodes, w.ngroups, w.lq, w.goff,
+                                                           w.state);
     e = hipMemcpyAsync(&state, w.state, sizeof(state), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host staging arrays go away
     if (e != hipSuccess) return e;
@@ -1047,9 +1071,8 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
     double least, most;
     std::memcpy(&least, &state.least, 8);
     std::memcpy(&most, &state.most, 8);
-    const int first = n < kStagedNodes || least > kStageShare[0] * most ? kStages - 1 : 0;
-    islands_groups<<<dim3(1), dim3(kGroupThreads), 0, s>>>(n, w.gpus, w.val, eps_c, eps_m, eps_i, w.grp, w.gstart,
-                                                           w.gnodes, w.ngroups, w.lq, w.goff);
+    const int staged = 2 * (int64_t)state.same >= nn ? kStagedNodes : kStagedOdd;
+    const int first = state.group < staged || least > kStageShare[0] * most ? kStages - 1 : 0;
     const dim3 pairs((unsigned)((nn + 255) / 256));
     islands_link_init<<<pairs, dim3(256), 0, s>>>(n, w.e, w.grp, w.gstart, w.lq, w.goff, w.L, w.M, w.XT, w.inown,
                                                   w.pos, w.cl, w.uf);
@@ -1078,11 +1101,11 @@ hipError_t launch_build_islands(int n, const tg_island *nodes_host, const double
                                                         w.M, w.XT, w.inown, w.pos, w.nxl, w.outv, w.cl,
                                                         &w.state->err);
         };
-        if (first == kStages - 1 && n > kOneSmall) {
+        if (last && state.group > kOneSmall) {
             merge(Int<kMergeThreads>{}, Int<2>{}, Int<kMaxNodes>{});
         } else {
             merge(Int<kSmallThreads>{}, Int<2>{}, Int<kSmallComp>{});
-            if (n > kSmallComp) merge(Int<kMergeThreads>{}, Int<kSmallComp + 1>{}, Int<kMaxNodes>{});
+            if (state.group > kSmallComp) merge(Int<kMergeThreads>{}, Int<kSmallComp + 1>{}, Int<kMaxNodes>{});
         }
     }
     islands_number<<<dim3(1), dim3(1024), 0, s>>>(n, w.cl, w.gpus, w.val, w.island_of, w.out_k, w.isl_gpus,

@@ -159,15 +159,17 @@ def test_islands_one_link_speed(bw):
     same(T.build_islands(c), oracle_islands(c))
 
 
-# one launch over whole groups: fewer than 16 nodes (levels 4:1), or every link
-# above half the fastest; and just outside both
-@pytest.mark.parametrize("n", [2, 3, 15, 16, 17, 32, 33, 64, 65, 130])
-@pytest.mark.parametrize("fab", ["levels", "flat", "above_half", "half"])
+# one launch over whole groups: a largest group of fewer than 16 nodes (levels 4:1),
+# of fewer than 48 (54 nodes) where links were measured one by one, or every link
+# above half the fastest; and just outside each
+@pytest.mark.parametrize("n", [2, 3, 15, 16, 17, 32, 33, 54, 55, 64, 65, 130])
+@pytest.mark.parametrize("fab", ["levels", "odd", "flat", "above_half", "half"])
 def test_islands_one_launch_or_stages(n, fab):
     say("one launch", n, fab)
     rng = np.random.default_rng([n, len(fab)])
     u = np.arange(n)
-    e = {"levels": np.where(u[:, None] // 4 == u // 4, 400e9, np.where(u[:, None] // 12 == u // 12, 100e9, 25e9)),
+    levels = np.where(u[:, None] // 4 == u // 4, 400e9, np.where(u[:, None] // 12 == u // 12, 100e9, 25e9))
+    e = {"levels": levels, "odd": np.round(levels * rng.uniform(0.98, 1.02, (n, n)), -3),
          "flat": np.full((n, n), 25e9) * rng.uniform(0.98, 1.02, (n, n)),
          "above_half": np.where(u[:, None] // 4 == u // 4, 50e9, 25.001e9),
          "half": np.where(u[:, None] // 4 == u // 4, 50e9, 25e9)}[fab].astype(float)
